@@ -684,8 +684,8 @@ def main():
                    "cell, line and traced ray; whole-configuration time and q_rad wall-point solves/s are "
                    "EXTRAPOLATED from the slice (x%d in points, accumulation by exact term counts)"
                    % (SLICE_RANGES, RANGE_POINTS, int(round(ratio))),
-                   "precision": "fp32 profile evaluation, per-point sums over 64-line blocks merged with Kahan "
-                   "compensation; populations, widths, windows, march state and quadrature in f64",
+                   "precision": "fp32 profile evaluation (wings at nodes of 64- to 512-point intervals), sums of at most 64 terms "
+                   "merged in f64; populations, widths, windows, march state and quadrature in f64",
                    "cells": sz["n_cells"], "lines": wl.lines.n, "grid_points": sz["n_points"],
                    "slice_ranges": [[int(a), int(b)] for a, b in zip(kf, npt)],
                    "traced_rays": sz["n_rays"], "wall_points": sz["n_wall"], "segments": n_seg,

@@ -55,8 +55,10 @@ typedef enum {
     LRT_FP64 = 0,       /* every step in double precision */
     LRT_FP32_COMP = 1   /* populations, widths, windows and quadrature in double;
                            profile evaluation in single precision; at each grid
-                           point lines are summed in blocks of 64 whose partials
-                           are merged with Kahan's compensation; eta/kappa stored
+                           point (or, away from a line's centre, at each node of
+                           a polynomial through a stretch of the grid, within
+                           1e-8 of the profile) at most 64 terms are added
+                           before they are merged in double; eta/kappa stored
                            as float with a per-cell power-of-two scale */
 } lrt_precision;
 

@@ -31,6 +31,8 @@
 
 #include "lrt_device.h"
 #include "lrt_internal.h"
+#include "lrt_math.h"
+#include "lrt_nodes.h"
 
 namespace lrt {
 
@@ -166,11 +168,19 @@ __device__ __forceinline__ const double *cr_row(const DevLines &L, int c)
     return L.lev ? L.lnd + (int64_t)c * L.lnd_stride : nullptr;
 }
 
+// a[i0 + t], i0 the same for the whole wave: a scalar base and a 32-bit offset.
+template <typename T>
+__device__ __forceinline__ T line_at(const T *a, int64_t i0, uint32_t t)
+{
+    return *(const T *)((const char *)(a + i0) + t * (uint32_t)sizeof(T));
+}
+
+// Line i0 + t of the list, i0 the same for the whole wave.
 __device__ __forceinline__ bool pair_setup(const DevLines &L, const DevGrid &g, const CellConst &k,
-                                           const CellSpecies *csc, const double *lnd_c, int64_t i,
+                                           const CellSpecies *csc, const double *lnd_c, int64_t i0, uint32_t t,
                                            PairF64 &p)
 {
-    const int s = L.species[i];
+    const int s = line_at(L.species, i0, t);
     const CellSpecies q = csc[s];
     if (!(q.lnNQ > -INFINITY)) {
         p.klo = p.kclo = 1;
@@ -178,45 +188,55 @@ __device__ __forceinline__ bool pair_setup(const DevLines &L, const DevGrid &g, 
         p.se = p.sk = p.inv2g = p.r = 0.0;
         return false;
     }
-    const double nu0 = L.nu0[i];
-    const double Eu_ev = L.Eu_ev[i], Eu_rot = L.Eu_rot[i];
-    const double El_ev = L.El_ev[i], El_rot = L.El_rot[i];
-    const double base = q.lnNQ + L.lngu[i];
+    const double nu0 = line_at(L.nu0, i0, t);
+    const double Eu_ev = line_at(L.Eu_ev, i0, t), Eu_rot = line_at(L.Eu_rot, i0, t);
+    const double El_ev = line_at(L.El_ev, i0, t), El_rot = line_at(L.El_rot, i0, t);
+    const double base = q.lnNQ + line_at(L.lngu, i0, t);
     // N_u = N g_u e^{-E_u}/Q, and N_l g_u/g_l = N_u e^{x} with x the line's
     // reduced energy, so N_l (g_u/g_l)(1 - e^{-x}) = N_u (e^{x} - 1)
     const double lnNu = base - k.beta_v * Eu_ev - k.beta_tr * Eu_rot;
     const double x = k.beta_v * (Eu_ev - El_ev) + k.beta_tr * (Eu_rot - El_rot);
-    const int32_t lv = lnd_c ? L.lev[i] : -1;
+    const int32_t lv = lnd_c ? line_at(L.lev, i0, t) : -1;
     double Nu, Nlx;
     if (lv < 0) {
-        Nu = exp(lnNu);
-        // (the two-factor form only while N_u e^{x} stays representable)
-        Nlx = (lnNu > -700.0 && x < 700.0) ? Nu * expm1(x) : exp(lnNu + x) * (-expm1(-x));
+        if (fabs(lnNu) < 700.0 && fabs(x) < 700.0) {
+            const ExpParts e = exp_parts(lnNu);
+            Nu = exp_of(e);
+            Nlx = Nu * expm1_of(exp_parts(x));
+        } else {
+            // (the two-factor form only while N_u e^{x} stays representable)
+            Nu = exp_any(lnNu);
+            Nlx = (lnNu > -700.0 && x < 700.0) ? Nu * expm1_any(x) : exp_any(lnNu + x) * (-expm1_any(-x));
+        }
     } else {
         // QSS-CR populations: both levels carry their departure from
         // Boltzmann, N_u = e^{lu}, N_l g_u/g_l = e^{ll}, and the absorption
         // takes N_l g_u/g_l - N_u (negative for an inverted pair)
         const double lu = lnNu + lnd_c[lv & 0xffff];
         const double ll = lnNu + x + lnd_c[lv >> 16];
-        Nu = exp(lu);
-        Nlx = (ll >= lu) ? (ll > -INFINITY ? exp(ll) * -expm1(lu - ll) : 0.0) : -(Nu * -expm1(ll - lu));
+        Nu = exp_any(lu);
+        Nlx = (ll >= lu) ? (ll > -INFINITY ? exp_any(ll) * -expm1_any(lu - ll) : 0.0) : Nu * expm1_any(ll - lu);
     }
-    const double Seta = L.seta0[i] * Nu;
-    const double Skap = L.skap0[i] * Nlx;
+    const double Seta = line_at(L.seta0, i0, t) * Nu;
+    const double Skap = line_at(L.skap0, i0, t) * Nlx;
     // widths (Sec. 2.2.1): Doppler, Lorentz, Voigt (Olivero fit)
     const double gG = q.dop * nu0;
-    const double gL = L.gN[i] + L.gS[i] * k.gL + q.gW;
-    const double sum = gL + gG;
-    const double d = (gL - gG) / sum;
-    const double gV = (1.0 - 0.18121 * (1.0 - d * d)
-                       - (0.023665 * exp(0.6 * d) + 0.00418 * exp(-1.9 * d)) * sinpi(d)) * sum;
-    const double inv_gV = 1.0 / gV;
+    const double gL = line_at(L.gN, i0, t) + line_at(L.gS, i0, t) * k.gL + q.gW;
+    const double gV = voigt_hwhm(gL, gG, rcp_f64(gL + gG));
+    const double inv_gV = rcp_f64(gV);
     const double r = gL * inv_gV;
-    const double norm = (0.5 * inv_gV) / (1.065 + 0.447 * r + 0.058 * r * r);
-    // window |nu_k - nu0| <= 100 gamma_V; rounding-exact operation order
+    const double norm = 0.5 * inv_gV * rcp_f64(1.065 + 0.447 * r + 0.058 * r * r);
+    // window |nu_k - nu0| <= 100 gamma_V; rounding-exact operation order.  The
+    // product by 1/h gives the same bound as the division unless it lies within
+    // its own rounding (below 1e-6 on grids of up to 2^31 points) of an integer.
     const double W = __dmul_rn(100.0, gV);
-    double lo = ceil(__ddiv_rn(__dsub_rn(__dsub_rn(nu0, W), g.nu_min), g.h));
-    double hi = floor(__ddiv_rn(__dsub_rn(__dadd_rn(nu0, W), g.nu_min), g.h));
+    const double dlo = __dsub_rn(__dsub_rn(nu0, W), g.nu_min), dhi = __dsub_rn(__dadd_rn(nu0, W), g.nu_min);
+    const double qlo = dlo * g.inv_h, qhi = dhi * g.inv_h;
+    double lo = ceil(qlo), hi = floor(qhi);
+    if (fabs(qlo - rint(qlo)) < 1e-5 || fabs(qhi - rint(qhi)) < 1e-5) {
+        lo = ceil(__ddiv_rn(dlo, g.h));
+        hi = floor(__ddiv_rn(dhi, g.h));
+    }
     lo = fmax(lo, 0.0);
     hi = fmin(hi, (double)(g.n_points - 1));
     if (lo > hi) {
@@ -359,8 +379,16 @@ __global__ void ranges_kernel(DevLines L, DevGrid g, const CellConst *cc, int32_
     const int32_t kb = min(k_first + n_band, ka + tile_points) - 1;
     const double nu_a = g.nu_min + (double)ka * g.h - g.h;
     const double nu_b = g.nu_min + (double)kb * g.h + g.h;
-    const double lo = (nu_a - k.cand_G) / (1.0 + k.cand_A);
-    const double hi = (nu_b + k.cand_G) / (1.0 - k.cand_A);
+    double lo = (nu_a - k.cand_G) / (1.0 + k.cand_A);
+    double hi = (nu_b + k.cand_G) / (1.0 - k.cand_A);
+    // Within those the window is at most the Voigt width of the largest Lorentz
+    // width and the Doppler width at the last of their centres (the fit grows
+    // with both), up to 18 % less than the sum of the two.
+    if (hi > 0.0) {
+        const double W = voigt_hwhm(k.cand_G, k.cand_A * hi, 1.0 / (k.cand_G + k.cand_A * hi));
+        lo = fmax(lo, nu_a - W);
+        hi = fmin(hi, nu_b + W);
+    }
     int2 r;
     r.x = (int)lower_bound_dev(L.nu0, L.n, lo);
     r.y = (int)lower_bound_dev(L.nu0, L.n, hi);
@@ -370,32 +398,6 @@ __global__ void ranges_kernel(DevLines L, DevGrid g, const CellConst *cc, int32_
 // ---------------------------------------------------------------------------
 // per-cell power-of-two scale for the single-precision form
 // ---------------------------------------------------------------------------
-
-__global__ void scale_kernel(DevLines L, int64_t i0, int64_t i1, DevGrid g, const CellConst *cc,
-                             const CellSpecies *cs, int32_t n_cells, int32_t n_species,
-                             int32_t *emax)
-{
-    const int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int c = blockIdx.y; c < n_cells; c += gridDim.y) {
-        int ee = INT_MIN, ek = INT_MIN;
-        if (i < i1) {
-            PairF64 p;
-            if (pair_setup(L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), i, p)) {
-                if (p.se != 0.0) ee = ilogb(p.se) + 1;
-                if (p.sk != 0.0) ek = ilogb(fabs(p.sk)) + 1;
-            }
-        }
-        // wave max, then one atomic per wave (max is order independent)
-        for (int o = 32; o > 0; o >>= 1) {
-            ee = max(ee, __shfl_xor(ee, o));
-            ek = max(ek, __shfl_xor(ek, o));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            if (ee != INT_MIN) atomicMax(&emax[2 * c + 0], ee);
-            if (ek != INT_MIN) atomicMax(&emax[2 * c + 1], ek);
-        }
-    }
-}
 
 // Per-cell scale from the level-energy bins: one wave per cell takes the
 // largest upper bound of ln(eta peak) and ln(|kappa peak|) over the bins.
@@ -461,17 +463,6 @@ __global__ void scale_bound_kernel(DevBins B, const CellConst *cc, const CellSpe
     }
 }
 
-__global__ void scale_finish_kernel(const int32_t *emax, const double *cont_lnb, int32_t n, int32_t *escale)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    int e = emax[t];
-    if (cont_lnb && cont_lnb[t] > -INFINITY)   // the atomic continuum's own bound: peak < 2^e
-        e = max(e, (int)fmax(-2000.0, fmin(2000.0, ceil(cont_lnb[t] * kLog2e) + 1.0)));
-    // keep values unscaled while the largest line peak stays within 2^+-60
-    escale[t] = (e == INT_MIN || (e >= -60 && e <= 60)) ? 0 : e;
-}
-
 // ---------------------------------------------------------------------------
 // a3: line-to-grid accumulation
 // ---------------------------------------------------------------------------
@@ -479,28 +470,19 @@ __global__ void scale_finish_kernel(const int32_t *emax, const double *cont_lnb,
 // Single-precision line record staged in LDS.  Grid indices inside the
 // kernel are relative to the tile start, so every float index is a small
 // exact integer whatever the grid size.
-//
-// `mode` holds three masks over the tile's 64-point slices (slice s = points
-// 64s..64s+63, bit s of each byte): bits 0-7 "window reaches the slice",
-// bits 8-15 "window edge inside the slice (mask lanes)", bits 16-23 "core
-// window reaches the slice (exponential terms)".  Decided once at staging; a
-// wave turns the bits of its own slices, over a block of lines, into scalar
-// bit masks and needs no vector work for control flow.
-constexpr int kSlices = kTilePoints / 64;
-struct __align__(16) RecF32 {
+struct __align__(16) RecPos {
     float k0f, hg, fg, qw;          // centre index (tile-relative), h/gV, frac0/gV, 0.016 r (1-r) / s
-    float qg, pad0, se, sk;         // (1-r) / s, -, strengths times s and the cell's scale
-    float klo, khi;                 // window, tile-relative, clamped to [-1, tile] (edge masks)
-    uint32_t mode, pad;
 };
-static_assert(kSlices <= 8 && kPPL <= 2, "mode masks hold at most 8 slices per tile");
-
-// Slices of the tile overlapped by [lo, hi] (tile-relative, possibly beyond
-// the tile): a contiguous run of bits.
+struct __align__(16) RecAmp {
+    float se, sk, qg;               // strengths times s and the cell's scale; (1-r) / s
+    uint32_t edges;                 // window, tile-relative, clamped to [-1, tile]: klo | khi << 16 (edge masks)
+};
+// Slices of the double-precision tile overlapped by [lo, hi] (tile-relative,
+// possibly beyond the tile): a contiguous run of bits.
 __device__ __forceinline__ uint32_t slice_run(int32_t lo, int32_t hi)
 {
-    if (lo > hi || hi < 0 || lo > kTilePoints - 1) return 0u;
-    const int32_t a = max(lo, 0) >> 6, b = min(hi, kTilePoints - 1) >> 6;
+    if (lo > hi || hi < 0 || lo > kTileF64 - 1) return 0u;
+    const int32_t a = max(lo, 0) >> 6, b = min(hi, kTileF64 - 1) >> 6;
     return (2u << b) - (1u << a);
 }
 
@@ -511,7 +493,7 @@ __device__ __forceinline__ uint32_t slice_modes(int32_t klo, int32_t khi, int32_
     // a slice holds a window edge when the window starts or ends strictly inside it
     uint32_t edge = 0u;
     if (klo >= 0 && (klo & 63) != 0) edge |= 1u << min(klo >> 6, 31);
-    if (khi < kTilePoints && (khi & 63) != 63 && khi >= 0) edge |= 1u << min(khi >> 6, 31);
+    if (khi < kTileF64 && (khi & 63) != 63 && khi >= 0) edge |= 1u << min(khi >> 6, 31);
     const uint32_t core = slice_run(max(kclo, klo), min(kchi, khi));
     return in | ((edge & in) << 8) | ((core & in) << 16);
 }
@@ -525,6 +507,8 @@ struct __align__(16) RecF64 {
 // The Whiting profile is evaluated in y = (nu_k - nu0) / gamma_V = +-2x, so that
 // 1 + 4x^2 = 1 + y^2 is one FMA and x^2.25 = 2^-2.25 |y|^2.25.
 constexpr double kTwoM225 = 0.21022410381342863;   // 2^-2.25
+
+__device__ const NodeBasis kBasis{};
 
 // Constants of the single-precision profile.  The kernels set them once,
 // outside their loops, and an empty asm keeps them in scalar registers: VOP3
@@ -553,7 +537,7 @@ __device__ __forceinline__ ShapeConsts shape_consts()
 // adds a Lorentzian of at most kRScaleMin of the line's own peak.  (Two
 // reciprocals save instructions but measured 4 % slower: the transcendental
 // pipe, not the instruction count, then sets the pace.)
-__device__ __forceinline__ float shape_rational_f32(float kf, const RecF32 &q, const ShapeConsts &K, float &d1,
+__device__ __forceinline__ float shape_rational_f32(float kf, const RecPos &q, const ShapeConsts &K, float &d1,
                                                     float &p)
 {
     const float y = fmaf(kf - q.k0f, q.hg, -q.fg);
@@ -568,12 +552,16 @@ __device__ __forceinline__ float shape_rational_f32(float kf, const RecF32 &q, c
 constexpr double kRScaleMin = 9.094947017729282e-13;
 
 // Exponential part [(1-r) e^{-2.772 x^2} + 0.016 r(1-r) e^{-0.4 x^2.25}] / s
-// added to P, with x^2 = (d1 - 1)/4 folded into the exponent's FMA.
-__device__ __forceinline__ float shape_exp_f32(const RecF32 &q, const ShapeConsts &K, float d1, float p, float P)
+// added to P, with x^2 = (d1 - 1)/4 folded into the exponent's FMA; wexp_f32
+// adds the second term alone.
+__device__ __forceinline__ float wexp_f32(float qw, const ShapeConsts &K, float p, float P)
+{
+    return fmaf(qw, __builtin_amdgcn_exp2f(p * K.ce), P);
+}
+__device__ __forceinline__ float shape_exp_f32(float qw, float qg, const ShapeConsts &K, float d1, float p, float P)
 {
     const float gs = __builtin_amdgcn_exp2f(fmaf(d1, K.cg, -K.cg));
-    const float e = __builtin_amdgcn_exp2f(p * K.ce);
-    return fmaf(q.qg, gs, fmaf(q.qw, e, P));
+    return fmaf(qg, gs, wexp_f32(qw, K, p, P));
 }
 
 // Block -> (tile, cell) order of the accumulation grid: groups of 8 tiles x
@@ -598,15 +586,6 @@ __device__ __forceinline__ void block_tile_cell(uint32_t b, int32_t n_cells, int
     }
 }
 
-// Compensated (Kahan) addition of a block partial v into (s, c).
-__device__ __forceinline__ void kahan_add(float &s, float &c, float v)
-{
-    const float y = v - c;
-    const float t = s + y;
-    c = (t - s) - y;
-    s = t;
-}
-
 // Square root of x > 0 from the hardware reciprocal square root (about 5e-8
 // relative) and one Newton step on y^2 = x.  Measured on the chip, the fourth
 // root as two such steps stays within 4.2e-15 relative of x^(1/4) over
@@ -618,24 +597,42 @@ __device__ __forceinline__ double sqrt_newton(double x)
     return fma(fma(-y, y, x), 0.5 * r, y);
 }
 
-// Lines per compensated block: partials of at most kBlock terms are added
-// plainly, blocks are merged with Kahan's compensation (64-line blocks
-// measured 1 % faster than 32-line ones).  A block is one ballot mask: one bit
-// per line.
+// Lines per block: partials of at most kBlock terms are added plainly in single
+// precision, blocks are merged in double precision.  A block is one ballot
+// mask: one bit per line.
 constexpr int kBlock = 64;
 using BlockMask = uint64_t;
+
+#ifndef LRT_NODE_LINES
+#define LRT_NODE_LINES 128
+#endif
+constexpr int kNodeLines = LRT_NODE_LINES;
+
+// Shared memory of the single-precision accumulation: the staged lines of a
+// round, and per wave the node sums of its intervals (its two 64-point ones,
+// then one of each larger size, shared with the other waves under it).
+constexpr int kSets = kPPL + kLevels - 1;
+struct AccumLds {
+    RecPos pos[kStage];
+    RecAmp amp[kStage];
+    RecMode mode[kStage];
+    uint32_t any[kStage / kBlock];   // per block of lines, of any line: its slices | its intervals << 8
+    double node[kAccumThreads / 64][kSets][2][kNodes];
+};
 
 // The terms of one staged line (bit t of the block masks) on this wave's
 // slices, added to the block partials.
 template <typename Mask>
-__device__ __forceinline__ void line_terms(const RecF32 &qr, int t, const float (&kf)[kPPL], const ShapeConsts &K,
-                                           const Mask (&m_in)[kPPL], const Mask (&m_core)[kPPL],
-                                           const Mask (&m_edge)[kPPL], float (&ae)[kPPL], float (&ak)[kPPL])
+__device__ __forceinline__ void line_terms(const RecPos &qr, const RecAmp &ar, int t, const float (&kf)[kPPL],
+                                           const ShapeConsts &K, const Mask (&m_in)[kPPL],
+                                           const Mask (&m_core)[kPPL], const Mask (&m_edge)[kPPL],
+                                           float (&ae)[kPPL], float (&ak)[kPPL])
 {
-    const RecF32 q = qr;
+    const RecPos q = qr;
+    const RecAmp a = ar;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        if (!((m_in[j] >> t) & 1u)) continue;      // slice outside the window
+        if (!((m_in[j] >> t) & 1u)) continue;      // slice outside the window, or at nodes
         float d1, pw;
         float P = shape_rational_f32(kf[j], q, K, d1, pw);
         // Within kCoreHalfWidth gamma_V of the centre the exponentials
@@ -644,87 +641,201 @@ __device__ __forceinline__ void line_terms(const RecF32 &qr, int t, const float 
         // scalar branches instead of computing both sides and selecting.
         if ((m_core[j] >> t) & 1u) {
             asm volatile("");
-            P = shape_exp_f32(q, K, d1, pw, P);
+            P = shape_exp_f32(q.qw, a.qg, K, d1, pw, P);
         }
         // slice crossing a window edge: mask the lanes outside
         if ((m_edge[j] >> t) & 1u) {
             asm volatile("");
-            P = (kf[j] >= q.klo && kf[j] <= q.khi) ? P : 0.0f;
+            P = (kf[j] >= (float)(int16_t)(a.edges & 0xffffu) && kf[j] <= (float)((int32_t)a.edges >> 16)) ? P : 0.0f;
         }
-        ae[j] = fmaf(P, q.se, ae[j]);
-        ak[j] = fmaf(P, q.sk, ak[j]);
+        ae[j] = fmaf(P, a.se, ae[j]);
+        ak[j] = fmaf(P, a.sk, ak[j]);
     }
+}
+
+// The terms of a block's lines (mask m, those with the exponential mw) at the
+// nodes of one interval, added to the lane's sums.  The wave takes four lines
+// at a time, sixteen lanes to a line, each lane at its node x (tile-relative):
+// the records of four consecutive lines are read from one base address, and a
+// lane whose line has no bit adds zero.  (The lines an interval takes lie in
+// two runs of the sorted list, so few of the four are idle.)
+__device__ __forceinline__ void node_terms(const RecPos *pos, const RecAmp *amp, BlockMask m, BlockMask mw, float x,
+                                           uint32_t grp, const ShapeConsts &K, float &ae, float &ak)
+{
+    uint32_t off = grp * 16u;
+    const uint64_t mine = m >> grp;
+    // 32 lines at a time: constant bit positions in 32-bit halves
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t mh = (uint32_t)(m >> (32 * h)), wh = (uint32_t)(mw >> (32 * h));
+        if (mh == 0) continue;
+        const uint32_t mi = (uint32_t)(mine >> (32 * h));
+        asm volatile("" : "+v"(off));
+        const char *pb = (const char *)pos + off, *ab = (const char *)amp + off;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            if (((mh >> (4 * g)) & 15u) == 0) continue;
+            const RecPos q = *(const RecPos *)(pb + (32 * h + 4 * g) * 16);
+            const float2 a = *(const float2 *)(ab + (32 * h + 4 * g) * 16);
+            float d1, p;
+            float P = shape_rational_f32(x, q, K, d1, p);
+            if ((wh >> (4 * g)) & 15u) {
+                asm volatile("");
+                P = wexp_f32(q.qw, K, p, P);
+            }
+            // all bits of P, or none
+            const int32_t keep = (int32_t)(mi << (31 - 4 * g)) >> 31;
+            P = __int_as_float(__float_as_int(P) & keep);
+            ae = fmaf(P, a.x, ae);
+            ak = fmaf(P, a.y, ak);
+        }
+    }
+}
+
+// The bits of any lane.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v)
+{
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast 15, 31
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_readlane(v, 63);
+}
+
+// Adds a round's sums of the four lane groups to an interval's node sums
+// (acc[0]: eta, acc[1]: kappa), in a fixed order: the halves of the wave are
+// added pairwise (its lower half then holds eta, its upper half kappa), then
+// the two groups of each half.
+__device__ __forceinline__ void node_flush(float pe, float pk, int lane, double (*acc)[kNodes])
+{
+    const uint64_t a = __double_as_longlong((double)pe), b = __double_as_longlong((double)pk);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    const double t = __longlong_as_double(((uint64_t)hi[0] << 32) | lo[0]) +
+                     __longlong_as_double(((uint64_t)hi[1] << 32) | lo[1]);
+    const uint64_t c = __double_as_longlong(t);
+    const auto l2 = __builtin_amdgcn_permlane16_swap((uint32_t)c, (uint32_t)c, false, false);
+    const auto h2 = __builtin_amdgcn_permlane16_swap((uint32_t)(c >> 32), (uint32_t)(c >> 32), false, false);
+    const double v = __longlong_as_double(((uint64_t)h2[0] << 32) | l2[0]) +
+                     __longlong_as_double(((uint64_t)h2[1] << 32) | l2[1]);
+    if ((lane & 16) == 0) acc[lane >> 5][lane & 15] += v;
 }
 
 // eta and kappa of one cell on one tile (kTilePoints points starting at the
 // global index kt) in single precision: every round stages kStage candidate
-// lines (one FP64 setup per thread) into `rec`, then each wave evaluates the
-// staged lines on its kPPL slices of 64 points.  Lanes hold the compensated sums;
-// the function returns eta[j], kappa[j] of point kt + kw + 64 j + lane (scaled
-// by 2^-ese, 2^-esk).  Must be called by the whole workgroup.
-__device__ __forceinline__ void accum_cell_tile_f32(RecF32 *rec, const DevLines &L, const DevGrid &g,
+// lines (one FP64 setup per thread) into LDS, then each wave evaluates the
+// staged lines on its kPPL slices of 64 points, point by point or at the nodes
+// of the intervals it owns: the 64-point intervals of its slices, the
+// 128-point interval they make, and of each larger one every 2^n-th block of
+// lines, shared with the other waves under it.  Lanes hold the sums in double
+// precision; the function returns eta[j], kappa[j] of point kt + kw + 64 j +
+// lane (scaled by 2^-ese, 2^-esk).  Must be called by the whole workgroup.
+__device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines &L, const DevGrid &g,
                                                     const CellConst &k, const CellSpecies *csc,
                                                     const double *lnd_c, int ese, int esk, int2 rg, int32_t kt,
                                                     int32_t kw, int lane, float (&eta)[kPPL],
                                                     float (&kap)[kPPL])
 {
-    // first slice of this wave (kw = wave * 64 * kPPL)
-    const uint32_t wshift = (uint32_t)(kw / 64);
+    constexpr int kWaves = kAccumThreads / 64, kBlocks = kStage / kBlock;
+    static_assert(kTilePoints == 1 << kTileBits && kPPL == 2 && kWaves * kPPL == kSlices && kBlocks == 4,
+                  "a wave owns the two halves of a 128-point interval");
+    const uint32_t wave = (uint32_t)(kw / (64 * kPPL));
+    const uint32_t wshift = wave * kPPL;   // first slice of this wave
     const ShapeConsts K = shape_consts();
     float kf[kPPL];
-    float se[kPPL], ce[kPPL], sk[kPPL], ck[kPPL], ae[kPPL], ak[kPPL];
+    float ae[kPPL], ak[kPPL];
+    double se[kPPL], sk[kPPL];
+    // A tile with few lines is summed point by point: below kNodeLines candidate
+    // lines the interpolation at the end costs more than the nodes save (131
+    // cells, 6,000 lines on 100,003 points, 30 to 60 lines a tile: 776 us per
+    // solve with a bound of 64, 727 with 128, the same up to 512).
+    const bool at_nodes = rg.y - rg.x >= kNodeLines;
+    double (*acc)[2][kNodes] = sm.node[wave];
+    float x64 = 0.0f;
+    if (at_nodes) {
+        for (int j = lane; j < kSets * 2 * kNodes; j += 64) (&acc[0][0][0])[j] = 0.0;
+#pragma unroll
+        for (int i = 0; i < kNodes; ++i)
+            if ((lane & 15) == i) x64 = (float)kNodePos[i];
+    }
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         kf[j] = (float)(kw + 64 * j + lane);
         asm volatile("" : "+v"(kf[j]));   // keep the float index in a register
-        se[j] = ce[j] = sk[j] = ck[j] = ae[j] = ak[j] = 0.0f;
+        se[j] = sk[j] = 0.0;
+        ae[j] = ak[j] = 0.0f;
     }
-
     for (int base = rg.x; base < rg.y; base += kStage) {
         // stage: one (cell, line) setup per thread, in double precision
-        const int64_t i = (int64_t)base + threadIdx.x;
-        RecF32 rr;
-        rr.mode = 0;
-        rr.klo = 1.0f;
-        rr.khi = 0.0f;
-        rr.k0f = rr.hg = rr.fg = rr.qw = rr.qg = rr.pad0 = rr.se = rr.sk = 0.0f;
-        rr.pad = 0;
-        if (i < rg.y) {
+        RecPos rp;
+        RecAmp ra;
+        RecMode rm;
+        rp.k0f = rp.hg = rp.fg = rp.qw = ra.se = ra.sk = ra.qg = 0.0f;
+        ra.edges = rm.pt = rm.node = 0u;
+        const int n = rg.y - base;   // lines left
+        // (opaque, so that no per-lane line pointers are kept across the rounds)
+        uint32_t t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        if ((int)t < n) {
             PairF64 p;
-            if (pair_setup(L, g, k, csc, lnd_c, i, p)) {
+            if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
-                rr.mode = slice_modes(lo, hi, p.kclo - kt, p.kchi - kt);
-                // small exact integers in float: the lanes compare their float index
-                rr.klo = (float)max(lo, -1);
-                rr.khi = (float)min(hi, kTilePoints);
-                rr.k0f = (float)(L.k0[i] - kt);
-                rr.hg = (float)(2.0 * g.h * p.inv2g);
-                rr.fg = (float)(2.0 * L.frac0[i] * p.inv2g);
+                const double frac0 = line_at(L.frac0, base, t);
+                const int32_t k0 = line_at(L.k0, base, t) - kt;
+                rp.k0f = (float)k0;
+                rp.hg = (float)(2.0 * g.h * p.inv2g);
+                rp.fg = (float)(2.0 * frac0 * p.inv2g);
                 // profile divided by s = r, strengths times s
-                const double sc = fmax(p.r, kRScaleMin), isc = 1.0 / sc;
-                rr.qw = (float)(0.016 * p.r * (1.0 - p.r) * isc);
-                rr.qg = (float)((1.0 - p.r) * isc);
-                rr.se = (float)ldexp(p.se * sc, -ese);
-                rr.sk = (float)ldexp(p.sk * sc, -esk);
+                const double sc = fmax(p.r, kRScaleMin), isc = rcp_f64(sc);
+                rp.qw = (float)(0.016 * p.r * (1.0 - p.r) * isc);
+                ra.qg = (float)((1.0 - p.r) * isc);
+                ra.se = (float)ldexp(p.se * sc, -ese);
+                ra.sk = (float)ldexp(p.sk * sc, -esk);
+                // small integers: the lanes compare their float index
+                ra.edges = ((uint32_t)max(lo, -1) & 0xffffu) | ((uint32_t)min(hi, kTilePoints) << 16);
+                // gamma_V, the two reaches and the centre in grid steps, the reaches
+                // rounded up and the centre down with a step of margin (k0 is
+                // clamped on very long grids, so the centre includes frac0)
+                const float gs = __builtin_amdgcn_rcpf(rp.hg);
+                const float yG = __builtin_amdgcn_sqrtf(37.0f - __builtin_amdgcn_logf((float)sc));
+                const float cf = floorf(fmaf(rp.fg, gs, rp.k0f));
+                rm = line_modes(lo, hi, (int32_t)fmaxf(-1e9f, fminf(cf, 1e9f)) - 1,
+                                (int32_t)fminf(yG * gs, 1.1e9f) + 2,
+                                (int32_t)fminf((float)kCoreHalfWidth * gs, 1.1e9f) + 2, at_nodes);
             }
         }
-        rec[threadIdx.x] = rr;
+        sm.pos[threadIdx.x] = rp;
+        sm.amp[threadIdx.x] = ra;
+        sm.mode[threadIdx.x] = rm;
+        const uint32_t any = wave_or((rm.pt & 0xffu) | (rm.node << 16 >> 8));
+        if (lane == 0) sm.any[wave] = any;
         __syncthreads();
-        const int n = min(kStage, rg.y - base);
-        for (int l0 = 0; l0 < n; l0 += kBlock) {
-            // Control of the block's lines on this wave, as bit masks over the
-            // block in scalar registers: lane t < kBlock reads line l0 + t's
-            // mode byte, one ballot per (slice, flag).  The loop then visits
-            // only the lines that reach this wave, in line order.
-            uint32_t mb = 0;
-            if (lane < kBlock && l0 + lane < n) mb = rec[l0 + lane].mode >> wshift;
-            BlockMask todo = (BlockMask)__ballot((mb & ((1u << kPPL) - 1u)) != 0);
+        // Control of the lines on this wave, as bit masks over a block in
+        // scalar registers: lane t reads the masks of the block's line t, one
+        // ballot per (interval, flag).  The loops then visit only the blocks
+        // with a line for this wave, and of those only such lines, in line order.
+        uint32_t of[kBlocks];
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)sm.any[b]);
+        auto blocks_of = [&](uint32_t bits) {
+            uint32_t m = 0u;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) m |= (of[b] & bits) ? 1u << b : 0u;
+            return m;
+        };
+#pragma unroll 1
+        for (uint32_t todo4 = blocks_of(((1u << kPPL) - 1u) << wshift); todo4; todo4 &= todo4 - 1u) {
+            const int l0 = __builtin_ctz(todo4) * kBlock;
+            const uint32_t mi = sm.mode[l0 + lane].pt >> wshift;
+            const BlockMask todo = (BlockMask)__ballot((mi & ((1u << kPPL) - 1u)) != 0);
             BlockMask m_in[kPPL], m_edge[kPPL], m_core[kPPL];
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
-                m_in[j] = (BlockMask)__ballot(mb & (1u << j));
-                m_edge[j] = (BlockMask)__ballot(mb & (1u << (8 + j)));
-                m_core[j] = (BlockMask)__ballot(mb & (1u << (16 + j)));
+                m_in[j] = (BlockMask)__ballot(mi & (1u << j));
+                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + j)));
+                m_core[j] = (BlockMask)__ballot(mi & (1u << (16 + j)));
             }
             // groups of 8 lines: within a group the LDS offsets are constants
             // from one base address held in a vector register, and the block
@@ -742,26 +853,90 @@ __device__ __forceinline__ void accum_cell_tile_f32(RecF32 *rec, const DevLines 
                 }
                 // one LDS base per group (a byte offset in a vector register),
                 // not one per line
-                uint32_t off = (uint32_t)((l0 + g8) * (int)sizeof(RecF32));
+                uint32_t off = (uint32_t)((l0 + g8) * 16);
                 asm volatile("" : "+v"(off));
-                const RecF32 *rg8 = (const RecF32 *)((const char *)rec + off);
+                const RecPos *rp8 = (const RecPos *)((const char *)sm.pos + off);
+                const RecAmp *ra8 = (const RecAmp *)((const char *)sm.amp + off);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if ((gt >> u) & 1u) line_terms(rg8[u], u, kf, K, gi, gc, ge, ae, ak);
+                    if ((gt >> u) & 1u) line_terms(rp8[u], ra8[u], u, kf, K, gi, gc, ge, ae, ak);
             }
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
-                kahan_add(se[j], ce[j], ae[j]);
-                kahan_add(sk[j], ck[j], ak[j]);
+                se[j] += (double)ae[j];
+                sk[j] += (double)ak[j];
                 ae[j] = ak[j] = 0.0f;
             }
         }
+        // Nodes, one interval after the other over the whole round (at most 64
+        // terms per lane, added plainly): the two 64-point intervals, then of
+        // level l interval wave >> (l-1), whose blocks of lines the 2^(l-1)
+        // waves under it share.
+#pragma unroll 1
+        for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
+            const int l = max(0, j - (kPPL - 1));
+            const uint32_t it = l > 0 ? wave >> (l - 1) : wshift + (uint32_t)j;
+            const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
+            uint32_t todo4 = blocks_of(bit << 8);
+            // the blocks b with b = wave (mod 2^(l-1))
+            if (l == 2) todo4 &= (wave & 1u) ? 0xau : 0x5u;
+            if (l == 3) todo4 &= 1u << wave;
+            if (todo4 == 0) continue;
+            const float w = (float)(64 << l);
+            const float x = fmaf(x64, (float)(1 << l), (float)it * w + (0.5f * w - 0.5f));
+            float pe = 0.0f, pk = 0.0f;
+#pragma unroll 1
+            for (; todo4; todo4 &= todo4 - 1u) {
+                const int l0 = __builtin_ctz(todo4) * kBlock;
+                const uint32_t nb = sm.mode[l0 + lane].node;
+                const BlockMask m = (BlockMask)__ballot((nb & bit) != 0);
+                const BlockMask mw = m & (BlockMask)__ballot((nb & wbit) != 0);
+                node_terms(sm.pos + l0, sm.amp + l0, m, mw, x, (uint32_t)lane >> 4, K, pe, pk);
+            }
+            node_flush(pe, pk, lane, acc[j]);
+        }
         __syncthreads();
+    }
+    // Node sums to the points: the waves' parts of each interval, then level by
+    // level from the whole tile down, each interval's polynomial taken at the
+    // nodes of its halves; at last at the points.
+    if (at_nodes) {
+#pragma unroll
+        for (int l = kLevels - 1; l >= 0; --l) {
+            // thread -> (interval, quantity, node)
+            const int node = threadIdx.x & 15, qy = (threadIdx.x >> 4) & 1;
+            for (int it = threadIdx.x >> 5; it < (kSlices >> l); it += kAccumThreads / 32) {
+                // the interval's sums end up with the first wave under it
+                const int w0 = l > 0 ? it << (l - 1) : it >> 1, set = l > 0 ? kPPL - 1 + l : it & 1;
+                double v = sm.node[w0][set][qy][node];
+                for (int w = 1; w < (1 << l) / 2; ++w) v += sm.node[w0 + w][set][qy][node];
+                if (l < kLevels - 1) {
+                    const double *up = sm.node[(it >> 1) << l][kPPL + l][qy];
+#pragma unroll 8
+                    for (int q = 0; q < kNodes; ++q) {
+                        const double c = (it & 1) ? kBasis.half[kNodes - 1 - q][kNodes - 1 - node] : kBasis.half[q][node];
+                        v = fma(c, up[q], v);
+                    }
+                }
+                sm.node[w0][set][qy][node] = v;
+            }
+            __syncthreads();
+        }
+#pragma unroll 8
+        for (int q = 0; q < kNodes; ++q) {
+            const double c = kBasis.pt[q][lane];
+#pragma unroll
+            for (int j = 0; j < kPPL; ++j) {
+                se[j] = fma(c, acc[j][0][q], se[j]);
+                sk[j] = fma(c, acc[j][1][q], sk[j]);
+            }
+        }
+        __syncthreads();   // the next call clears the sums
     }
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        eta[j] = se[j] - ce[j];
-        kap[j] = sk[j] - ck[j];
+        eta[j] = (float)se[j];
+        kap[j] = (float)sk[j];
     }
 }
 
@@ -771,7 +946,7 @@ void accum_f32_kernel(
     const int2 *ranges, int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band,
     int32_t n_tiles, uint32_t b0, DevCont ct, float *eta, float *kappa)
 {
-    __shared__ RecF32 rec[kStage];
+    __shared__ AccumLds sm;
     int tile, c;
     block_tile_cell(b0 + blockIdx.x, n_cells, n_tiles, tile, c);
     // the wave index is uniform across the wave: keep it (and every bound
@@ -781,7 +956,7 @@ void accum_f32_kernel(
     const int32_t kw = wave * 64 * kPPL;               // first point of the wave, tile-relative
     const int32_t kend = k_first + n_band;             // exclusive, global
     float e[kPPL], kp[kPPL];
-    accum_cell_tile_f32(rec, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), escale[2 * c + 0],
+    accum_cell_tile_f32(sm, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), escale[2 * c + 0],
                         escale[2 * c + 1], ranges[(int64_t)c * n_tiles + tile], kt, kw, lane, e, kp);
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
@@ -856,16 +1031,16 @@ __device__ __forceinline__ void line_terms_f64(const RecF64 &qr, int t, const in
 #ifndef LRT_F64_WAVES
 #define LRT_F64_WAVES 6
 #endif
-__global__ __launch_bounds__(kAccumThreads) __attribute__((amdgpu_waves_per_eu(LRT_F64_WAVES))) void accum_f64_kernel(
+__global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(LRT_F64_WAVES))) void accum_f64_kernel(
     DevLines L, DevGrid g, const CellConst *cc, const CellSpecies *cs, const int2 *ranges,
     int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band, int32_t n_tiles,
     uint32_t b0, DevCont ct, double *eta, double *kappa)
 {
-    __shared__ RecF64 rec[kStage];
+    __shared__ RecF64 rec[kThreadsF64];
     int tile, c;
     block_tile_cell(b0 + blockIdx.x, n_cells, n_tiles, tile, c);
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
-    const int32_t kt = k_first + tile * kTilePoints;
+    const int32_t kt = k_first + tile * kTileF64;
     const int32_t kw = kt + wave * 64 * kPPL;
     const int32_t kend = k_first + n_band;
     const CellConst k = cc[c];
@@ -881,27 +1056,28 @@ __global__ __launch_bounds__(kAccumThreads) __attribute__((amdgpu_waves_per_eu(L
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) kk[j] = kw + 64 * j + lane;
 
-    for (int base = rg.x; base < rg.y; base += kStage) {
-        const int64_t i = (int64_t)base + threadIdx.x;
+    for (int base = rg.x; base < rg.y; base += kThreadsF64) {
         RecF64 rr;
         rr.klo = 1;
         rr.khi = 0;
         rr.k0 = 0;
         rr.mode = 0;
         rr.frac0 = rr.inv2g = rr.r = rr.se = rr.sk = rr.pad2 = 0.0;
-        if (i < rg.y) {
+        uint32_t t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        if ((int)t < rg.y - base) {
             PairF64 p;
-            if (pair_setup(L, g, k, csc, lnd_c, i, p)) {
+            if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 rr.klo = p.klo;
                 rr.khi = p.khi;
-                rr.k0 = L.k0[i];
-                rr.frac0 = L.frac0[i];
+                rr.k0 = line_at(L.k0, base, t);
+                rr.frac0 = line_at(L.frac0, base, t);
                 rr.inv2g = p.inv2g;
                 rr.r = p.r;
                 rr.se = p.se;
                 rr.sk = p.sk;
                 // windows of the two exponentials, one point of margin each side
-                const double nu0 = L.nu0[i], gV = 0.5 / p.inv2g;
+                const double nu0 = line_at(L.nu0, base, t), gV = 0.5 / p.inv2g;
                 const double wg = kF64GaussHalfWidth * gV, ww = kF64WexpHalfWidth * gV;
                 const int32_t glo = (int32_t)fmax(ceil((nu0 - wg - g.nu_min) * g.inv_h) - 1.0, (double)p.klo);
                 const int32_t ghi = (int32_t)fmin(floor((nu0 + wg - g.nu_min) * g.inv_h) + 1.0, (double)p.khi);
@@ -914,7 +1090,7 @@ __global__ __launch_bounds__(kAccumThreads) __attribute__((amdgpu_waves_per_eu(L
         }
         rec[threadIdx.x] = rr;
         __syncthreads();
-        const int n = min(kStage, rg.y - base);
+        const int n = min(kThreadsF64, rg.y - base);
         for (int l0 = 0; l0 < n; l0 += kBlock) {
             uint32_t mb = 0;
             if (lane < kBlock && l0 + lane < n) mb = rec[l0 + lane].mode >> wshift;
@@ -977,10 +1153,11 @@ __global__ void count_kernel(DevLines L, DevGrid g, const CellConst *cc, const C
     unsigned long long n = 0, nc = 0;
     for (int c = blockIdx.y; c < n_cells; c += gridDim.y) {
         const int2 rg = band_ranges[c];
-        for (int64_t i = (int64_t)rg.x + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rg.y;
-             i += (int64_t)gridDim.x * blockDim.x) {
+        for (int64_t i0 = (int64_t)rg.x + (int64_t)blockIdx.x * blockDim.x; i0 < rg.y;
+             i0 += (int64_t)gridDim.x * blockDim.x) {
             PairF64 p;
-            if (pair_setup(L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), i, p)) {
+            if (i0 + threadIdx.x < rg.y &&
+                pair_setup(L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), i0, threadIdx.x, p)) {
                 const int32_t a = max(p.klo, k_first), b = min(p.khi, k_first + n_band - 1);
                 if (b >= a) n += (unsigned long long)(b - a + 1);
                 const int32_t ca = max(p.kclo, k_first), cb = min(p.kchi, k_first + n_band - 1);
@@ -1099,7 +1276,7 @@ __device__ __forceinline__ void serve_compose_tile(const ServeReq &R, const DevG
 __global__ __launch_bounds__(kAccumThreads) __attribute__((amdgpu_waves_per_eu(LRT_SERVE_WAVES)))
 void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *items, int32_t n_species)
 {
-    __shared__ RecF32 rec[kStage];
+    __shared__ AccumLds sm;
     __shared__ int32_t s_last;
     __shared__ double s_part[kAccumThreads / 64];
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
@@ -1133,7 +1310,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
         for (int32_t c = cs0; c < c1; ++c) {
             float e[kPPL], kp[kPPL];
             const int ese = R.escale[2 * c + 0], esk = R.escale[2 * c + 1];
-            accum_cell_tile_f32(rec, L, g, R.cc[c], R.cs + (int64_t)c * n_species,
+            accum_cell_tile_f32(sm, L, g, R.cc[c], R.cs + (int64_t)c * n_species,
                                 R.lnd ? R.lnd + (int64_t)c * R.lnd_stride : nullptr, ese, esk,
                                 R.ranges[(int64_t)c * R.n_tiles + w.tile], kt, kw, lane, e, kp);
             if (R.ct.n_thr >= 0) {
@@ -1264,22 +1441,6 @@ hipError_t launch_cont_cells(const ContThr *thr, int32_t n_thr, const ContRec *r
     return hipGetLastError();
 }
 
-hipError_t launch_scale(const DevLines &L, int64_t i0, int64_t i1, const DevGrid &g,
-                        const CellConst *cc, const CellSpecies *cs, int32_t n_cells,
-                        int32_t n_species, const double *cont_lnb, int32_t *emax, int32_t *escale,
-                        hipStream_t st)
-{
-    // emax must hold INT_MIN on entry (set by a fill kernel of the caller);
-    // lines i0 <= i < i1 are scanned
-    if (i1 > i0) {
-        hipLaunchKernelGGL(scale_kernel, dim3(blocks_for(i1 - i0, 256), min(n_cells, 65535)),
-                           dim3(256), 0, st, L, i0, i1, g, cc, cs, n_cells, n_species, emax);
-    }
-    hipLaunchKernelGGL(scale_finish_kernel, dim3(blocks_for(2 * n_cells, 256)), dim3(256), 0, st,
-                       emax, cont_lnb, 2 * n_cells, escale);
-    return hipGetLastError();
-}
-
 hipError_t launch_accum_f32(const DevLines &L, const DevGrid &g, const CellConst *cc,
                             const CellSpecies *cs, const int32_t *escale, const int2 *ranges,
                             int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band,
@@ -1303,12 +1464,12 @@ hipError_t launch_accum_f64(const DevLines &L, const DevGrid &g, const CellConst
                             int32_t n_species, int32_t k_first, int32_t n_band, const DevCont &ct,
                             double *eta, double *kappa, hipStream_t st)
 {
-    const int32_t n_tiles = (n_band + kTilePoints - 1) / kTilePoints;
+    const int32_t n_tiles = (n_band + kTileF64 - 1) / kTileF64;
     const int64_t n_blocks = (int64_t)n_tiles * n_cells;
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kMaxLaunchBlocks) {
         hipLaunchKernelGGL(accum_f64_kernel, dim3((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0)),
-                           dim3(kAccumThreads), 0, st, L, g, cc, cs, ranges, n_cells, n_species, k_first,
+                           dim3(kThreadsF64), 0, st, L, g, cc, cs, ranges, n_cells, n_species, k_first,
                            n_band, n_tiles, (uint32_t)b0, ct, eta, kappa);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

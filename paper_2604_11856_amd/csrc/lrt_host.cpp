@@ -899,13 +899,14 @@ lrt_status coeffs_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisi
     if (!eta || !kappa) return fail(c, LRT_E_ARG, "eta and kappa must be non-NULL");
     lrt_status r;
     if ((r = prepare(c, st, prec == LRT_FP32_COMP))) return r;
-    const int32_t n_tiles = (n_band + kTilePoints - 1) / kTilePoints;
+    const int32_t tile = prec == LRT_FP64 ? kTileF64 : kTilePoints;
+    const int32_t n_tiles = (n_band + tile - 1) / tile;
     if ((r = ensure(c, c->w_ranges, (size_t)c->n_cells * n_tiles * sizeof(int2)))) return r;
     const DevLines L = dev_lines(c);
     const DevGrid g = dev_grid(c);
     const int32_t nc = (int32_t)c->n_cells;
     LRT_HIP(c, timed(c, LRT_K_RANGES, st, [&] {
-                return launch_ranges(L, g, c->d_cc.as<CellConst>(), nc, k_first, n_band, kTilePoints,
+                return launch_ranges(L, g, c->d_cc.as<CellConst>(), nc, k_first, n_band, tile,
                                      c->w_ranges.as<int2>(), st);
             }));
     DevCont ct{-1, nullptr, nullptr, nullptr, nullptr};

@@ -20,9 +20,10 @@ constexpr double kPi = 3.14159265358979323846;
 // one workgroup owns 256 * kPPL consecutive points of one cell.  The
 // accumulation kernels are compiled for LRT_ACCUM_WAVES waves per SIMD
 // (register budget 512 / waves per lane).  Measured on the 400-cell, 2.2M-line
-// stagnation case: 2 points per lane at 8 waves per SIMD beats 4 points at 4
-// waves by 22% (1385 ms vs 1785 ms per launch).  At 8 waves the FP64 staging
-// code fits the 64-register budget only if the compiler's machine-level loop
+// stagnation case: 8 waves 400 ms, 7 waves 404 ms, 6 waves 427 ms; 1,024-point
+// tiles of 8 waves, which set up fewer (cell, line) pairs but leave more waves
+// waiting at the rounds' barriers, 429 ms.  At 8 waves the FP64 staging code
+// fits the 64-register budget only if the compiler's machine-level loop
 // invariant motion is off (it hoists FP64 constants into registers that then
 // spill); the build passes that option for the accumulation's unit.
 #ifndef LRT_ACCUM_PPL
@@ -42,6 +43,9 @@ constexpr int kPPL = LRT_ACCUM_PPL;
 constexpr int kTilePoints = kAccumThreads * kPPL;
 // Line records staged in LDS per round: one per thread.
 constexpr int kStage = kAccumThreads;
+// Double-precision accumulation: 512-point tiles, 256 threads.
+constexpr int kThreadsF64 = 256;
+constexpr int kTileF64 = kThreadsF64 * kPPL;
 
 // March tile: one workgroup of 4 waves; each wave marches one ray over one
 // chunk of 64 x PPT consecutive points, PPT per lane, and the waves share no
@@ -282,11 +286,6 @@ hipError_t launch_cont_cells(const ContThr *thr, int32_t n_thr, const ContRec *r
 // largest n_model / n_lev over the records.
 hipError_t launch_cr(const DevSpecies &sp, const DevCells &cells, const DevCR &cr, int32_t max_l,
                      int32_t max_lev, const CellSpecies *cs, hipStream_t st);
-hipError_t launch_scale(const DevLines &L, int64_t i0, int64_t i1, const DevGrid &g,
-                        const CellConst *cc, const CellSpecies *cs, int32_t n_cells,
-                        int32_t n_species, const double *cont_lnb, int32_t *emax, int32_t *escale,
-                        hipStream_t st);
-
 hipError_t launch_accum_f32(const DevLines &L, const DevGrid &g, const CellConst *cc,
                             const CellSpecies *cs, const int32_t *escale, const int2 *ranges,
                             int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band,

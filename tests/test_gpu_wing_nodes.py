@@ -1,0 +1,65 @@
+"""Single-precision coefficients where the wings are summed at nodes of 64- to
+512-point intervals, against the FP64 oracle: line widths from a third of a
+grid step to a hundred steps (no interval allowed, all levels used, a tile
+inside the Gaussian core), bands of one point, around a tile and around its
+slices, windows cut by both ends of the grid, and Lorentz fractions from almost
+none to almost one."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2604_11856_amd import lrt, synth
+from parity_util import edge_mask, normwise, say
+
+pytestmark = pytest.mark.gpu
+
+# A term's rounding in single precision: the centre's distance and width (1.5
+# ulp of y, twice in 1/(1+y^2)), |y|^2.25 (2.25 log2|y| <= 15, half an ulp of it:
+# 16 ulp, in a term of at most a tenth), the reciprocal, the products and the
+# two strengths' own rounding: under 8 ulp = 5e-7 of the largest value of a
+# row; sums of up to 64 terms before the double-precision merge add as much.
+TOL = 1e-6
+
+
+def _case(steps, n_points, band, n_e, seed):
+    """A few lines per species on a grid whose step makes the mean Doppler
+    HWHM `steps` grid steps."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    species = [synth.atom_species(rng, "N"), synth.atom_species(rng, "O"), synth.none_species("e-")]
+    T = rng.uniform(5000.0, 12000.0, 3)
+    lo = 40000.0
+    h = 7.16e-7 / 2.0 * np.sqrt(8000.0 / 15.0) * lo / steps
+    hi = lo + h * (n_points - 1)
+    nu0 = np.sort(rng.uniform(lo - 60.0 * steps * h, hi + 60.0 * steps * h, 90))
+    Eu = rng.uniform(80000.0, 110000.0, nu0.size)
+    z = np.zeros(nu0.size)
+    lines = synth.Lines(nu0, 10 ** rng.uniform(5, 8, nu0.size), Eu, z.copy(), Eu - nu0, z.copy(),
+                        rng.integers(2, 13, nu0.size).astype(float), rng.integers(2, 13, nu0.size).astype(float),
+                        rng.integers(0, 2, nu0.size).astype(np.int32))
+    cells = synth.Cells(T, T * 1.1, 10 ** rng.uniform(14, 16, (3, 3)), np.full(3, n_e) * [1.0, 3.0, 0.2])
+    return synth.Workload("wings", species, lines, cells, synth.Grid(lo, hi, n_points, band),
+                          synth.SlabGeometry(np.full(3, 0.1), 1))
+
+
+@pytest.mark.parametrize("steps", [0.3, 2.0, 5.0, 9.0, 25.0, 100.0])
+@pytest.mark.parametrize("n_points,band", [(1537, 1537), (2100, 511), (1100, 513), (640, 64), (130, 1)])
+@pytest.mark.parametrize("n_e", [1e2, 1e15, 3e17])
+def test_wings_against_oracle(steps, n_points, band, n_e):
+    import torch
+    wl = _case(steps, n_points, band, n_e, int(10 * steps) + n_points)
+    say("wings: steps", steps, "points", n_points, "band", band, "n_e", n_e)
+    ref_e, ref_k, _ = O.coeffs(wl.species, wl.lines, wl.cells, wl.grid)
+    ctx = lrt.Context(0).load(wl)
+    nb = ctx.sizes()["n_bands"]
+    got_e, got_k = [], []
+    for b in (range(nb) if band > 1 else list(range(3)) + [nb - 1]):
+        eta, kap, esc = ctx.coeffs_torch(b, lrt.LRT_FP32_COMP)
+        torch.cuda.synchronize()
+        e, k = lrt.scaled_to_f64(eta, kap, esc)
+        got_e.append((b, e))
+        got_k.append((b, k))
+    ctx.close()
+    cols = np.concatenate([np.arange(b * band, b * band + e.shape[1]) for b, e in got_e])
+    m = edge_mask(wl, 0, n_points)[:, cols]
+    assert normwise(np.concatenate([e for _, e in got_e], 1), ref_e[:, cols], m) <= TOL
+    assert normwise(np.concatenate([k for _, k in got_k], 1), ref_k[:, cols], m) <= TOL

@@ -1,0 +1,165 @@
+"""The single-precision accumulation sums a line's wings at nodes of intervals of
+64 to 512 points (lrt_nodes.h) and the (cell, line) setup uses its own
+exponential and Voigt width (lrt_math.h).  CPU only: both headers compiled for
+the host.
+
+- Every point of a line's window belongs to exactly one slice or interval of
+  the tile, nothing outside does, and every interval keeps its conditions.
+- The interpolated wing is within 7.2e-9 of the profile (the bound the header
+  states), at every point an interval may cover.
+- The functions are within the rounding of their operations.
+"""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle as O
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = r'''
+#include <algorithm>
+#include "lrt_nodes.h"
+using namespace lrt;
+extern "C" {
+void modes(int klo, int khi, int cl, int wg, int wc, int at, unsigned *pt, unsigned *node)
+{ const RecMode m = line_modes(klo, khi, cl, wg, wc, at != 0); *pt = m.pt; *node = m.node; }
+int bit0(int l) { return node_bit0(l); }
+int levels() { return kLevels; }
+static constexpr NodeBasis B{};
+void basis(double *pos, double *pt, double *half)
+{ std::copy(kNodePos, kNodePos + kNodes, pos); std::copy(&B.pt[0][0], &B.pt[0][0] + kNodes * 64, pt);
+  std::copy(&B.half[0][0], &B.half[0][0] + kNodes * kNodes, half); }
+void fexp(int n, const double *x, double *e, double *m)
+{ for (int i = 0; i < n; ++i) { e[i] = exp_any(x[i]); m[i] = expm1_any(x[i]); } }
+void fexp_in(int n, const double *x, double *e, double *m)
+{ for (int i = 0; i < n; ++i) { const ExpParts q = exp_parts(x[i]); e[i] = exp_of(q); m[i] = expm1_of(q); } }
+void width(int n, const double *gL, const double *gG, double *v)
+{ for (int i = 0; i < n; ++i) v[i] = voigt_hwhm(gL[i], gG[i], rcp_f64(gL[i] + gG[i])); }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shim")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-ffp-contract=off",
+                    "-I", os.path.join(ROOT, "paper_2604_11856_amd", "csrc"), str(d / "shim.cpp"), "-o", so], check=True)
+    return C.CDLL(so)
+
+
+def _dp(a):
+    return a.ctypes.data_as(C.POINTER(C.c_double))
+
+
+def test_every_point_of_the_window_once(shim):
+    rng = np.random.Generator(np.random.PCG64(5))
+    T, L = 512, shim.levels()
+    pt, node = C.c_uint(), C.c_uint()
+    for _ in range(4000):
+        g = 10.0 ** rng.uniform(-1.5, 2.5)          # gamma_V in grid steps
+        c = rng.uniform(-100.0 * g - 20.0, T + 100.0 * g + 20.0)
+        lo, hi = int(np.ceil(c - 100.0 * g)), int(np.floor(c + 100.0 * g))
+        if rng.random() < 0.2:                      # a window the grid's end cuts
+            lo = max(lo, int(rng.integers(-300, T)))
+            hi = min(hi, int(rng.integers(0, T + 300)))
+        if lo > hi:
+            continue
+        k0 = int(np.rint(c))
+        wg, wc = int(rng.uniform(6.0, 8.8) * g) + 2, int(12.0 * g) + 2
+        at = rng.random() < 0.9
+        shim.modes(lo, hi, k0 - 1, wg, wc, int(at), C.byref(pt), C.byref(node))
+        assert at or node.value == 0
+        seen = np.zeros(T, int)
+        for s in range(8):
+            p = np.arange(64 * s, 64 * s + 64)
+            if pt.value >> s & 1:
+                inside = (p >= lo) & (p <= hi)
+                assert inside.any()
+                seen[p[inside]] += 1
+                assert bool(pt.value >> (8 + s) & 1) == (not inside.all())
+                if np.any(np.abs(p - c) <= 12.0 * g):
+                    assert pt.value >> (16 + s) & 1
+            else:
+                assert not (pt.value >> (8 + s) & 1) and not (pt.value >> (16 + s) & 1)
+        for l in range(L):
+            w = 64 << l
+            for i in range(8 >> l):
+                if node.value >> (shim.bit0(l) + i) & 1:
+                    a, b = w * i, w * i + w - 1
+                    assert a >= lo and b <= hi
+                    d = abs(0.5 * (a + b) - c)
+                    assert d >= 1.25 * w - 1.0 and d - 0.5 * w >= wg - 2
+                    seen[a:b + 1] += 1
+                    if d - 0.5 * w < 12.0 * g:
+                        assert node.value >> (16 + l) & 1
+        p = np.arange(T)
+        assert np.array_equal(seen, ((p >= lo) & (p <= hi)).astype(int)), (g, c, lo, hi)
+
+
+def _wing(y, r):
+    """The profile without its Gaussian, over r-independent factors."""
+    x = np.abs(y) / 2.0
+    w = 0.016 * r * (1.0 - r)
+    return r / (1 + 4 * x * x) - w / (1 + 0.1 * x ** 2.25) + w * np.exp(-0.4 * x ** 2.25)
+
+
+@pytest.mark.parametrize("r", [2.0 ** -40, 1e-6, 1e-3, 0.03, 0.3, 0.7, 0.98])
+def test_interpolated_wing(shim, r):
+    pos, pt, half = np.zeros(16), np.zeros((16, 64)), np.zeros((16, 16))
+    shim.basis(_dp(pos), _dp(pt), _dp(half))
+    # an interval's polynomial taken at its halves' nodes, then at the points
+    left, right = half, half[::-1, ::-1]
+    yG = np.sqrt(37.0 - np.log2(max(r, 2.0 ** -40)))
+    worst = 0.0
+    for g in np.exp(np.linspace(np.log(0.3), np.log(64.0), 60)):
+        for w in (64, 128, 512):
+            for extra in (0.0, 0.3, 1.0, 3.0, 8.0, 20.0, 60.0):
+                D = max(1.25 * w - 1.0, w / 2 + yG * g) + extra * g
+                if D + w / 2 > 100.0 * g:
+                    continue
+                v = [_wing((pos * (w / 64) + D) / g, r)]
+                while len(v) * 64 < w:
+                    v = [u @ m for u in v for m in (left, right)]
+                got = np.concatenate([u @ pt for u in v])
+                # against the oracle's profile, normalisation taken out
+                q = np.arange(w) - (w - 1) / 2 + D
+                ref = np.array([O.voigt_profile(k, g, r * g) for k in q[::7]])
+                ref *= 2.0 * g * (1.065 + 0.447 * r + 0.058 * r * r)
+                worst = max(worst, np.max(np.abs(got[::7] - ref) / ref))
+    assert worst <= 9e-9, worst     # 7.2e-9, and the 2^-30 of the Gaussian left out
+
+
+def test_exponentials(shim):
+    rng = np.random.Generator(np.random.PCG64(6))
+    x = np.concatenate([rng.uniform(-690.0, 690.0, 20000), rng.uniform(-2.0, 2.0, 20000),
+                        10.0 ** rng.uniform(-18, 0, 5000), -10.0 ** rng.uniform(-18, 0, 5000)])
+    e, m = np.zeros_like(x), np.zeros_like(x)
+    for f in (shim.fexp, shim.fexp_in):
+        f(x.size, _dp(x), _dp(e), _dp(m))
+        xl = x.astype(np.longdouble)
+        # the reduction's rounding (half an ulp of r), the series and two more
+        # roundings: under 2 ulps; e^x - 1 loses a factor 2.4 where k = +-1
+        assert np.max(np.abs(e - np.exp(xl)) / np.exp(xl)) <= 4.5e-16
+        assert np.max(np.abs(m - np.expm1(xl)) / np.abs(np.expm1(xl))) <= 1.1e-15
+    x = np.array([0.0, np.inf, -np.inf, np.nan, 1e300, -1e300, 709.0, -745.0, 720.0, -800.0])
+    e, m = np.zeros_like(x), np.zeros_like(x)
+    shim.fexp(x.size, _dp(x), _dp(e), _dp(m))
+    with np.errstate(over="ignore"):
+        np.testing.assert_allclose(e, np.exp(x), rtol=1e-15)
+        np.testing.assert_allclose(m, np.expm1(x), rtol=1e-15)
+
+
+def test_voigt_width(shim):
+    rng = np.random.Generator(np.random.PCG64(7))
+    gL = np.concatenate([10.0 ** rng.uniform(-12, 3, 20000), np.zeros(3), [1e-3, 1.0, 5.0]])
+    gG = np.concatenate([10.0 ** rng.uniform(-3, 1, 20000), [0.1, 1.0, 3.0], np.full(3, 1e-9)])
+    v = np.zeros_like(gL)
+    shim.width(gL.size, _dp(gL), _dp(gG), _dp(v))
+    ref = np.array([O.voigt_hwhm(a, b) for a, b in zip(gL, gG)])
+    # both round a handful of operations near one
+    assert np.max(np.abs(v - ref) / ref) <= 1e-15
