@@ -32,6 +32,22 @@ struct DBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+// Pinned host buffer that kernels write to, grow-only (hipHostFree on release).
+struct HBuf {
+    void *p = nullptr;
+    size_t bytes = 0;
+    HBuf() = default;
+    HBuf(const HBuf &) = delete;
+    HBuf &operator=(const HBuf &) = delete;
+    ~HBuf() { release(); }
+    void release()
+    {
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 0;
+    }
+};
+
 }  // namespace lrt
 
 struct lrt_ctx {
@@ -117,7 +133,8 @@ struct lrt_ctx {
     int march_scheme = 0;     // lrt_march_scheme
 
     // workspace
-    DBuf w_ranges, w_eta, w_kappa, w_partials, w_Iband, w_Itot, w_qband, w_count;
+    DBuf w_ranges, w_eta, w_kappa, w_partials, w_Iband, w_Itot, w_count;
+    lrt::HBuf h_result;   // results of a solve: wall fluxes per range, then intensities per ray
     DBuf w_gen_sys, w_gen_re2, w_gen_cnt, w_gen_off;   // rovibronic line generation
 
     // profiler: event pairs per kernel family
@@ -181,9 +198,15 @@ inline DevWidths dev_widths(const lrt_ctx *c)
 }
 lrt_status line_widths(lrt_ctx *c);
 lrt_status band_range(lrt_ctx *c, int64_t band, int32_t &k_first, int32_t &n_band);
+// Where a solve sums its ranges' intensities (acc NULL: no sum).
+struct RaySums {
+    double *acc = nullptr;    // device, [n_rays]
+    bool first = false;       // set, not added to
+    double *host = nullptr;   // pinned copy written with the last range
+};
 lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precision prec, const void *eta,
                        const void *kappa, const int32_t *escale, double *I_out, double *I_int_out,
-                       hipStream_t st, double *partials, int64_t cap);
+                       hipStream_t st, double *partials, int64_t cap, const RaySums &sums = RaySums());
 // Device address of the static scratch array on `device` (current device),
 // looked up once per device; lrt_march_noalloc's buffer.
 hipError_t noalloc_scratch_init(int device);

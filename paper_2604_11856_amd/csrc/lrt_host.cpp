@@ -69,6 +69,19 @@ lrt_status ensure(lrt_ctx *c, DBuf &b, size_t bytes)
     return upload(c, b, nullptr, bytes);
 }
 
+lrt_status ensure_host(lrt_ctx *c, HBuf &b, size_t bytes)
+{
+    if (b.bytes >= bytes && b.p) return LRT_OK;
+    b.release();
+    const hipError_t e = hipHostMalloc(&b.p, bytes, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        b.p = nullptr;
+        return fail(c, LRT_E_OOM, "hipHostMalloc(%zu): %s", bytes, hipGetErrorString(e));
+    }
+    b.bytes = bytes;
+    return LRT_OK;
+}
+
 }  // namespace lrt
 
 namespace {
@@ -949,7 +962,7 @@ lrt_status coeffs_impl(lrt_ctx *c, int64_t band, lrt_precision prec, void *eta, 
 // then nothing is allocated and no launch is profiled.
 lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precision prec, const void *eta,
                        const void *kappa, const int32_t *escale, double *I_out, double *I_int_out,
-                       hipStream_t st, double *partials, int64_t cap)
+                       hipStream_t st, double *partials, int64_t cap, const RaySums &sums)
 {
     if (prec != LRT_FP64 && prec != LRT_FP32_COMP) return fail(c, LRT_E_ARG, "unknown precision %d", (int)prec);
     if (!eta || !kappa || !I_int_out) return fail(c, LRT_E_ARG, "eta, kappa and I_int_out must be non-NULL");
@@ -988,7 +1001,7 @@ lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisio
     };
     if (partials) LRT_HIP(c, go());
     else LRT_HIP(c, timed(c, LRT_K_MARCH, st, go));
-    LRT_HIP(c, launch_reduce_rows(part, (int32_t)c->n_rays, n_chunks, I_int_out, st));
+    LRT_HIP(c, launch_reduce_rows(part, (int32_t)c->n_rays, n_chunks, I_int_out, sums.acc, sums.first, sums.host, st));
     return LRT_OK;
 }
 
@@ -1014,29 +1027,27 @@ lrt_status solve_ranges(lrt_ctx *c, lrt_precision prec, int64_t n_rng, const int
     const size_t esz = prec == LRT_FP64 ? 8 : 4;
     const size_t plane = (size_t)std::max<int64_t>(c->n_cells, 1) * (size_t)max_pts * esz;
     lrt_status r;
+    const size_t n_q = (size_t)c->n_wall * (size_t)n_rng;
     if ((r = ensure(c, c->w_eta, plane)) || (r = ensure(c, c->w_kappa, plane)) ||
         (r = ensure(c, c->w_Iband, (size_t)c->n_rays * 8)) || (r = ensure(c, c->w_Itot, (size_t)c->n_rays * 8)) ||
-        (r = ensure(c, c->w_qband, (size_t)c->n_wall * n_rng * 8)))
+        (r = ensure_host(c, c->h_result, (n_q + (size_t)c->n_rays) * 8)))
         return r;
-    // zero the accumulators (all-zero bits are +0.0)
-    LRT_HIP(c, launch_fill_u64(c->w_Itot.as<unsigned long long>(), 0ull, c->n_rays, st));
-    LRT_HIP(c, launch_fill_u64(c->w_qband.as<unsigned long long>(), 0ull, c->n_wall * n_rng, st));
+    // the kernels write the results to pinned host memory: [n_rng][n_wall]
+    // fluxes, then the rays' intensities with the last range
+    double *qb = static_cast<double *>(c->h_result.p), *it = qb + n_q;
     int32_t *esc = (prec == LRT_FP32_COMP) ? c->d_escale.as<int32_t>() : nullptr;
     // populations and scales belong to the path: recompute them on every call
     if ((r = prepare(c, st, prec == LRT_FP32_COMP, true))) return r;
     for (int64_t b = 0; b < n_rng; ++b) {
         if ((r = coeffs_range(c, k_first[b], n_pts[b], prec, c->w_eta.p, c->w_kappa.p, nullptr, st))) return r;
+        const RaySums sums{c->w_Itot.as<double>(), b == 0, b == n_rng - 1 ? it : nullptr};
         if ((r = march_range(c, k_first[b], n_pts[b], prec, c->w_eta.p, c->w_kappa.p, esc, nullptr,
-                             c->w_Iband.as<double>(), st, nullptr, 0)))
+                             c->w_Iband.as<double>(), st, nullptr, 0, sums)))
             return r;
-        LRT_HIP(c, launch_add(c->w_Itot.as<double>(), c->w_Iband.as<double>(), (int32_t)c->n_rays, st));
-        // per-range wall flux into row b of the [n_rng][n_wall] staging array
+        // per-range wall flux into row b
         LRT_HIP(c, launch_wall_sum(c->w_Iband.as<double>(), c->d_weight.as<double>(), c->d_wall_off.as<int64_t>(),
-                                   (int32_t)c->n_wall, c->w_qband.as<double>() + b * c->n_wall, st));
+                                   (int32_t)c->n_wall, qb + b * c->n_wall, st));
     }
-    std::vector<double> qb((size_t)c->n_wall * n_rng), it((size_t)c->n_rays);
-    LRT_HIP(c, hipMemcpyAsync(qb.data(), c->w_qband.p, qb.size() * 8, hipMemcpyDeviceToHost, st));
-    LRT_HIP(c, hipMemcpyAsync(it.data(), c->w_Itot.p, it.size() * 8, hipMemcpyDeviceToHost, st));
     LRT_HIP(c, hipStreamSynchronize(st));
     for (int64_t w = 0; w < c->n_wall; ++w) {
         double sum = 0.0;
@@ -1046,7 +1057,7 @@ lrt_status solve_ranges(lrt_ctx *c, lrt_precision prec, int64_t n_rng, const int
         }
         if (q) q[w] = sum;
     }
-    if (I_int) std::copy(it.begin(), it.end(), I_int);
+    if (I_int) std::copy(it, it + c->n_rays, I_int);
     return LRT_OK;
 }
 

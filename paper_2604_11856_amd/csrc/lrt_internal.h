@@ -306,13 +306,11 @@ hipError_t launch_march(bool fp32, bool linear, int32_t ppt, const DevRays &rays
                         const int32_t *escale, const double *T_far, double *I_out,
                         double *partials, int32_t n_chunks, hipStream_t st);
 
-hipError_t launch_reduce_rows(const double *partials, int32_t n_rows, int32_t n_cols,
-                              double *out, hipStream_t st);
+hipError_t launch_reduce_rows(const double *partials, int32_t n_rows, int32_t n_cols, double *out, double *acc,
+                              bool first, double *acc_host, hipStream_t st);
 
 hipError_t launch_wall_sum(const double *I_int, const double *weight, const int64_t *wall_off,
                            int32_t n_wall, double *q, hipStream_t st);
-
-hipError_t launch_add(double *acc, const double *x, int32_t n, hipStream_t st);
 
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 // Cell-state validation on the device: flags[0] |= 1 for a temperature that is

@@ -258,29 +258,47 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     if (lane == 0) partials[(int64_t)ray * n_chunks + chunk] = part;
 }
 
-__global__ void reduce_rows_kernel(const double *p, int32_t n_rows, int32_t n_cols, double *out)
+// Row sums of the march's per-chunk partials, 2^lg lanes to a row: each lane
+// takes every 2^lg-th column, then the lanes are summed by xor-shuffles, a fixed
+// order for a given row length.  acc (NULL: none) receives the running sum over
+// calls (set by the first, added to by the others), acc_host (NULL: none) a copy of it
+// in pinned host memory.  (One thread per row, its loads one after the other,
+// took 813 us on the stagnation line's 17 rows of 8,192 and 16 us on 8 rows of
+// 118.)
+__global__ void reduce_rows_kernel(const double *p, int32_t n_rows, int32_t n_cols, int32_t lg, double *out,
+                                   double *acc, int32_t first, double *acc_host)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rows) return;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = t >> lg;
+    const int lane = (int)(t & ((1 << lg) - 1));
     double s = 0.0;
-    for (int j = 0; j < n_cols; ++j) s += p[(int64_t)r * n_cols + j];
-    out[r] = s;
+    if (r < n_rows) {
+        const double *row = p + r * n_cols;
+#pragma unroll 8
+        for (int j = lane; j < n_cols; j += 1 << lg) s += row[j];
+    }
+    for (int o = (1 << lg) >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0 && r < n_rows) {
+        out[r] = s;
+        if (acc) {
+            const double v = first ? s : acc[r] + s;
+            acc[r] = v;
+            if (acc_host) acc_host[r] = v;
+        }
+    }
 }
 
-__global__ void wall_sum_kernel(const double *I_int, const double *weight, const int64_t *wall_off,
-                                int32_t n_wall, double *q)
+// Flux of each wall point, one wave per wall point: its rays over the lanes,
+// then the lanes by xor-shuffles.
+__global__ __launch_bounds__(64) void wall_sum_kernel(const double *I_int, const double *weight,
+                                                      const int64_t *wall_off, double *q)
 {
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= n_wall) return;
+    const int w = blockIdx.x;
+    const int64_t r1 = wall_off[w + 1];
     double s = 0.0;
-    for (int64_t r = wall_off[w]; r < wall_off[w + 1]; ++r) s += weight[r] * I_int[r];
-    q[w] = s;
-}
-
-__global__ void add_kernel(double *acc, const double *x, int32_t n)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) acc[t] += x[t];
+    for (int64_t r = wall_off[w] + threadIdx.x; r < r1; r += 64) s += weight[r] * I_int[r];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (threadIdx.x == 0) q[w] = s;
 }
 
 }  // namespace
@@ -318,12 +336,14 @@ hipError_t launch_march(bool fp32, bool linear, int32_t ppt, const DevRays &rays
     return hipSuccess;
 }
 
-hipError_t launch_reduce_rows(const double *partials, int32_t n_rows, int32_t n_cols, double *out,
-                              hipStream_t st)
+hipError_t launch_reduce_rows(const double *partials, int32_t n_rows, int32_t n_cols, double *out, double *acc,
+                              bool first, double *acc_host, hipStream_t st)
 {
     if (n_rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(blocks_for(n_rows, 64)), dim3(64), 0, st, partials,
-                       n_rows, n_cols, out);
+    int32_t lg = 0;   // a wave per row, or as many lanes as a short row has columns
+    while (lg < 6 && (1 << lg) < n_cols && ((int64_t)n_rows << lg) < (int64_t(1) << 30)) ++lg;
+    hipLaunchKernelGGL(reduce_rows_kernel, dim3(blocks_for((int64_t)n_rows << lg, 256)), dim3(256), 0, st, partials,
+                       n_rows, n_cols, lg, out, acc, first ? 1 : 0, acc_host);
     return hipGetLastError();
 }
 
@@ -331,15 +351,7 @@ hipError_t launch_wall_sum(const double *I_int, const double *weight, const int6
                            int32_t n_wall, double *q, hipStream_t st)
 {
     if (n_wall == 0) return hipSuccess;
-    hipLaunchKernelGGL(wall_sum_kernel, dim3(blocks_for(n_wall, 64)), dim3(64), 0, st, I_int,
-                       weight, wall_off, n_wall, q);
-    return hipGetLastError();
-}
-
-hipError_t launch_add(double *acc, const double *x, int32_t n, hipStream_t st)
-{
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(add_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, acc, x, n);
+    hipLaunchKernelGGL(wall_sum_kernel, dim3((unsigned)n_wall), dim3(64), 0, st, I_int, weight, wall_off, q);
     return hipGetLastError();
 }
 
