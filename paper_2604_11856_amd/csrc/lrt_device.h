@@ -30,11 +30,15 @@ static __device__ __forceinline__ double planck_f64(double nu, double T)
 // where 1 - e cancels (relative error ~6e-8/|t|), the Taylor series
 // F = sum_n (-t)^n/(n+1)! through t^4 (first omitted term below 1.4e-8
 // relative) rewritten in u: H = sum_n (-1)^n ln2^(n+1) u^n/(n+1)!.
-static __device__ __forceinline__ float fexp_u_f32(float u, float e)
+static __device__ __forceinline__ float fexp_u_thin_f32(float u)
 {
     constexpr double l = kLn2, l2 = l * l, l3 = l2 * l;
-    const float poly = fmaf(u, fmaf(u, fmaf(u, fmaf(u, (float)(l3 * l2 / 120.0), (float)(-l2 * l2 / 24.0)),
-                                            (float)(l3 / 6.0)), (float)(-l2 / 2.0)), (float)l);
+    return fmaf(u, fmaf(u, fmaf(u, fmaf(u, (float)(l3 * l2 / 120.0), (float)(-l2 * l2 / 24.0)),
+                                (float)(l3 / 6.0)), (float)(-l2 / 2.0)), (float)l);
+}
+static __device__ __forceinline__ float fexp_u_f32(float u, float e)
+{
+    const float poly = fexp_u_thin_f32(u);
     const float direct = (1.0f - e) * __builtin_amdgcn_rcpf(u);
     return fabsf(u) < (float)(0.1 * kLog2e) ? poly : direct;
 }
@@ -61,6 +65,31 @@ static __device__ __forceinline__ void segment_scales(double ds, int32_t ese, in
     const double d = ds * kLog2e;
     dsu = (float)fmin(ldexp(d, esk), 3.0e38);
     dsl = ldexp(d, ese);
+}
+
+// One cell-constant segment at N points, added to the intensities I.  Where
+// every lane of the wave is thin (|tau| < 0.1; most of a spectrum away from
+// strong lines) the series alone serves: 1 - e^-tau = u H, so I <- I - I u H +
+// eta H dsl, 11 instructions instead of 17 with the exponential, the reciprocal
+// and the selection, and the attenuation is rounded relative to tau.
+template <int N>
+static __device__ __forceinline__ void segment_points_f32(const float (&ev)[N], const float (&kv)[N], float dsu,
+                                                          double dsl, double (&I)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const float u = kv[j] * dsu;
+        const float thin_H = fexp_u_thin_f32(u);
+        if (__all(fabsf(u) < (float)(0.1 * kLog2e))) {
+            const double x = (double)(u * thin_H), em = (double)(ev[j] * thin_H);
+            I[j] = fma(-x, I[j], fma(em, dsl, I[j]));
+        } else {
+            const float e = __builtin_amdgcn_exp2f(-u);
+            const float direct = (1.0f - e) * __builtin_amdgcn_rcpf(u);
+            const float H = fabsf(u) < (float)(0.1 * kLog2e) ? thin_H : direct;
+            I[j] = fma(I[j], (double)e, (double)(ev[j] * H) * dsl);
+        }
+    }
 }
 
 // Weights per unit length of the two nodes of a linear-j segment (Sec. 2.2.3:

@@ -973,13 +973,17 @@ lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisio
     if (c->rays_cells != c->n_cells)
         return fail(c, LRT_E_STATE, "rays expect %lld cells, %lld set", (long long)c->rays_cells, (long long)c->n_cells);
     lrt_status r;
-    const int32_t ppt = march_points_per_lane(c->h_off.back(), c->n_cells), chunk_points = 64 * ppt;
-    const int32_t n_chunks = (n_band + chunk_points - 1) / chunk_points;
-    const int64_t need = c->n_rays * (int64_t)n_chunks;
+    const MarchPlan plan = march_plan(c->n_rays, c->n_cells, n_band, prec == LRT_FP32_COMP);
+    const int64_t need = c->n_rays * (int64_t)plan.n_chunks;
     if (partials) {
-        if (need > cap)
+        // what the caller's buffer is held to: chunks of 128 points from 128
+        // segments per cell on, else of 256 (never fewer sums than the plan's,
+        // but where it takes 128-point chunks for want of waves, which are few)
+        const int32_t points = c->h_off.back() >= 128 * c->n_cells ? 128 : 256;
+        const int64_t held = c->n_rays * (int64_t)((n_band + points - 1) / points);
+        if (std::max(held, need) > cap)
             return fail(c, LRT_E_ARG, "the march needs %lld partial sums (rays x %d-point chunks), the buffer holds %lld",
-                        (long long)need, chunk_points, (long long)cap);
+                        (long long)held, points, (long long)cap);
     } else {
         if ((r = ensure(c, c->w_partials, (size_t)need * sizeof(double)))) return r;
     }
@@ -995,13 +999,13 @@ lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisio
     }
     const DevGrid g = dev_grid(c);
     auto go = [&] {
-        return launch_march(prec == LRT_FP32_COMP, c->march_scheme == LRT_MARCH_LINEAR_J, ppt, rays, g, k_first, n_band,
-                            eta, kappa, escale, c->have_Tfar ? c->d_Tfar.as<double>() : nullptr, I_out, part,
-                            n_chunks, st);
+        return launch_march(prec == LRT_FP32_COMP, c->march_scheme == LRT_MARCH_LINEAR_J, plan, rays, g, k_first,
+                            n_band, eta, kappa, escale, c->have_Tfar ? c->d_Tfar.as<double>() : nullptr, I_out, part,
+                            st);
     };
     if (partials) LRT_HIP(c, go());
     else LRT_HIP(c, timed(c, LRT_K_MARCH, st, go));
-    LRT_HIP(c, launch_reduce_rows(part, (int32_t)c->n_rays, n_chunks, I_int_out, sums.acc, sums.first, sums.host, st));
+    LRT_HIP(c, launch_reduce_rows(part, (int32_t)c->n_rays, plan.n_chunks, I_int_out, sums.acc, sums.first, sums.host, st));
     return LRT_OK;
 }
 

@@ -48,25 +48,40 @@ constexpr int kThreadsF64 = 256;
 constexpr int kTileF64 = kThreadsF64 * kPPL;
 
 // March tile: one workgroup of 4 waves; each wave marches one ray over one
-// chunk of 64 x PPT consecutive points, PPT per lane, and the waves share no
-// state.  Smaller chunks keep more cell rows in L2 while a chunk's rays run
-// (a row is 8 B per point), at more per-segment work per point, so the tile
-// follows how often the rays cross a cell: from kMarchReuseNarrow segments per
-// cell on, 128-point chunks (PPT 2) and 4 rays per workgroup; below, 256-point
-// chunks (PPT 4) and 4 consecutive chunks of one ray per workgroup.  March time per step of the large
-// axisymmetric slice (131,072 rays, 391 segments per cell), by chunk points /
-// rays per workgroup: 1024 / 1 (4 points per lane): 826 ms; 256 / 1: 794;
-// 256 / 2: 794; 256 / 4: 712; 256 / 8: 717; 128 / 4: 641-651; 128 / 8: 656;
-// 64 / 4: 909; 64 / 8: 928.  On the 256 x 128-cell case (8,192 rays, few
-// segments per cell), per band: 128 / 4: 97 ms; 256 / 4: 88 ms; 256-point
-// chunks, 4 of one ray per workgroup: 84 ms.
+// chunk of 64 x ppt consecutive points, ppt per lane, and the waves share no
+// state.
+//   ppt: 256-point chunks, or 128-point ones where those would leave fewer than
+//     three waves per SIMD (kMarchFewWaves).  March time with 256 / 128 points:
+//     782 waves of 256 points (one ray, 64 cells) 40 / 30 us; 944 (8 rays, 131
+//     cells) 69 / 51; 2,304 (384 rays, 2,400 cells) 57 / 43; 4,096 (128 rays,
+//     8,192 cells) 113 / 121; 17 rays on 2^19 points 1.80 / 1.99 ms.
+//   rays: from kMarchManyRays rays on a workgroup takes 4 of them on one chunk,
+//     which then share rows in the L1; below, 4 consecutive chunks of one ray.
+//     4 rays / one ray: 128 rays 133 / 113 us, 256: 191 / 192, 512: 304 / 366,
+//     1,024: 522 / 684, 2,048: 0.99 / 1.26 ms, 4,096: 1.78 / 2.16.
+//   shared: every XCD on the same chunk (march_item) where the rows of eight
+//     chunks, one per XCD, exceed the last-level cache, and there are many rays
+//     to share them.  32,768 cells, 8,192 rays: 4.13 ms against 4.48 without;
+//     8,192 cells, 4,096 rays: 1.84 against 1.73.
 constexpr int kMarchThreads = 256;
-constexpr int64_t kMarchReuseNarrow = 128;
+constexpr int64_t kMarchFewWaves = 3072;
+constexpr int32_t kMarchManyRays = 256;
+constexpr int64_t kLastLevelBytes = int64_t(256) << 20;
 
-// Points per lane of the march for a ray set with n_seg segments over n_cells cells.
-inline int32_t march_points_per_lane(int64_t n_seg, int64_t n_cells)
+struct MarchPlan {
+    int32_t ppt, rays, n_chunks;
+    bool shared;
+};
+inline MarchPlan march_plan(int64_t n_rays, int64_t n_cells, int32_t n_band, bool fp32)
 {
-    return n_seg >= kMarchReuseNarrow * n_cells ? 2 : 4;
+    MarchPlan p;
+    const int64_t wide = n_rays * ((n_band + 255) / 256);
+    p.ppt = wide < kMarchFewWaves ? 2 : 4;
+    p.n_chunks = (n_band + 64 * p.ppt - 1) / (64 * p.ppt);
+    p.rays = n_rays >= kMarchManyRays ? 4 : 1;
+    const int64_t rows = 8 * n_cells * (int64_t)(64 * p.ppt) * 2 * (fp32 ? 4 : 8);
+    p.shared = p.rays > 1 && rows > kLastLevelBytes;
+    return p;
 }
 
 // Workgroups per launch of a kernel whose grid can be large (the accumulation
@@ -301,10 +316,10 @@ hipError_t launch_count(const DevLines &L, const DevGrid &g, const CellConst *cc
                         int32_t n_species, int32_t k_first, int32_t n_band,
                         unsigned long long *count, hipStream_t st);
 
-hipError_t launch_march(bool fp32, bool linear, int32_t ppt, const DevRays &rays, const DevGrid &g,
+hipError_t launch_march(bool fp32, bool linear, const MarchPlan &plan, const DevRays &rays, const DevGrid &g,
                         int32_t k_first, int32_t n_band, const void *eta, const void *kappa,
                         const int32_t *escale, const double *T_far, double *I_out,
-                        double *partials, int32_t n_chunks, hipStream_t st);
+                        double *partials, hipStream_t st);
 
 hipError_t launch_reduce_rows(const double *partials, int32_t n_rows, int32_t n_cols, double *out, double *acc,
                               bool first, double *acc_host, hipStream_t st);

@@ -11,32 +11,46 @@
 
 #include "lrt_device.h"
 #include "lrt_internal.h"
+#include "lrt_math.h"
 
 namespace lrt {
 
 namespace {
 
+// e^-t - 1 of an optical thickness and the two quotients of the segment laws.
+// One exponential series and one reciprocal (refined to the rounding of a
+// division) per point, 45 instructions, where the library's expm1, exp and
+// divisions took 110.
+__device__ __forceinline__ double expm1_neg(double t)
+{
+    return fabs(t) < 700.0 ? expm1_of(exp_parts(-t)) : expm1_any(-t);
+}
+__device__ __forceinline__ double div_f64(double a, double b, double rb)
+{
+    const double q = a * rb;
+    return fma(fma(-b, q, a), rb, q);
+}
+
 __device__ __forceinline__ void linear_j_weights_f64(double t, double &e, double &wf, double &wn)
 {
-    e = exp(-t);
+    const double em = expm1_neg(t);
+    e = 1.0 + em;
     if (fabs(t) >= 0.05) {
-        const double f = -expm1(-t) / t;
-        wn = (1.0 - f) / t;
-        wf = (f - e) / t;
+        const double rt = rcp_f64(t);
+        const double f = div_f64(-em, t, rt);
+        wn = div_f64(1.0 - f, t, rt);
+        wf = div_f64(f - e, t, rt);
         return;
     }
-    // Horner over n = 17..0 of c_n t^n with c_n = (-1)^n/(n+2)! and (n+1) c_n
-    double inv_fact[18];
-    double fct = 2.0;
-    for (int n = 0; n < 18; ++n) {
-        inv_fact[n] = 1.0 / fct;
-        fct *= (double)(n + 3);
-    }
-    double a = 0.0, b = 0.0;
-    for (int n = 17; n >= 0; --n) {
-        const double c = (n & 1) ? -inv_fact[n] : inv_fact[n];
+    // Horner over n = 8..0 of c_n t^n with c_n = (-1)^n/(n+2)! and (n+1) c_n
+    // (first omitted terms below 5e-19)
+    double a = 0.0, b = 0.0, inv = 1.0 / 3628800.0;
+#pragma unroll
+    for (int n = 8; n >= 0; --n) {
+        const double c = (n & 1) ? -inv : inv;
         a = fma(a, t, c);
         b = fma(b, t, (double)(n + 1) * c);
+        inv *= (double)(n + 2);
     }
     wn = a;
     wf = b;
@@ -49,18 +63,21 @@ template <int PPT, typename T>
 __device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t kb, uint32_t ob, int32_t n_band,
                                          bool vec, T (&ev)[PPT], T (&kv)[PPT])
 {
-    if constexpr (sizeof(T) == 4) {
-        if (vec) {   // one vector load per array and lane
-            typedef float VecF __attribute__((ext_vector_type(PPT)));
-            const VecF a = *(const VecF *)((const char *)erow + ob);
-            const VecF b = *(const VecF *)((const char *)krow + ob);
+    if (vec) {   // vector loads of up to 16 bytes
+        constexpr int V = sizeof(T) == 4 ? PPT : 2;
+        // (aligned to the element only: global loads take any such address)
+        typedef T Vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
 #pragma unroll
-            for (int j = 0; j < PPT; ++j) {
-                ev[j] = a[j];
-                kv[j] = b[j];
+        for (int j = 0; j < PPT; j += V) {
+            const Vec a = *(const Vec *)((const char *)erow + ob + j * sizeof(T));
+            const Vec b = *(const Vec *)((const char *)krow + ob + j * sizeof(T));
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                ev[j + i] = a[i];
+                kv[j + i] = b[i];
             }
-            return;
         }
+        return;
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -81,33 +98,27 @@ __device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t 
 // The (ray, chunk) of wave `wave` of workgroup b (b: index in the whole grid,
 // launch offset b0 + blockIdx.x): the workgroup owns RAYS rays x (4 / RAYS)
 // consecutive chunks, one (ray, chunk) per wave.  Workgroups go round-robin to
-// the 8 XCDs (b % 8), each with its own L2.  With one ray per workgroup (few
-// segments per cell) XCD x takes a contiguous range of the chunk-major items,
-// so every ray of a spectral chunk runs on one XCD and the rows the rays share
-// come from that XCD's L2.  With four rays per workgroup (many segments per
-// cell) the items are taken in their own chunk-major order, so all XCDs work on
-// the same chunk and its rows, read by every XCD, stay in the chip-wide last-
-// level cache (measured on 131,072 rays over 131,072 cells: 544 against 560 ms
-// per step; on the stagnation line and the 256 x 128 case, with one ray per
-// workgroup, that order took 12.7 against 7.8 ms and 97.8 against 82.9 ms per
-// launch).  When every wall point has
-// the same rays (per_wall > 0) a chunk's rays are taken direction-major: the
-// rays an XCD runs together are then nearly parallel lines from neighbouring
-// wall points, which cross nearly the same cells.  (Measured against
-// ray-fastest items with a contiguous ray range per XCD: 8.6 vs 11.2 ms on the
-// 17 slab rays of the stagnation line, 100.6 vs 107.5 ms on 8192 axisymmetric
-// rays.)  A bijection onto [0, n_rays) x [0, n_chunks) for any sizes (ray = -1
-// for the waves past the last ray or chunk).
+// the 8 XCDs (b % 8), each with its own L2.  Without `shared`, XCD x takes a
+// contiguous range of the chunk-major items, so every ray of a spectral chunk
+// runs on one XCD and the rows the rays share come from that XCD's L2; with it
+// the items are taken in their own chunk-major order, so all XCDs work on the
+// same chunk, whose rows stay in the chip-wide last-level cache.  When every
+// wall point has the same rays (per_wall > 0) a chunk's rays are taken
+// direction-major: the rays an XCD runs together are then nearly parallel lines
+// from neighbouring wall points, which cross nearly the same cells.  A bijection
+// onto [0, n_rays) x [0, n_chunks) for any sizes (ray = -1 for the waves past
+// the last ray or chunk).  (A contiguous range of each chunk's rays per XCD was
+// 60 % slower: the directions' paths differ in length.)
 template <int RAYS>
 __device__ __forceinline__ void march_item(uint32_t b, int32_t wave, const DevRays &rays, int32_t n_chunks,
-                                           int &ray, int &chunk)
+                                           int32_t shared, int &ray, int &chunk)
 {
     constexpr int CHUNKS = kMarchThreads / 64 / RAYS;
     const uint32_t n_groups = ((uint32_t)rays.n_rays + RAYS - 1) / RAYS;
     const uint32_t n_cgroups = ((uint32_t)n_chunks + CHUNKS - 1) / CHUNKS;
     const uint32_t n = n_groups * n_cgroups, x = b % kXCDs, i = b / kXCDs;
     const uint32_t per = n / kXCDs, rem = n % kXCDs;
-    const uint32_t gi = RAYS > 1 ? b : x * per + min(x, rem) + i;
+    const uint32_t gi = shared ? b : x * per + min(x, rem) + i;
     chunk = (int)(gi / n_groups) * CHUNKS + wave / RAYS;
     const int32_t q = (int32_t)(gi % n_groups) * RAYS + wave % RAYS;
     if (q >= rays.n_rays || chunk >= n_chunks) {
@@ -120,15 +131,35 @@ __device__ __forceinline__ void march_item(uint32_t b, int32_t wave, const DevRa
     }
 }
 
+//
+// The rays' segments come 64 at a time, one per lane: its cell, its length and
+// the factors of the segment law from the length and the cell's scales.  The
+// wave then walks them, the segment's values broadcast from its lane, its rows
+// (one vector load per array) requested kAhead segments before they are used,
+// so that few rays, too few waves to hide a load behind each other, do not wait
+// for every row in turn.
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int l)
+{
+    if constexpr (sizeof(T) == 8) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+        return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+    } else {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+    }
+}
+
 template <bool FP32, bool LINEAR, int PPT, int RAYS>
 __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     DevRays rays, DevGrid g, int32_t k_first, int32_t n_band, const void *eta_v,
     const void *kappa_v, const int32_t *escale, const double *T_far, double *I_out,
-    double *partials, int32_t n_chunks, int32_t aligned16, uint32_t b0)
+    double *partials, int32_t n_chunks, int32_t shared, uint32_t b0)
 {
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
     int ray, chunk;
-    march_item<RAYS>(b0 + blockIdx.x, wave, rays, n_chunks, ray, chunk);
+    march_item<RAYS>(b0 + blockIdx.x, wave, rays, n_chunks, shared, ray, chunk);
     if (ray < 0) return;
     const int32_t kb = chunk * (64 * PPT) + lane * PPT;   // band-relative
     const int64_t m0 = rays.off[ray], m1 = rays.off[ray + 1];
@@ -139,107 +170,131 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
         I[j] = 0.0;
         if (Tw > 0.0 && kb + j < n_band) I[j] = planck_f64(g.nu_min + (double)(k_first + kb + j) * g.h, Tw);
     }
-    // vector loads only when every row start is aligned to PPT floats
-    // (16-byte aligned bases, n_band a multiple of PPT) and the wave's
-    // points are all inside the band (a wave-uniform choice)
-    const bool vec = aligned16 && (int64_t)(chunk + 1) * (64 * PPT) <= n_band && (n_band % PPT) == 0;
+    // vector loads only when the wave's points are all inside the band (a
+    // wave-uniform choice)
+    const bool vec = (int64_t)(chunk + 1) * (64 * PPT) <= n_band;
     using T = std::conditional_t<FP32, float, double>;
     const T *eta = (const T *)eta_v;
     const T *kap = (const T *)kappa_v;
     const uint32_t ob = (uint32_t)kb * (uint32_t)sizeof(T);   // byte offset of the lane's points in a row
+    constexpr int kAhead = FP32 ? 4 : 2;
+    T ev[kAhead][PPT], kv[kAhead][PPT];
 
-    if constexpr (!LINEAR) {
-        // the segment loop, with vector or guarded row loads chosen once
-        // outside it; a 32-bit trip count keeps the loop test on the scalar unit
-        const int32_t *cell_m = rays.cell + m0;
-        const double *ds_m = rays.ds + m0;
-        const int32_t n_seg = (int32_t)(m1 - m0);
-        auto cell_march = [&](auto vec_c) {
-#pragma unroll 2
-            for (int32_t i = 0; i < n_seg; ++i) {
-                const int32_t c = cell_m[i];
-                const double ds = ds_m[i];
-                const int64_t row = (int64_t)c * n_band;
-                T ev[PPT], kv[PPT];
-                load_row<PPT, T>(eta + row, kap + row, (uint32_t)kb, ob, n_band, decltype(vec_c)::value, ev, kv);
+    // linear-j: the far node of the next segment (its coefficients, scales and length)
+    [[maybe_unused]] T pe[PPT], pk[PPT];
+    [[maybe_unused]] int32_t pee = 0, pek = 0;
+    [[maybe_unused]] double pds = 0.0;
+    // one linear-j segment from node (fe, fk) to node ne, lengths scaled by the
+    // nodes' powers of two (Lf = Ln = L and Lk = L in double precision)
+    [[maybe_unused]] auto linear_segment = [&](const T (&fe)[PPT], const T (&fk)[PPT], const T (&ne)[PPT], double Lf,
+                                               double Ln, T Lk) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            if constexpr (FP32) {
+                const float t = fk[j] * Lk;
+                const float e = __builtin_amdgcn_exp2f(t * (float)(-kLog2e));
+                float wf, wn;
+                linear_j_weights_f32(t, e, wf, wn);
+                I[j] = fma(I[j], (double)e, (double)(wf * fe[j]) * Lf + (double)(wn * ne[j]) * Ln);
+            } else {
+                double e, wf, wn;
+                linear_j_weights_f64(fk[j] * Lk, e, wf, wn);
+                I[j] = I[j] * e + Lf * (wf * fe[j] + wn * ne[j]);
+            }
+        }
+    };
+
+    // the segment loop, with vector or guarded row loads chosen once outside it
+    const int32_t n_seg = (int32_t)(m1 - m0);
+    auto march = [&](auto vec_c) {
+        auto load = [&](int slot, int32_t c) {
+            const int64_t row = (int64_t)c * n_band;
+            load_row<PPT, T>(eta + row, kap + row, (uint32_t)kb, ob, n_band, decltype(vec_c)::value, ev[slot],
+                             kv[slot]);
+        };
+        for (int32_t i0 = 0; i0 < n_seg; i0 += 64) {
+            const int32_t n = min(64, n_seg - i0);
+            int32_t c = 0, ee = 0, ek = 0;
+            double ds = 0.0;
+            if (lane < n) {
+                c = rays.cell[m0 + i0 + lane];
+                ds = rays.ds[m0 + i0 + lane];
                 if constexpr (FP32) {
-                    float dsu;
-                    double dsl;
-                    segment_scales(ds, escale[2 * c + 0], escale[2 * c + 1], dsu, dsl);
+                    ee = escale[2 * c + 0];
+                    ek = escale[2 * c + 1];
+                }
+            }
+            // the segment's factors, per lane: cell-constant dsu, dsl; linear-j
+            // (far node: the previous lane's, or the last of the previous 64,
+            // or at the far end the segment's own with half its length) Lf, Ln, Lk
+            [[maybe_unused]] float dsu = 0.0f;
+            [[maybe_unused]] double dsl = 0.0, Lf = 0.0, Ln = 0.0;
+            [[maybe_unused]] T Lk = 0;
+            if constexpr (!LINEAR) {
+                if constexpr (FP32) segment_scales(ds, ee, ek, dsu, dsl);
+            } else {
+                double fds = __shfl_up(ds, 1);
+                int32_t fee = __shfl_up(ee, 1), fek = __shfl_up(ek, 1);
+                if (lane == 0) {
+                    fds = i0 > 0 ? pds : 0.0;
+                    fee = i0 > 0 ? pee : ee;
+                    fek = i0 > 0 ? pek : ek;
+                }
+                const double L = 0.5 * (fds + ds);
+                Lf = ldexp(L, fee);
+                Ln = ldexp(L, ee);
+                Lk = FP32 ? (T)fmin(ldexp(L, fek), 3.0e38) : (T)L;
+                pds = lane_value(ds, n - 1);
+                pee = lane_value(ee, n - 1);
+                pek = lane_value(ek, n - 1);
+            }
 #pragma unroll
-                    for (int j = 0; j < PPT; ++j) {
-                        double at, em;
-                        segment_f32(ev[j], kv[j], dsu, dsl, at, em);
-                        I[j] = fma(I[j], at, em);
-                    }
-                } else {
+            for (int j = 0; j < kAhead; ++j)
+                if (j < n) load(j, lane_value(c, j));
+            for (int32_t s0 = 0; s0 < n; s0 += kAhead) {
 #pragma unroll
-                    for (int j = 0; j < PPT; ++j) {
-                        if (kb + j < n_band) {
-                            const double tau = kv[j] * ds;
-                            const double em = expm1(-tau);
-                            const double F = (tau == 0.0) ? 1.0 : -em / tau;
-                            I[j] = I[j] * (1.0 + em) + ev[j] * ds * F;
+                for (int q = 0; q < kAhead; ++q) {
+                    const int32_t s = s0 + q;
+                    if (s >= n) break;
+                    if constexpr (LINEAR) {
+                        const double lf = lane_value(Lf, s), ln = FP32 ? lane_value(Ln, s) : lf;
+                        const T lk = FP32 ? lane_value(Lk, s) : (T)lf;
+                        if (i0 + s == 0)
+                            linear_segment(ev[q], kv[q], ev[q], lf, ln, lk);   // far end -> first midpoint
+                        else
+                            linear_segment(pe, pk, ev[q], lf, ln, lk);         // midpoint -> midpoint
+#pragma unroll
+                        for (int j = 0; j < PPT; ++j) {
+                            pe[j] = ev[q][j];
+                            pk[j] = kv[q][j];
+                        }
+                    } else if constexpr (FP32) {
+                        segment_points_f32<PPT>(ev[q], kv[q], lane_value(dsu, s), lane_value(dsl, s), I);
+                    } else {
+                        const double d = lane_value(ds, s);
+#pragma unroll
+                        for (int j = 0; j < PPT; ++j) {
+                            const double tau = kv[q][j] * d;
+                            const double em = expm1_neg(tau);
+                            const double F = (tau == 0.0) ? 1.0 : div_f64(-em, tau, rcp_f64(tau));
+                            I[j] = fma(I[j], em, I[j]) + ev[q][j] * d * F;
                         }
                     }
+                    if (s + kAhead < n) load(q, lane_value(c, s + kAhead));
                 }
             }
-        };
-        if (vec)
-            cell_march(std::true_type{});
-        else
-            cell_march(std::false_type{});
-    } else {
-        // previous node (the far node of the next segment)
-        T pe[PPT], pk[PPT];
-        int32_t pee = 0, pek = 0;
-        double pds = 0.0;
-        // one linear-j segment of length L from node (fe, fk) to node (ne_)
-        auto segment = [&](const T (&fe)[PPT], const T (&fk)[PPT], int32_t fee,
-                           int32_t fek, const T (&ne_)[PPT], int32_t nee, double L) {
-            if constexpr (FP32) {
-                const double Lf = ldexp(L, fee), Ln = ldexp(L, nee);
-                const float Lk = (float)fmin(ldexp(L, fek), 3.0e38);
-#pragma unroll
-                for (int j = 0; j < PPT; ++j) {
-                    const float t = fk[j] * Lk;
-                    const float e = __builtin_amdgcn_exp2f(t * (float)(-kLog2e));
-                    float wf, wn;
-                    linear_j_weights_f32(t, e, wf, wn);
-                    I[j] = fma(I[j], (double)e, (double)(wf * fe[j]) * Lf + (double)(wn * ne_[j]) * Ln);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < PPT; ++j) {
-                    if (kb + j < n_band) {
-                        double e, wf, wn;
-                        linear_j_weights_f64(fk[j] * L, e, wf, wn);
-                        I[j] = I[j] * e + L * (wf * fe[j] + wn * ne_[j]);
-                    }
-                }
-            }
-        };
-        for (int64_t m = m0; m < m1; ++m) {
-            const int32_t c = rays.cell[m];
-            const double ds = rays.ds[m];
-            T ev[PPT], kv[PPT];
-            load_row<PPT, T>(eta + (int64_t)c * n_band, kap + (int64_t)c * n_band, (uint32_t)kb, ob, n_band, vec,
-                             ev, kv);
-            const int32_t ee = FP32 ? escale[2 * c + 0] : 0, ek = FP32 ? escale[2 * c + 1] : 0;
-            if (m == m0)
-                segment(ev, kv, ee, ek, ev, ee, 0.5 * ds);             // far end -> first midpoint
-            else
-                segment(pe, pk, pee, pek, ev, ee, 0.5 * (pds + ds));   // midpoint -> midpoint
-#pragma unroll
-            for (int j = 0; j < PPT; ++j) {
-                pe[j] = ev[j];
-                pk[j] = kv[j];
-            }
-            pee = ee;
-            pek = ek;
-            pds = ds;
         }
-        if (m1 > m0) segment(pe, pk, pee, pek, pe, pee, 0.5 * pds);     // last midpoint -> target
+    };
+    if (vec)
+        march(std::true_type{});
+    else
+        march(std::false_type{});
+    if constexpr (LINEAR) {
+        if (n_seg > 0) {   // last midpoint -> target
+            const double L = 0.5 * pds;
+            linear_segment(pe, pk, pe, ldexp(L, pee), ldexp(L, pee),
+                           FP32 ? (T)fmin(ldexp(L, pek), 3.0e38) : (T)L);
+        }
     }
     // outputs: I and the trapezoid partial with global-index weights
     double part = 0.0;
@@ -303,26 +358,30 @@ __global__ __launch_bounds__(64) void wall_sum_kernel(const double *I_int, const
 
 }  // namespace
 
-hipError_t launch_march(bool fp32, bool linear, int32_t ppt, const DevRays &rays, const DevGrid &g,
+hipError_t launch_march(bool fp32, bool linear, const MarchPlan &plan, const DevRays &rays, const DevGrid &g,
                         int32_t k_first, int32_t n_band, const void *eta, const void *kappa,
                         const int32_t *escale, const double *T_far, double *I_out,
-                        double *partials, int32_t n_chunks, hipStream_t st)
+                        double *partials, hipStream_t st)
 {
     if (rays.n_rays == 0) return hipSuccess;
-    if (ppt != 2 && ppt != 4) return hipErrorInvalidValue;
-    // 128-point chunks: 4 rays per workgroup; 256-point chunks: 4 chunks of one ray
-    const int64_t waves = kMarchThreads / 64, n_rays = rays.n_rays;
-    const int64_t n_blocks = ppt == 2 ? (n_rays + waves - 1) / waves * n_chunks
-                                      : n_rays * ((n_chunks + waves - 1) / waves);
+    const int64_t n_rays = rays.n_rays, cg = kMarchThreads / 64 / plan.rays;
+    const int64_t n_blocks = (n_rays + plan.rays - 1) / plan.rays * ((plan.n_chunks + cg - 1) / cg);
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
-    const int32_t al = ((((uintptr_t)eta) | ((uintptr_t)kappa)) & 15) == 0;
+    // Where the XCDs share a chunk, too many rays at once push each other's rows
+    // out of the L2s: 40 KB of (unused) LDS per workgroup leaves 16 waves per CU
+    // (8,192 rays: 4.13 against 4.72 ms with 28 waves, 5.83 with 12; 131,072 rays:
+    // 29.7 against 31.6).
+    const unsigned lds = plan.shared ? 40960u : 0u;
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kMaxLaunchBlocks) {
         const dim3 grid((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0));
-#define LRT_MARCH(F, LIN, P, R)                                                                          \
-    hipLaunchKernelGGL((march_kernel<F, LIN, P, R>), grid, dim3(kMarchThreads), 0, st, rays, g, k_first, \
-                       n_band, eta, kappa, escale, T_far, I_out, partials, n_chunks, al, (uint32_t)b0)
-#define LRT_MARCH_P(F, LIN) \
-    if (ppt == 2) LRT_MARCH(F, LIN, 2, 4); else LRT_MARCH(F, LIN, 4, 1)
+#define LRT_MARCH(F, LIN, P, R)                                                                            \
+    hipLaunchKernelGGL((march_kernel<F, LIN, P, R>), grid, dim3(kMarchThreads), lds, st, rays, g, k_first, \
+                       n_band, eta, kappa, escale, T_far, I_out, partials, plan.n_chunks,                  \
+                       plan.shared ? 1 : 0, (uint32_t)b0)
+#define LRT_MARCH_P(F, LIN)                                                       \
+    if (plan.ppt == 2 && plan.rays == 1) LRT_MARCH(F, LIN, 2, 1);                 \
+    else if (plan.ppt == 2) LRT_MARCH(F, LIN, 2, 4);                              \
+    else if (plan.rays == 1) LRT_MARCH(F, LIN, 4, 1); else LRT_MARCH(F, LIN, 4, 4)
         if (fp32) {
             if (linear) LRT_MARCH_P(true, true); else LRT_MARCH_P(true, false);
         } else {
