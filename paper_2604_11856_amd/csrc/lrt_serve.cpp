@@ -47,7 +47,15 @@ using Clock = std::chrono::steady_clock;
 
 constexpr size_t kAlign = 256;
 constexpr int kEpochStreams = 2;
-constexpr int32_t kChunkCells = 32;
+// Cells of a request's work item.  Long chunks write and compose fewer
+// transmittances; short ones give a request enough workgroups for the chip: a
+// request takes the largest chunk of at most kChunkCells that makes kMinItems
+// items, but no less than kMinChunkCells (a linear-j chunk evaluates one cell
+// more than it owns).  Alone, 190 cells on 28,000 points took 6.2 ms as 330 items
+// of 32 cells, 3.4 as 1,024, 2.9 as 2,048 and 2.6 as 2,600 of 4 cells (the least);
+// 3.5 with chunks of down to one cell.  Sixteen mixed requests: 45 and 41 ms.
+constexpr int32_t kChunkCells = 32, kMinChunkCells = 4;
+constexpr int64_t kMinItems = 4096;
 constexpr int kEpochCap = 32768;            // items per epoch at most
 constexpr int64_t kEpochUnits = 512ll << 20; // cell x point units per epoch (target)
 constexpr int kItemsPerTurn = 64;          // round-robin share per request
@@ -109,7 +117,7 @@ struct Req {
     double T_far = 0.0;   // solid far boundary (0: free)
     int scheme = 0;       // LRT_MARCH_CELL or LRT_MARCH_LINEAR_J
     // layout
-    int32_t n_tiles = 0, n_chunks = 0;
+    int32_t n_tiles = 0, n_chunks = 0, chunk_cells = 0;
     size_t bytes = 0, off = 0;
     int slot = -1;
     int64_t items_total = 0, items_issued = 0, items_done = 0;
@@ -132,12 +140,11 @@ struct Epoch {
 
 // Device bytes of one request (inputs, per-cell constants, ranges, chunk
 // transmittance / source, outputs), each sub-buffer 256-byte aligned.
-size_t request_bytes(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t cr_row, int32_t &n_tiles,
-                     int32_t &n_chunks)
+size_t request_bytes(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t cr_row, int32_t chunk_cells,
+                     int32_t &n_tiles, int32_t &n_chunks)
 {
     n_tiles = (n_window + kTilePoints - 1) / kTilePoints;
-    n_chunks = (int32_t)((nc + kChunkCells - 1) / kChunkCells);
-    const size_t nb = (size_t)(n_window + 255) / 256;
+    n_chunks = (int32_t)((nc + chunk_cells - 1) / chunk_cells);
     size_t b = 0;
     b += 4 * align_up(nc * 8);                              // T_tr, T_v, n_e, ds
     b += align_up((size_t)nc * S * 8);                      // N
@@ -154,6 +161,19 @@ size_t request_bytes(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t
     if (cr_row > 0)                                         // QSS-CR: populations, departures
         b += 2 * align_up((size_t)nc * cr_row * 8);
     return b;
+}
+
+// Chunk length of a request: by its sizes and the server's budget alone, so that
+// its result does not depend on what else is served.  Short chunks need more
+// memory; a request whose buffers would then pass an eighth of the budget keeps
+// the longest.
+int32_t chunk_cells_of(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t cr_row, size_t budget)
+{
+    const int64_t tiles = (n_window + kTilePoints - 1) / kTilePoints;
+    const int64_t most = nc * tiles / kMinItems;
+    const int32_t c = (int32_t)std::max<int64_t>(kMinChunkCells, std::min<int64_t>(kChunkCells, most));
+    int32_t t, m;
+    return request_bytes(nc, S, n_window, n_thr, cr_row, c, t, m) <= budget / 8 ? c : kChunkCells;
 }
 
 double ms_between(Clock::time_point a, Clock::time_point b)
@@ -221,7 +241,8 @@ bool lrt_server::admit(Req &r)
     const int S = ctx->n_species;
     const int32_t n_thr = ctx->n_cont_rec > 0 ? ctx->n_cont_thr : -1;
     const int32_t cr_row = ctx->n_cr > 0 ? ctx->n_cr * ctx->cr_LS : 0;
-    const size_t bytes = request_bytes(r.n_cells, S, r.n_window, n_thr, cr_row, r.n_tiles, r.n_chunks);
+    r.chunk_cells = chunk_cells_of(r.n_cells, S, r.n_window, n_thr, cr_row, budget);
+    const size_t bytes = request_bytes(r.n_cells, S, r.n_window, n_thr, cr_row, r.chunk_cells, r.n_tiles, r.n_chunks);
     if (free_slots.empty()) return false;
     size_t off;
     if (!arena.alloc(bytes, off)) return false;
@@ -328,7 +349,7 @@ bool lrt_server::admit(Req &r)
             return true;
     }
     if (!ok(launch_fill_i32(done, 0, (int64_t)r.n_tiles + 1, st), "counters")) return true;
-    r.dev = ServeReq{(int32_t)nc, r.k_first, r.n_window, r.n_tiles, r.n_chunks, kChunkCells,
+    r.dev = ServeReq{(int32_t)nc, r.k_first, r.n_window, r.n_tiles, r.n_chunks, r.chunk_cells,
                      cc, cs, escale, ds, ranges, TS, I_out, done, tile_part, I_int, h_I_int + r.slot, ct, r.T_far,
                      r.scheme == LRT_MARCH_LINEAR_J ? 1 : 0, L.lnd_stride, L.lnd};
     if (!ok(hipMemcpyAsync(d_reqs.as<ServeReq>() + r.slot, &r.dev, sizeof(ServeReq),
@@ -366,7 +387,7 @@ bool lrt_server::launch_epoch(Epoch &e)
                 const int64_t it = r.items_issued++;
                 const int32_t tile = (int32_t)(it / r.n_chunks), chunk = (int32_t)(it % r.n_chunks);
                 e.h_items[n++] = ServeItem{r.slot, tile, chunk};
-                const int64_t cells = std::min<int64_t>(kChunkCells, r.n_cells - (int64_t)chunk * kChunkCells);
+                const int64_t cells = std::min<int64_t>(r.chunk_cells, r.n_cells - (int64_t)chunk * r.chunk_cells);
                 units += cells * kTilePoints;
                 credit[r.ticket] += 1;
                 progress = true;
@@ -472,7 +493,7 @@ void lrt_server::run()
         const bool in_flight = !admitted.empty() || epochs[0].busy || epochs[1].busy;
         if (stopping && pending.empty() && !in_flight) break;
         if (!progress) {
-            if (in_flight) cv_work.wait_for(lk, std::chrono::microseconds(100));
+            if (in_flight) cv_work.wait_for(lk, std::chrono::microseconds(25));
             else cv_work.wait_for(lk, std::chrono::milliseconds(20));
         }
     }
@@ -547,7 +568,7 @@ lrt_status lrt_submit(lrt_server *s, const lrt_los_request *q, uint64_t *ticket)
     int32_t nt, nch;
     const int32_t n_thr = ctx->n_cont_rec > 0 ? ctx->n_cont_thr : -1;
     const int32_t cr_row = ctx->n_cr > 0 ? ctx->n_cr * ctx->cr_LS : 0;
-    const size_t bytes = request_bytes(q->n_cells, S, (int32_t)q->n_window, n_thr, cr_row, nt, nch);
+    const size_t bytes = request_bytes(q->n_cells, S, (int32_t)q->n_window, n_thr, cr_row, kChunkCells, nt, nch);
     if (bytes > s->budget)
         return fail(nullptr, LRT_E_BUDGET, "request needs %zu bytes, budget is %zu", bytes, s->budget);
     std::unique_ptr<Req> r(new (std::nothrow) Req());

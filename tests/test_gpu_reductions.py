@@ -5,6 +5,7 @@ double precision: the two sides add the same positive numbers in different
 orders, so they agree within (terms) x 2^-53; the bar is 1e-12."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime is the one the library uses)
 
 from paper_2604_11856_amd import lrt, synth
 
