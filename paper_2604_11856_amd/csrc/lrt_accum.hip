@@ -1,11 +1,10 @@
 // gfx950 kernels of the line-by-line path (arXiv 2604.11856): populations,
 // line setups and the line-to-grid accumulation.
 //
-//   thermo      per (cell, species): atomic partition function, ln(N/Q),
-//               Doppler coefficient; per cell: beta's, Lorentz HWHM, line-skip
-//               bound (Sec. 2.1 Boltzmann populations, Sec. 2.2.1 widths);
-//               molq: ln(N/Q) of the molecules, one wave per (cell, species); the
-//               QSS-CR populations of selected atoms come from lrt_cr.hip
+//   thermo      per (cell, species): partition function, ln(N/Q), Doppler
+//               coefficient; per cell: beta's, Lorentz HWHM, line-skip bound
+//               (Sec. 2.1 Boltzmann populations, Sec. 2.2.1 widths); the
+//               QSS-CR populations of selected species come from lrt_cr.hip
 //               and enter the line setup as departures from Boltzmann
 //   ranges      per (cell, tile): index range of the nu0-sorted lines that
 //               can reach the tile
@@ -62,31 +61,74 @@ __device__ double vdw_width(const DevSpecies &sp, const DevCells &cells, int c, 
     return 1e7 * w;
 }
 
-__global__ void thermo_kernel(DevSpecies sp, DevCells cells, DevWidths wd, double M_min,
-                              uint64_t mask, CellConst *cc, CellSpecies *cs)
+// Per-cell constants and, per (cell, species), the Doppler coefficient and
+// ln(N/Q) with Q the partition function of an atom (Sec. 2.1, electronic
+// levels) or a molecule (Sec. 2.1 molecular Boltzmann relation: Q = sum_e g_e
+// e^{-beta_v T_e} sum_v e^{-beta_v G_v} sum_J (2J+1) e^{-beta_tr (B_v J(J+1) -
+// D_v J^2(J+1)^2)}).  One wave per (cell, species): lane l takes levels l (mod
+// 64), or of every (e, v) the J = l (mod 64), then the lanes are summed in a
+// fixed butterfly order.  Where all vibrational levels of a state have the same
+// rotational constants (a rigid rotor) the vibrational and the rotational sum
+// factor.  Bound by the exponentials' instructions: 32,768 cells with four
+// molecules of 50 levels and 152 J each took 3.54 ms with a rotational sum per
+// level and the library's exponential, 0.28 ms so (1.28 where the constants
+// differ); on 8 cells of two atoms, an atom's levels one after the other and the
+// molecules in a launch of their own, 7.8 us, 4.8 so.
+__global__ __launch_bounds__(64) void thermo_kernel(DevSpecies sp, DevCells cells, DevWidths wd, double M_min,
+                                                    uint64_t mask, CellConst *cc, CellSpecies *cs)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int S = cells.n_species;
-    if (t >= (int64_t)cells.n_cells * S) return;
+    const int64_t t = blockIdx.x;
     const int c = (int)(t / S), s = (int)(t % S);
+    const int lane = threadIdx.x;
     const double Tv = cells.T_v[c], Ttr = cells.T_tr[c];
     const double bv = kC2 / Tv, br = kC2 / Ttr;
     const int kind = sp.kind[s];
     double Q = 0.0;
     if (kind == 1) {
-        for (int64_t j = sp.lev_off[s]; j < sp.lev_off[s + 1]; ++j)
-            Q += sp.lev_g[j] * exp(-bv * sp.lev_E[j]);
+        for (int64_t j = sp.lev_off[s] + lane; j < sp.lev_off[s + 1]; j += 64)
+            Q += sp.lev_g[j] * exp_any(-bv * sp.lev_E[j]);
+    } else if (kind == 2) {
+        // this lane's part of the rotational sum of constants (B, D)
+        auto rotational = [&](double B, double D, int Jmax) {
+            double qr = 0.0;
+            for (int J = lane; J <= Jmax; J += 64) {
+                const double jj = (double)J * (J + 1.0);
+                qr += (2.0 * J + 1.0) * exp_any(-br * (B * jj - D * jj * jj));
+            }
+            return qr;
+        };
+        for (int64_t e = sp.el_off[s]; e < sp.el_off[s + 1]; ++e) {
+            const int Jmax = sp.el_Jmax[e];
+            const int64_t v0 = sp.vib_off[e], v1 = sp.vib_off[e + 1];
+            double qvr = 0.0;
+            // every level with the first one's constants: the two sums factor
+            const double B0 = sp.vib_B[v0], D0 = sp.vib_D[v0];
+            bool same = true;
+            for (int64_t v = v0 + lane; v < v1; v += 64) same = same && sp.vib_B[v] == B0 && sp.vib_D[v] == D0;
+            if (__all(same)) {
+                for (int64_t v = v0 + lane; v < v1; v += 64) qvr += exp_any(-bv * sp.vib_G[v]);
+                for (int o = 32; o > 0; o >>= 1) qvr += __shfl_xor(qvr, o);
+                qvr *= rotational(B0, D0, Jmax);
+            } else {
+                for (int64_t v = v0; v < v1; ++v)
+                    qvr += exp_any(-bv * sp.vib_G[v]) * rotational(sp.vib_B[v], sp.vib_D[v], Jmax);
+            }
+            Q += sp.el_g[e] * exp_any(-bv * sp.el_T[e]) * qvr;
+        }
     }
-    const double N = cells.N[(int64_t)c * S + s];
-    CellSpecies o;
-    // species outside a non-zero mask carry no lines (bit s of mask); a
-    // molecule's ln(N/Q) comes from molq_kernel, launched next
-    const bool on = species_on(mask, s);
-    o.lnNQ = (on && kind == 1 && N > 0.0 && Q > 0.0) ? log(N) - log(Q) : -INFINITY;
-    o.dop = 7.16233e-7 / 2.0 * sqrt(Ttr / sp.mass[s]);
-    o.gW = (wd.E_ion && kind == 1 && wd.E_ion[s] > 0.0) ? vdw_width(sp, cells, c, s) : 0.0;
-    cs[t] = o;
-    if (s == 0) {
+    if (kind == 1 || kind == 2)
+        for (int o = 32; o > 0; o >>= 1) Q += __shfl_xor(Q, o);
+    if (lane == 0) {
+        const double N = cells.N[(int64_t)c * S + s];
+        CellSpecies o;
+        // species outside a non-zero mask carry no lines (bit s of mask)
+        o.lnNQ = (species_on(mask, s) && kind != 0 && N > 0.0 && Q > 0.0) ? log(N) - log(Q) : -INFINITY;
+        o.dop = 7.16233e-7 / 2.0 * sqrt(Ttr / sp.mass[s]);
+        o.gW = (wd.E_ion && kind == 1 && wd.E_ion[s] > 0.0) ? vdw_width(sp, cells, c, s) : 0.0;
+        cs[t] = o;
+    }
+    if (s == 0 && lane == 1) {
         CellConst k;
         k.beta_v = bv;
         k.beta_tr = br;
@@ -100,41 +142,6 @@ __global__ void thermo_kernel(DevSpecies sp, DevCells cells, DevWidths wd, doubl
         k.cand_G = 100.0 * (wd.gN_max + wd.gS_max * k.gL + gWmax) * (1.0 + 1e-6);
         k.cand_A = 100.0 * (7.16233e-7 / 2.0) * sqrt(Ttr / M_min) * (1.0 + 1e-6);
         cc[c] = k;
-    }
-}
-
-// ln(N/Q) of a molecule (Sec. 2.1 molecular Boltzmann relation), one wave per
-// (cell, species): Q = sum_e g_e e^{-beta_v T_e} sum_v e^{-beta_v G_v}
-// sum_J (2J+1) e^{-beta_tr (B_v J(J+1) - D_v J^2(J+1)^2)}, lane l taking the
-// J = l (mod 64) terms of every (e, v), then the lanes summed in a fixed
-// butterfly order.  Waves of other species leave at once.
-__global__ __launch_bounds__(64) void molq_kernel(DevSpecies sp, DevCells cells, uint64_t mask, CellSpecies *cs)
-{
-    const int S = cells.n_species;
-    const int64_t t = blockIdx.x;
-    const int c = (int)(t / S), s = (int)(t % S);
-    if (sp.kind[s] != 2) return;
-    const int lane = threadIdx.x;
-    const double bv = kC2 / cells.T_v[c], br = kC2 / cells.T_tr[c];
-    double Q = 0.0;
-    for (int64_t e = sp.el_off[s]; e < sp.el_off[s + 1]; ++e) {
-        double qvr = 0.0;
-        const int Jmax = sp.el_Jmax[e];
-        for (int64_t v = sp.vib_off[e]; v < sp.vib_off[e + 1]; ++v) {
-            const double B = sp.vib_B[v], D = sp.vib_D[v];
-            double qr = 0.0;
-            for (int J = lane; J <= Jmax; J += 64) {
-                const double jj = (double)J * (J + 1.0);
-                qr += (2.0 * J + 1.0) * exp(-br * (B * jj - D * jj * jj));
-            }
-            qvr += exp(-bv * sp.vib_G[v]) * qr;
-        }
-        Q += sp.el_g[e] * exp(-bv * sp.el_T[e]) * qvr;
-    }
-    for (int o = 32; o > 0; o >>= 1) Q += __shfl_xor(Q, o);
-    if (lane == 0) {
-        const double N = cells.N[(int64_t)c * S + s];
-        cs[t].lnNQ = (species_on(mask, s) && N > 0.0 && Q > 0.0) ? log(N) - log(Q) : -INFINITY;
     }
 }
 
@@ -399,22 +406,36 @@ __global__ void ranges_kernel(DevLines L, DevGrid g, const CellConst *cc, int32_
 // per-cell power-of-two scale for the single-precision form
 // ---------------------------------------------------------------------------
 
-// Per-cell scale from the level-energy bins: one wave per cell takes the
+// Per-cell scale from the level-energy bins: the cell's waves take the
 // largest upper bound of ln(eta peak) and ln(|kappa peak|) over the bins.
 // Peak of line i: strength * norm with norm = 1/(2 gV (1.065 + ...)) and
 // gV >= 0.9 gG (the Voigt width is at least the Doppler one; 0.9 leaves room
 // for the fit), gG = dop_s nu0; |kappa| <= skap0 max(N_u, N_l g_u/g_l).  The
 // bound exceeds the true peak by a modest factor (bin width, Lorentz part of
 // the width), which the power-of-two scale absorbs.
-__global__ void scale_bound_kernel(DevBins B, const CellConst *cc, const CellSpecies *cs,
-                                   const double *cont_lnb, int32_t n_cells, int32_t n_species,
-                                   int32_t *escale)
+// kWaves waves per cell: four while the cells alone leave the chip idle, else one.
+// The species' part of the bound is taken once per cell (LDS, up to
+// kScaleSpecies species), so a bin costs two multiply-adds and two maxima; bound
+// by the bins' loads.  32,768 cells of the 1M-line list 1.71 -> 1.04 ms, 190 cells
+// 240 -> 63 us.
+constexpr int kScaleSpecies = 64;
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void scale_bound_kernel(DevBins B, const CellConst *cc,
+                                                                  const CellSpecies *cs, const double *cont_lnb,
+                                                                  int32_t n_cells, int32_t n_species, int32_t *escale)
 {
-    const int c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    __shared__ double v0[kScaleSpecies];
+    __shared__ double part[kWaves][2];
+    const int c = blockIdx.x;
     const int lane = threadIdx.x & 63;
-    if (c >= n_cells) return;
     const CellConst k = cc[c];
     const double ln_norm = -log(2.0 * 1.065 * 0.9);
+    auto species_part = [&](int s) {
+        const CellSpecies q = cs[(int64_t)c * n_species + s];
+        return q.lnNQ > -INFINITY ? q.lnNQ + ln_norm - log(q.dop) : -INFINITY;
+    };
+    if ((int)threadIdx.x < min(n_species, kScaleSpecies)) v0[threadIdx.x] = species_part(threadIdx.x);
+    __syncthreads();
     double ve = -INFINITY, vk = -INFINITY;
     const double *lnd_c = B.lev_off ? B.lnd + (int64_t)c * B.lnd_stride : nullptr;
     // a spectral window: line centres that can reach it (as ranges_kernel)
@@ -423,11 +444,12 @@ __global__ void scale_bound_kernel(DevBins B, const CellConst *cc, const CellSpe
         ca = (B.win_a - k.cand_G) / (1.0 + k.cand_A);
         cb = (B.win_b + k.cand_G) / (1.0 - k.cand_A);
     }
-    for (int b = lane; b < B.n; b += 64) {
+    for (int b = threadIdx.x; b < B.n; b += 64 * kWaves) {
         if (B.nu_lo && (B.nu_hi[b] < ca || B.nu_lo[b] > cb)) continue;
-        const CellSpecies q = cs[(int64_t)c * n_species + B.species[b]];
-        if (!(q.lnNQ > -INFINITY)) continue;
-        double v = q.lnNQ + ln_norm - log(q.dop) - k.beta_v * B.Ev[b] - k.beta_tr * B.Er[b];
+        const int s = B.species[b];
+        const double v1 = s < kScaleSpecies ? v0[s] : species_part(s);
+        if (!(v1 > -INFINITY)) continue;
+        double v = v1 - k.beta_v * B.Ev[b] - k.beta_tr * B.Er[b];
         if (lnd_c) {
             // QSS-CR: the largest departure from Boltzmann among the bin's levels
             double d = -INFINITY;
@@ -444,11 +466,22 @@ __global__ void scale_bound_kernel(DevBins B, const CellConst *cc, const CellSpe
         ve = fmax(ve, __shfl_xor(ve, o));
         vk = fmax(vk, __shfl_xor(vk, o));
     }
+    if constexpr (kWaves > 1) {
+        if (lane == 0) {
+            part[threadIdx.x >> 6][0] = ve;
+            part[threadIdx.x >> 6][1] = vk;
+        }
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w) {
+            ve = fmax(ve, part[w][0]);
+            vk = fmax(vk, part[w][1]);
+        }
+    }
     if (cont_lnb) {   // the atomic continuum's own bound
         ve = fmax(ve, cont_lnb[2 * c + 0]);
         vk = fmax(vk, cont_lnb[2 * c + 1]);
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         // peak < 2^e; stay unscaled while e is within 2^+-60
         const double v2[2] = {ve, vk};
         for (int j = 0; j < 2; ++j) {
@@ -1400,12 +1433,8 @@ hipError_t launch_thermo(const DevSpecies &sp, const DevCells &cells, const DevW
 {
     const int64_t n = (int64_t)cells.n_cells * cells.n_species;
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(thermo_kernel, dim3(blocks_for(n, 64)), dim3(64), 0, st, sp, cells, wd, M_min,
-                       species_mask, cc, cs);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     if (n > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(molq_kernel, dim3((unsigned)n), dim3(64), 0, st, sp, cells, species_mask, cs);
+    hipLaunchKernelGGL(thermo_kernel, dim3((unsigned)n), dim3(64), 0, st, sp, cells, wd, M_min, species_mask, cc, cs);
     return hipGetLastError();
 }
 
@@ -1425,8 +1454,12 @@ hipError_t launch_scale_bound(const DevBins &B, const CellConst *cc, const CellS
                               int32_t *escale, hipStream_t st)
 {
     if (n_cells == 0) return hipSuccess;
-    hipLaunchKernelGGL(scale_bound_kernel, dim3(blocks_for(n_cells, 4)), dim3(256), 0, st, B, cc, cs,
-                       cont_lnb, n_cells, n_species, escale);
+    if (n_cells < 8192)
+        hipLaunchKernelGGL(scale_bound_kernel<4>, dim3((unsigned)n_cells), dim3(256), 0, st, B, cc, cs, cont_lnb,
+                           n_cells, n_species, escale);
+    else
+        hipLaunchKernelGGL(scale_bound_kernel<1>, dim3((unsigned)n_cells), dim3(64), 0, st, B, cc, cs, cont_lnb,
+                           n_cells, n_species, escale);
     return hipGetLastError();
 }
 
