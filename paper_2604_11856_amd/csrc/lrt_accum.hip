@@ -510,38 +510,22 @@ struct __align__(16) RecAmp {
     float se, sk, qg;               // strengths times s and the cell's scale; (1-r) / s
     uint32_t edges;                 // window, tile-relative, clamped to [-1, tile]: klo | khi << 16 (edge masks)
 };
-// Slices of the double-precision tile overlapped by [lo, hi] (tile-relative,
-// possibly beyond the tile): a contiguous run of bits.
-__device__ __forceinline__ uint32_t slice_run(int32_t lo, int32_t hi)
-{
-    if (lo > hi || hi < 0 || lo > kTileF64 - 1) return 0u;
-    const int32_t a = max(lo, 0) >> 6, b = min(hi, kTileF64 - 1) >> 6;
-    return (2u << b) - (1u << a);
-}
-
-// Mode masks of a window [klo, khi] with core window [kclo, kchi] (tile-relative).
-__device__ __forceinline__ uint32_t slice_modes(int32_t klo, int32_t khi, int32_t kclo, int32_t kchi)
-{
-    const uint32_t in = slice_run(klo, khi);
-    // a slice holds a window edge when the window starts or ends strictly inside it
-    uint32_t edge = 0u;
-    if (klo >= 0 && (klo & 63) != 0) edge |= 1u << min(klo >> 6, 31);
-    if (khi < kTileF64 && (khi & 63) != 63 && khi >= 0) edge |= 1u << min(khi >> 6, 31);
-    const uint32_t core = slice_run(max(kclo, klo), min(kchi, khi));
-    return in | ((edge & in) << 8) | ((core & in) << 16);
-}
-
-struct __align__(16) RecF64 {
-    int32_t klo, khi, k0;
-    uint32_t mode;          // slice masks: in, edge, x^2.25 window, Gaussian window
-    double frac0, inv2g, r, se, sk, pad2;
+// Double-precision line record: x = |(k - k0) h2 - f2| with h2 = h/(2 gamma_V),
+// f2 = frac0/(2 gamma_V) and the tile-relative index k.
+struct __align__(16) RecPos64 {
+    double k0, h2, f2, r;   // centre index (tile-relative), h2, f2, gamma_L / gamma_V
+};
+struct __align__(16) RecAmp64 {
+    double w, se, sk;       // 0.016 r (1-r), strengths
+    uint32_t edges, pad;    // window, tile-relative, clamped to [-1, tile]: klo | khi << 16
 };
 
 // The Whiting profile is evaluated in y = (nu_k - nu0) / gamma_V = +-2x, so that
 // 1 + 4x^2 = 1 + y^2 is one FMA and x^2.25 = 2^-2.25 |y|^2.25.
 constexpr double kTwoM225 = 0.21022410381342863;   // 2^-2.25
 
-__device__ const NodeBasis kBasis{};
+__device__ const NodeBasis<kNodes> kBasis(kNodePos);
+__device__ const NodeBasis<kNodes64> kBasis64(kNodePos64);
 
 // Constants of the single-precision profile.  The kernels set them once,
 // outside their loops, and an empty asm keeps them in scalar registers: VOP3
@@ -756,6 +740,36 @@ __device__ __forceinline__ void node_flush(float pe, float pk, int lane, double 
     if ((lane & 16) == 0) acc[lane >> 5][lane & 15] += v;
 }
 
+// The node sums of a tile's intervals brought down to its 64-point intervals:
+// the waves' parts of each interval, then level by level from the whole tile,
+// each interval's polynomial taken at the nodes of its halves.  An interval's
+// sums end up with the first wave under it.  Called by the whole workgroup, after
+// a barrier; ends with one.
+template <int N, int kThreads>
+__device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][2][N], const NodeBasis<N> &basis)
+{
+#pragma unroll
+    for (int l = kLevels - 1; l >= 0; --l) {
+        // thread -> (interval, quantity, node)
+        const int node = threadIdx.x % N, qy = threadIdx.x / N % 2;
+        for (int it = threadIdx.x / (2 * N); it < (kSlices >> l); it += kThreads / (2 * N)) {
+            const int w0 = l > 0 ? it << (l - 1) : it >> 1, set = l > 0 ? kPPL - 1 + l : it & 1;
+            double v = sums[w0][set][qy][node];
+            for (int w = 1; w < (1 << l) / 2; ++w) v += sums[w0 + w][set][qy][node];
+            if (l < kLevels - 1) {
+                const double *up = sums[(it >> 1) << l][kPPL + l][qy];
+#pragma unroll 8
+                for (int q = 0; q < N; ++q) {
+                    const double c = (it & 1) ? basis.half[N - 1 - q][N - 1 - node] : basis.half[q][node];
+                    v = fma(c, up[q], v);
+                }
+            }
+            sums[w0][set][qy][node] = v;
+        }
+        __syncthreads();
+    }
+}
+
 // eta and kappa of one cell on one tile (kTilePoints points starting at the
 // global index kt) in single precision: every round stages kStage candidate
 // lines (one FP64 setup per thread) into LDS, then each wave evaluates the
@@ -930,31 +944,9 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
         }
         __syncthreads();
     }
-    // Node sums to the points: the waves' parts of each interval, then level by
-    // level from the whole tile down, each interval's polynomial taken at the
-    // nodes of its halves; at last at the points.
+    // node sums to the points
     if (at_nodes) {
-#pragma unroll
-        for (int l = kLevels - 1; l >= 0; --l) {
-            // thread -> (interval, quantity, node)
-            const int node = threadIdx.x & 15, qy = (threadIdx.x >> 4) & 1;
-            for (int it = threadIdx.x >> 5; it < (kSlices >> l); it += kAccumThreads / 32) {
-                // the interval's sums end up with the first wave under it
-                const int w0 = l > 0 ? it << (l - 1) : it >> 1, set = l > 0 ? kPPL - 1 + l : it & 1;
-                double v = sm.node[w0][set][qy][node];
-                for (int w = 1; w < (1 << l) / 2; ++w) v += sm.node[w0 + w][set][qy][node];
-                if (l < kLevels - 1) {
-                    const double *up = sm.node[(it >> 1) << l][kPPL + l][qy];
-#pragma unroll 8
-                    for (int q = 0; q < kNodes; ++q) {
-                        const double c = (it & 1) ? kBasis.half[kNodes - 1 - q][kNodes - 1 - node] : kBasis.half[q][node];
-                        v = fma(c, up[q], v);
-                    }
-                }
-                sm.node[w0][set][qy][node] = v;
-            }
-            __syncthreads();
-        }
+        nodes_down<kNodes, kAccumThreads>(sm.node, kBasis);
 #pragma unroll 8
         for (int q = 0; q < kNodes; ++q) {
             const double c = kBasis.pt[q][lane];
@@ -1009,132 +1001,209 @@ void accum_f32_kernel(
     }
 }
 
-// Whiting profile in double precision.  The two rational terms share one
-// division.  An exponential whose argument is below -745.6 underflows to
-// exactly zero (e^-745.14 is under half the smallest subnormal), so the
-// windows of the two exponentials, in units of gamma_V, stop where that
-// happens: beyond |dnu| = 33 gamma_V (x = 16.5) e^{-2.772 x^2} is exactly
-// zero in double precision, beyond 57 gamma_V (x = 28.5) so is
-// e^{-0.4 x^2.25}, while the line windows reach x = 50; the point windows
-// carry one point of margin on each side, and a lane inside a window slice
-// but beyond its exponential's bound adds an exact zero.
-constexpr double kF64GaussHalfWidth = 33.0;
-constexpr double kF64WexpHalfWidth = 57.0;
+// Reach of e^{-0.4 x^2.25} in double precision, in units of gamma_V: at y = 2x =
+// 16 it is 2^-59 of the rational part, for any r.  The Gaussian's reach is y_G
+// (lrt_nodes.h).  A lane of a slice within a term's reach but beyond it adds what
+// the term is there.
+constexpr double kF64WexpReach = 16.0;
+
+// Rational part r/(1+4x^2) - w/(1+0.1 x^2.25) over one quotient (the hardware
+// reciprocal refined to the rounding of a division); also x^2 and x^2.25.
+__device__ __forceinline__ double shape_rational_f64(double k, const RecPos64 &q, double w, double &u, double &p)
+{
+    const double x = fabs(fma(k - q.k0, q.h2, -q.f2));
+    u = x * x;
+    p = u * (x > 0.0 ? sqrt_newton(sqrt_newton(x)) : 0.0);
+    const double d1 = fma(4.0, u, 1.0), d2 = fma(0.1, p, 1.0);
+    const double num = fma(q.r, d2, -(w * d1)), den = d1 * d2;
+    const double inv = rcp_f64(den), P = num * inv;
+    return fma(fma(-den, P, num), inv, P);
+}
+// e^v of v <= 0 (zero from -745 on, however far)
+__device__ __forceinline__ double exp_neg_f64(double v) { return exp_of(exp_parts(v)); }
 
 // The terms of one staged line (bit t of the block masks) on this wave's
-// slices of points kk[j], added to the sums.
+// slices of points kd[j], added to the sums.
 template <typename Mask>
-__device__ __forceinline__ void line_terms_f64(const RecF64 &qr, int t, const int32_t (&kk)[kPPL], double h,
+__device__ __forceinline__ void line_terms_f64(const RecPos64 &qr, const RecAmp64 &ar, int t, const double (&kd)[kPPL],
                                                const Mask (&m_in)[kPPL], const Mask (&m_w)[kPPL],
                                                const Mask (&m_g)[kPPL], const Mask (&m_edge)[kPPL],
                                                double (&se)[kPPL], double (&sk)[kPPL])
 {
-    const RecF64 q = qr;
+    const RecPos64 q = qr;
+    const RecAmp64 a = ar;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         if (!((m_in[j] >> t) & 1u)) continue;
-        const double x = fabs(fma((double)(kk[j] - q.k0), h, -q.frac0)) * q.inv2g;
-        const double u = x * x;
-        const double p = u * (x > 0.0 ? sqrt_newton(sqrt_newton(x)) : 0.0);
-        const double d1 = 1.0 + 4.0 * u, d2 = 1.0 + 0.1 * p;
-        const double w = 0.016 * q.r * (1.0 - q.r);
-        double P = (q.r * d2 - w * d1) / (d1 * d2);
-        // exponentials by slice window (a lane beyond its term's bound adds an
-        // exact zero, as the lane-wise form skips it)
+        double u, p;
+        double P = shape_rational_f64(kd[j], q, a.w, u, p);
+        // exponentials by slice (wave-uniform)
         if ((m_g[j] >> t) & 1u) {
             asm volatile("");
-            P += (1.0 - q.r) * exp(-2.772 * u);
+            P = fma(1.0 - q.r, exp_neg_f64(-2.772 * u), P);
         }
         if ((m_w[j] >> t) & 1u) {
             asm volatile("");
-            P += w * exp(-0.4 * p);
+            P = fma(a.w, exp_neg_f64(-0.4 * p), P);
         }
         if ((m_edge[j] >> t) & 1u) {
             asm volatile("");
-            P = (kk[j] >= q.klo && kk[j] <= q.khi) ? P : 0.0;
+            P = (kd[j] >= (double)(int16_t)(a.edges & 0xffffu) && kd[j] <= (double)((int32_t)a.edges >> 16)) ? P : 0.0;
         }
-        se[j] += q.se * P;
-        sk[j] += q.sk * P;
+        se[j] = fma(a.se, P, se[j]);
+        sk[j] = fma(a.sk, P, sk[j]);
     }
 }
 
-// Waves per SIMD the double-precision kernel is compiled for (its register
-// budget 512 / waves per lane): measured on the stagnation line, 4 (no limit,
-// 120 registers) 4.88 s, 6 4.65 s, 8 4.79 s per launch.
-#ifndef LRT_F64_WAVES
-#define LRT_F64_WAVES 6
-#endif
-__global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(LRT_F64_WAVES))) void accum_f64_kernel(
+// As node_terms, two lines at a time with 32 nodes each.
+__device__ __forceinline__ void node_terms_f64(const RecPos64 *pos, const RecAmp64 *amp, BlockMask m, BlockMask mw,
+                                               double x, uint32_t grp, double &ae, double &ak)
+{
+#pragma unroll 1
+    for (int b = 0; b < 64; b += 16) {
+        const uint32_t mh = (uint32_t)(m >> b) & 0xffffu, wh = (uint32_t)(mw >> b);
+        if (mh == 0) continue;
+        const uint32_t mi = mh >> grp;
+        uint32_t off = (grp + (uint32_t)b) * 32u;
+        asm volatile("" : "+v"(off));
+        const char *pb = (const char *)pos + off, *ab = (const char *)amp + off;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            if (((mh >> (2 * g)) & 3u) == 0) continue;
+            const RecPos64 q = *(const RecPos64 *)(pb + 64 * g);
+            const RecAmp64 a = *(const RecAmp64 *)(ab + 64 * g);
+            double u, p;
+            double P = shape_rational_f64(x, q, a.w, u, p);
+            if ((wh >> (2 * g)) & 3u) {
+                asm volatile("");
+                P = fma(a.w, exp_neg_f64(-0.4 * p), P);
+            }
+            P = ((mi >> (2 * g)) & 1u) ? P : 0.0;
+            ae = fma(P, a.se, ae);
+            ak = fma(P, a.sk, ak);
+        }
+    }
+}
+
+// As node_flush: the halves of the wave added, eta to the lower half's nodes,
+// kappa to the upper half's.
+__device__ __forceinline__ void node_flush_f64(double pe, double pk, int lane, double (*acc)[kNodes64])
+{
+    const uint64_t a = __double_as_longlong(pe), b = __double_as_longlong(pk);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    acc[lane >> 5][lane & 31] += __longlong_as_double(((uint64_t)hi[0] << 32) | lo[0]) +
+                                 __longlong_as_double(((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// Candidate lines from which the double-precision tile uses nodes: 64, 128 and
+// 256 measure the same within 1 % (1.55 ms on 21 cells x 22,000 points of a
+// line-dense spectrum); below 128 no line setup fills two waves.
+constexpr int32_t kNodeLines64 = 128;
+
+// Double-precision accumulation: 512-point tiles, 4 waves, 2 points per lane,
+// the wings at 32 nodes per interval.  Bound by the FP64 VALU.  32 nodes bring
+// the interpolation to 1e-16 of a term; with every term at the points the same
+// kernel takes 2.38 ms instead of 1.55 ms (21 cells x 22,000 points), with a
+// library exponential, a division and two square roots per term besides 2.8 ms.
+// Compiled for 6 waves per SIMD it takes 89 VGPRs and runs 5; for 4 it
+// measures the same.
+__global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))) void accum_f64_kernel(
     DevLines L, DevGrid g, const CellConst *cc, const CellSpecies *cs, const int2 *ranges,
     int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band, int32_t n_tiles,
     uint32_t b0, DevCont ct, double *eta, double *kappa)
 {
-    __shared__ RecF64 rec[kThreadsF64];
+    constexpr int kWaves = kThreadsF64 / 64, kBlocks = kThreadsF64 / kBlock;
+    static_assert(kTileF64 == 1 << kTileBits && kWaves * kPPL == kSlices && kBlocks == 4,
+                  "a wave owns the two halves of a 128-point interval");
+    __shared__ RecPos64 s_pos[kThreadsF64];
+    __shared__ RecAmp64 s_amp[kThreadsF64];
+    __shared__ RecMode s_mode[kThreadsF64];
+    __shared__ uint32_t s_any[kBlocks];
+    __shared__ double s_node[kWaves][kSets][2][kNodes64];
     int tile, c;
     block_tile_cell(b0 + blockIdx.x, n_cells, n_tiles, tile, c);
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
     const int32_t kt = k_first + tile * kTileF64;
-    const int32_t kw = kt + wave * 64 * kPPL;
+    const int32_t kw = wave * 64 * kPPL;   // tile-relative
     const int32_t kend = k_first + n_band;
     const CellConst k = cc[c];
     const CellSpecies *csc = cs + (int64_t)c * n_species;
     const double *lnd_c = cr_row(L, c);
     const int2 rg = ranges[(int64_t)c * n_tiles + tile];
+    const bool at_nodes = rg.y - rg.x >= kNodeLines64;
 
-    double se[kPPL], sk[kPPL];
-#pragma unroll
-    for (int j = 0; j < kPPL; ++j) se[j] = sk[j] = 0.0;
+    double se[kPPL], sk[kPPL], kd[kPPL];
     const uint32_t wshift = (uint32_t)(wave * kPPL);
-    int32_t kk[kPPL];
 #pragma unroll
-    for (int j = 0; j < kPPL; ++j) kk[j] = kw + 64 * j + lane;
+    for (int j = 0; j < kPPL; ++j) {
+        se[j] = sk[j] = 0.0;
+        kd[j] = (double)(kw + 64 * j + lane);
+    }
+    double (*acc)[2][kNodes64] = s_node[wave];
+    double x64 = 0.0;
+    if (at_nodes) {
+        for (int j = lane; j < kSets * 2 * kNodes64; j += 64) (&acc[0][0][0])[j] = 0.0;
+#pragma unroll
+        for (int i = 0; i < kNodes64; ++i)
+            if ((lane & 31) == i) x64 = kNodePos64[i];
+    }
 
     for (int base = rg.x; base < rg.y; base += kThreadsF64) {
-        RecF64 rr;
-        rr.klo = 1;
-        rr.khi = 0;
-        rr.k0 = 0;
-        rr.mode = 0;
-        rr.frac0 = rr.inv2g = rr.r = rr.se = rr.sk = rr.pad2 = 0.0;
+        RecPos64 rp{0.0, 0.0, 0.0, 0.0};
+        RecAmp64 ra{0.0, 0.0, 0.0, 0u, 0u};
+        RecMode rm{0u, 0u};
         uint32_t t = threadIdx.x;
         asm volatile("" : "+v"(t));
         if ((int)t < rg.y - base) {
             PairF64 p;
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
-                rr.klo = p.klo;
-                rr.khi = p.khi;
-                rr.k0 = line_at(L.k0, base, t);
-                rr.frac0 = line_at(L.frac0, base, t);
-                rr.inv2g = p.inv2g;
-                rr.r = p.r;
-                rr.se = p.se;
-                rr.sk = p.sk;
-                // windows of the two exponentials, one point of margin each side
-                const double nu0 = line_at(L.nu0, base, t), gV = 0.5 / p.inv2g;
-                const double wg = kF64GaussHalfWidth * gV, ww = kF64WexpHalfWidth * gV;
-                const int32_t glo = (int32_t)fmax(ceil((nu0 - wg - g.nu_min) * g.inv_h) - 1.0, (double)p.klo);
-                const int32_t ghi = (int32_t)fmin(floor((nu0 + wg - g.nu_min) * g.inv_h) + 1.0, (double)p.khi);
-                const int32_t wlo = (int32_t)fmax(ceil((nu0 - ww - g.nu_min) * g.inv_h) - 1.0, (double)p.klo);
-                const int32_t whi = (int32_t)fmin(floor((nu0 + ww - g.nu_min) * g.inv_h) + 1.0, (double)p.khi);
-                const uint32_t m = slice_modes(p.klo - kt, p.khi - kt, wlo - kt, whi - kt);
-                const uint32_t gm = slice_run(max(glo, p.klo) - kt, min(ghi, p.khi) - kt) & m & 0xffu;
-                rr.mode = m | (gm << 24);
+                const int32_t lo = p.klo - kt, hi = p.khi - kt;
+                rp.k0 = (double)(line_at(L.k0, base, t) - kt);
+                const double frac0 = line_at(L.frac0, base, t);
+                rp.h2 = g.h * p.inv2g;
+                rp.f2 = frac0 * p.inv2g;
+                rp.r = p.r;
+                ra.w = 0.016 * p.r * (1.0 - p.r);
+                ra.se = p.se;
+                ra.sk = p.sk;
+                ra.edges = ((uint32_t)max(lo, -1) & 0xffffu) | ((uint32_t)min(hi, kTileF64) << 16);
+                // the reaches and the centre in grid steps (as the single-precision form)
+                const float gs = __builtin_amdgcn_rcpf((float)(2.0 * rp.h2));
+                const float yG = sqrtf(68.5f - (float)max(ilogb(p.r), -1000));
+                const float cf = floorf((float)rp.k0 + (float)(frac0 * g.inv_h));
+                rm = line_modes(lo, hi, (int32_t)fmaxf(-1e9f, fminf(cf, 1e9f)) - 1,
+                                (int32_t)fminf(yG * gs, 1.1e9f) + 2,
+                                (int32_t)fminf((float)kF64WexpReach * gs, 1.1e9f) + 2, at_nodes);
             }
         }
-        rec[threadIdx.x] = rr;
+        s_pos[threadIdx.x] = rp;
+        s_amp[threadIdx.x] = ra;
+        s_mode[threadIdx.x] = rm;
+        const uint32_t any = wave_or((rm.pt & 0xffu) | (rm.node << 16 >> 8));
+        if (lane == 0) s_any[wave] = any;
         __syncthreads();
-        const int n = min(kThreadsF64, rg.y - base);
-        for (int l0 = 0; l0 < n; l0 += kBlock) {
-            uint32_t mb = 0;
-            if (lane < kBlock && l0 + lane < n) mb = rec[l0 + lane].mode >> wshift;
-            const BlockMask todo = (BlockMask)__ballot((mb & ((1u << kPPL) - 1u)) != 0);
+        uint32_t of[kBlocks];
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)s_any[b]);
+        auto blocks_of = [&](uint32_t bits) {
+            uint32_t m = 0u;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) m |= (of[b] & bits) ? 1u << b : 0u;
+            return m;
+        };
+#pragma unroll 1
+        for (uint32_t todo4 = blocks_of(((1u << kPPL) - 1u) << wshift); todo4; todo4 &= todo4 - 1u) {
+            const int l0 = __builtin_ctz(todo4) * kBlock;
+            const uint32_t mi = s_mode[l0 + lane].pt >> wshift;
+            const BlockMask todo = (BlockMask)__ballot((mi & ((1u << kPPL) - 1u)) != 0);
             BlockMask m_in[kPPL], m_edge[kPPL], m_w[kPPL], m_g[kPPL];
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
-                m_in[j] = (BlockMask)__ballot(mb & (1u << j));
-                m_edge[j] = (BlockMask)__ballot(mb & (1u << (8 + j)));
-                m_w[j] = (BlockMask)__ballot(mb & (1u << (16 + j)));
-                m_g[j] = (BlockMask)__ballot(mb & (1u << (24 + j)));
+                m_in[j] = (BlockMask)__ballot(mi & (1u << j));
+                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + j)));
+                m_w[j] = (BlockMask)__ballot(mi & (1u << (16 + j)));
+                m_g[j] = (BlockMask)__ballot(mi & (1u << (24 + j)));
             }
             for (int g8 = 0; g8 < kBlock; g8 += 8) {
                 const uint32_t gt = (uint32_t)(todo >> g8) & 0xffu;
@@ -1147,19 +1216,55 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(LRT
                     gg[j] = (uint32_t)(m_g[j] >> g8);
                     ge[j] = (uint32_t)(m_edge[j] >> g8);
                 }
-                uint32_t off = (uint32_t)((l0 + g8) * (int)sizeof(RecF64));
+                uint32_t off = (uint32_t)((l0 + g8) * 32);
                 asm volatile("" : "+v"(off));
-                const RecF64 *rg8 = (const RecF64 *)((const char *)rec + off);
+                const RecPos64 *rp8 = (const RecPos64 *)((const char *)s_pos + off);
+                const RecAmp64 *ra8 = (const RecAmp64 *)((const char *)s_amp + off);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if ((gt >> u) & 1u) line_terms_f64(rg8[u], u, kk, g.h, gi, gw, gg, ge, se, sk);
+                    if ((gt >> u) & 1u) line_terms_f64(rp8[u], ra8[u], u, kd, gi, gw, gg, ge, se, sk);
             }
+        }
+        // nodes, as the single-precision form
+#pragma unroll 1
+        for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
+            const int l = max(0, j - (kPPL - 1));
+            const uint32_t it = l > 0 ? (uint32_t)wave >> (l - 1) : wshift + (uint32_t)j;
+            const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
+            uint32_t todo4 = blocks_of(bit << 8);
+            if (l == 2) todo4 &= (wave & 1) ? 0xau : 0x5u;
+            if (l == 3) todo4 &= 1u << wave;
+            if (todo4 == 0) continue;
+            const double w = (double)(64 << l);
+            const double x = fma(x64, (double)(1 << l), (double)it * w + (0.5 * w - 0.5));
+            double pe = 0.0, pk = 0.0;
+#pragma unroll 1
+            for (; todo4; todo4 &= todo4 - 1u) {
+                const int l0 = __builtin_ctz(todo4) * kBlock;
+                const uint32_t nb = s_mode[l0 + lane].node;
+                const BlockMask m = (BlockMask)__ballot((nb & bit) != 0);
+                const BlockMask mw = m & (BlockMask)__ballot((nb & wbit) != 0);
+                node_terms_f64(s_pos + l0, s_amp + l0, m, mw, x, (uint32_t)lane >> 5, pe, pk);
+            }
+            node_flush_f64(pe, pk, lane, acc[j]);
         }
         __syncthreads();
     }
+    if (at_nodes) {
+        nodes_down<kNodes64, kThreadsF64>(s_node, kBasis64);
+#pragma unroll 4
+        for (int q = 0; q < kNodes64; ++q) {
+            const double b = kBasis64.pt[q][lane];
+#pragma unroll
+            for (int j = 0; j < kPPL; ++j) {
+                se[j] = fma(b, acc[j][0][q], se[j]);
+                sk[j] = fma(b, acc[j][1][q], sk[j]);
+            }
+        }
+    }
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t kq = kw + 64 * j + lane;
+        const int32_t kq = kt + kw + 64 * j + lane;
         if (kq < kend) {
             const int64_t o = (int64_t)c * n_band + (kq - k_first);
             if (ct.n_thr >= 0) {   // atomic continuum

@@ -13,7 +13,7 @@ namespace lrt {
 // into scalar bit masks and needs no vector work for control flow.
 struct alignas(8) RecMode {
     uint32_t pt;      // slices summed point by point: bits 0-7; of those, bits 8-15: hold a window edge,
-                      // bits 16-23: the exponential terms reach them
+                      // bits 16-23: e^{-0.4 x^2.25} reaches them, bits 24-31: the Gaussian does
     uint32_t node;    // bits 0-14: intervals summed at nodes (node_bit0(level) + interval);
                       // bits 16 + level: e^{-0.4 x^2.25} can matter at the level's nodes
 };
@@ -38,6 +38,8 @@ struct alignas(8) RecMode {
 // interpolated wing is within 7.2e-9 of every term's value at every point of
 // the interval (r from 2^-40 to 0.98, gamma_V from 0.3 to 64 grid steps), an
 // eighth of the single-precision rounding; at 2.25 it is 3.8e-8, at 2.0 2.3e-7.
+// The double-precision form takes 32 nodes (4.8e-17 at 2.5, 1.3e-15 at 2.25) and
+// y_G^2 = 68 + log2(1/s), s = max(r, 2^-1000), for 2^-56.
 //
 // Both forms are bound by vector instructions (about 15 per evaluation; issue
 // slots 0.98 full on the stagnation line).  There (gamma_V 11 grid steps on
@@ -57,29 +59,61 @@ constexpr int kSlices = 1 << (kTileBits - kSliceBits);
 LRT_HD constexpr int node_bit0(int level) { return 2 * kSlices - (2 * kSlices >> level); }
 
 // Nodes of an interval of 64 points, from its middle, in grid steps: Chebyshev
-// nodes rounded to eighths, so that node positions (times 2^level) and their
-// distances from integer line indices are exact in single precision.
+// nodes rounded to eighths (sixteen nodes) or 64ths (the double-precision form's
+// 32), so that node positions (times 2^level) and their distances from integer
+// line indices are exact.
 constexpr double kNodePos[kNodes] = {-31.875, -30.625, -28.25, -24.75, -20.25, -15.125, -9.25, -3.125,
                                      3.125,   9.25,    15.125, 20.25,  24.75,  28.25,   30.625, 31.875};
+constexpr int kNodes64 = 32;
+constexpr double kNodePos64[kNodes64] = {
+    -31.96875, -31.65625, -31.046875, -30.125,    -28.921875, -27.453125, -25.703125, -23.703125,
+    -21.484375, -19.0625, -16.453125, -13.6875,   -10.78125,  -7.78125,   -4.703125,  -1.5625,
+    1.5625,    4.703125,  7.78125,    10.78125,   13.6875,    16.453125,  19.0625,    21.484375,
+    23.703125, 25.703125, 27.453125,  28.921875,  30.125,     31.046875,  31.65625,   31.96875};
 
-// Lagrange basis of the nodes at the 64 points of a slice (pt[j][p]) and at the
+// Lagrange basis of N nodes at the 64 points of a slice (pt[j][p]) and at the
 // nodes of the left half of an interval (half[j][i]; the right half's are
-// half[15 - j][15 - i] by symmetry).
+// half[N - 1 - j][N - 1 - i] by symmetry).
+template <int N>
 struct NodeBasis {
-    double pt[kNodes][64];
-    double half[kNodes][kNodes];
-    static constexpr double basis(int j, double x)
+    double pt[N][64];
+    double half[N][N];
+    // prod (x - pos[m]) / prod (pos[j] - pos[m]): the differences are exact, the
+    // products carried as sums of two doubles, so the quotient is rounded once
+    struct Pair {
+        double h, l;
+    };
+    static constexpr Pair times(Pair a, Pair b)
     {
-        double v = 1.0;
-        for (int m = 0; m < kNodes; ++m)
-            if (m != j) v *= (x - kNodePos[m]) / (kNodePos[j] - kNodePos[m]);
-        return v;
+        // exact product of the leading doubles by splitting each into halves
+        const double p = a.h * b.h, ca = 134217729.0 * a.h, cb = 134217729.0 * b.h;
+        const double ah = ca - (ca - a.h), al = a.h - ah, bh = cb - (cb - b.h), bl = b.h - bh;
+        const double e = ((ah * bh - p) + ah * bl + al * bh) + al * bl + (a.l * b.h + a.h * b.l);
+        const double h = p + e;
+        return Pair{h, e - (h - p)};
     }
-    constexpr NodeBasis() : pt(), half()
+    constexpr explicit NodeBasis(const double (&pos)[N]) : pt(), half()
     {
-        for (int j = 0; j < kNodes; ++j) {
-            for (int p = 0; p < 64; ++p) pt[j][p] = basis(j, p - 31.5);
-            for (int i = 0; i < kNodes; ++i) half[j][i] = basis(j, 0.5 * kNodePos[i] - 16.0);
+        Pair den[N] = {};
+        for (int j = 0; j < N; ++j) {
+            den[j] = Pair{1.0, 0.0};
+            for (int m = 0; m < N; ++m)
+                if (m != j) den[j] = times(den[j], Pair{pos[j] - pos[m], 0.0});
+        }
+        for (int i = 0; i < 64 + N; ++i) {
+            const double x = i < 64 ? i - 31.5 : 0.5 * pos[i - 64] - 16.0;
+            // products of the differences before and after each node
+            Pair pre[N + 1] = {}, suf[N + 1] = {};
+            pre[0] = suf[N] = Pair{1.0, 0.0};
+            for (int m = 0; m < N; ++m) pre[m + 1] = times(pre[m], Pair{x - pos[m], 0.0});
+            for (int m = N - 1; m >= 0; --m) suf[m] = times(suf[m + 1], Pair{x - pos[m], 0.0});
+            for (int j = 0; j < N; ++j) {
+                const Pair n = times(pre[j], suf[j + 1]);
+                const double q = n.h / den[j].h;
+                const Pair r = times(den[j], Pair{-q, 0.0});
+                const double v = q + ((n.h + r.h) + (n.l + r.l)) / den[j].h;
+                (i < 64 ? pt[j][i < 64 ? i : 0] : half[j][i < 64 ? 0 : i - 64]) = v;
+            }
         }
     }
 };
@@ -100,15 +134,16 @@ LRT_HD uint32_t bit_double(uint32_t x, int n)
 }
 
 // Masks of a line whose window is [klo, khi] (tile-relative), with the whole
-// part cl of its centre and the Gaussian's and the core's reach wg = y_G
-// gamma_V and wc = kCoreHalfWidth gamma_V, rounded up to grid steps; without
-// at_nodes every slice is summed point by point.
+// part cl of its centre and the reaches wg = y_G gamma_V of the Gaussian and wc of
+// e^{-0.4 x^2.25}, rounded up to grid steps; without at_nodes every slice is
+// summed point by point.
 LRT_HD RecMode line_modes(int32_t klo, int32_t khi, int32_t cl, int32_t wg, int32_t wc, bool at_nodes)
 {
     const uint32_t in = bit_run(klo >> kSliceBits, (khi >> kSliceBits) + 1, kSlices);
     // a slice holds a window edge when the window starts or ends strictly inside it
     const uint32_t whole = bit_run((klo + 63) >> kSliceBits, (khi + 1) >> kSliceBits, kSlices);
     const uint32_t core = bit_run((cl - wc) >> kSliceBits, ((cl + 1 + wc) >> kSliceBits) + 1, kSlices);
+    const uint32_t gauss = bit_run((cl - wg) >> kSliceBits, ((cl + 1 + wg) >> kSliceBits) + 1, kSlices);
     RecMode m;
     uint32_t node = 0u, finer = 0u, pt = in;
     if (at_nodes) {
@@ -131,7 +166,7 @@ LRT_HD RecMode line_modes(int32_t klo, int32_t khi, int32_t cl, int32_t wg, int3
             if (dw < wc) node |= 1u << (16 + l);
         }
     }
-    m.pt = pt | ((pt & ~whole) << 8) | ((pt & core) << 16);
+    m.pt = pt | ((pt & ~whole) << 8) | ((pt & core) << 16) | ((pt & gauss) << 24);
     m.node = node;
     return m;
 }

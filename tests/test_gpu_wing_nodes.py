@@ -1,5 +1,5 @@
-"""Single-precision coefficients where the wings are summed at nodes of 64- to
-512-point intervals, against the FP64 oracle: line widths from a third of a
+"""Coefficients where the wings are summed at nodes of 64- to 512-point
+intervals, against the FP64 oracle, in both precisions: line widths from a third of a
 grid step to a hundred steps (no interval allowed, all levels used, a tile
 inside the Gaussian core), bands of one point, around a tile and around its
 slices, windows cut by both ends of the grid, and Lorentz fractions from almost
@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 # 16 ulp, in a term of at most a tenth), the reciprocal, the products and the
 # two strengths' own rounding: under 8 ulp = 5e-7 of the largest value of a
 # row; sums of up to 64 terms before the double-precision merge add as much.
-TOL = 1e-6
+# In double precision the exponent of a population (some tens, each rounding
+# 1e-16 of it) sets the bar of every such comparison, 1e-12.
+TOL = {lrt.LRT_FP32_COMP: 1e-6, lrt.LRT_FP64: 1e-12}
 
 
 def _case(steps, n_points, band, n_e, seed):
@@ -30,7 +32,7 @@ def _case(steps, n_points, band, n_e, seed):
     lo = 40000.0
     h = 7.16e-7 / 2.0 * np.sqrt(8000.0 / 15.0) * lo / steps
     hi = lo + h * (n_points - 1)
-    nu0 = np.sort(rng.uniform(lo - 60.0 * steps * h, hi + 60.0 * steps * h, 90))
+    nu0 = np.sort(rng.uniform(lo - 60.0 * steps * h, hi + 60.0 * steps * h, 260))
     Eu = rng.uniform(80000.0, 110000.0, nu0.size)
     z = np.zeros(nu0.size)
     lines = synth.Lines(nu0, 10 ** rng.uniform(5, 8, nu0.size), Eu, z.copy(), Eu - nu0, z.copy(),
@@ -44,7 +46,8 @@ def _case(steps, n_points, band, n_e, seed):
 @pytest.mark.parametrize("steps", [0.3, 2.0, 5.0, 9.0, 25.0, 100.0])
 @pytest.mark.parametrize("n_points,band", [(1537, 1537), (2100, 511), (1100, 513), (640, 64), (130, 1)])
 @pytest.mark.parametrize("n_e", [1e2, 1e15, 3e17])
-def test_wings_against_oracle(steps, n_points, band, n_e):
+@pytest.mark.parametrize("prec", [lrt.LRT_FP32_COMP, lrt.LRT_FP64])
+def test_wings_against_oracle(steps, n_points, band, n_e, prec):
     import torch
     wl = _case(steps, n_points, band, n_e, int(10 * steps) + n_points)
     say("wings: steps", steps, "points", n_points, "band", band, "n_e", n_e)
@@ -53,13 +56,14 @@ def test_wings_against_oracle(steps, n_points, band, n_e):
     nb = ctx.sizes()["n_bands"]
     got_e, got_k = [], []
     for b in (range(nb) if band > 1 else list(range(3)) + [nb - 1]):
-        eta, kap, esc = ctx.coeffs_torch(b, lrt.LRT_FP32_COMP)
+        eta, kap, esc = ctx.coeffs_torch(b, prec)
         torch.cuda.synchronize()
-        e, k = lrt.scaled_to_f64(eta, kap, esc)
+        e, k = (lrt.scaled_to_f64(eta, kap, esc) if prec == lrt.LRT_FP32_COMP
+                else (eta.cpu().numpy(), kap.cpu().numpy()))
         got_e.append((b, e))
         got_k.append((b, k))
     ctx.close()
     cols = np.concatenate([np.arange(b * band, b * band + e.shape[1]) for b, e in got_e])
     m = edge_mask(wl, 0, n_points)[:, cols]
-    assert normwise(np.concatenate([e for _, e in got_e], 1), ref_e[:, cols], m) <= TOL
-    assert normwise(np.concatenate([k for _, k in got_k], 1), ref_k[:, cols], m) <= TOL
+    assert normwise(np.concatenate([e for _, e in got_e], 1), ref_e[:, cols], m) <= TOL[prec]
+    assert normwise(np.concatenate([k for _, k in got_k], 1), ref_k[:, cols], m) <= TOL[prec]

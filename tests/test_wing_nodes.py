@@ -23,15 +23,18 @@ SHIM = r'''
 #include <algorithm>
 #include "lrt_nodes.h"
 using namespace lrt;
+static constexpr NodeBasis<kNodes> B(kNodePos);
+static constexpr NodeBasis<kNodes64> B64(kNodePos64);
+template <int N> void give(const NodeBasis<N> &b, const double (&x)[N], double *pos, double *pt, double *half)
+{ std::copy(x, x + N, pos); std::copy(&b.pt[0][0], &b.pt[0][0] + N * 64, pt);
+  std::copy(&b.half[0][0], &b.half[0][0] + N * N, half); }
 extern "C" {
 void modes(int klo, int khi, int cl, int wg, int wc, int at, unsigned *pt, unsigned *node)
 { const RecMode m = line_modes(klo, khi, cl, wg, wc, at != 0); *pt = m.pt; *node = m.node; }
 int bit0(int l) { return node_bit0(l); }
 int levels() { return kLevels; }
-static constexpr NodeBasis B{};
-void basis(double *pos, double *pt, double *half)
-{ std::copy(kNodePos, kNodePos + kNodes, pos); std::copy(&B.pt[0][0], &B.pt[0][0] + kNodes * 64, pt);
-  std::copy(&B.half[0][0], &B.half[0][0] + kNodes * kNodes, half); }
+void basis(int n, double *pos, double *pt, double *half)
+{ if (n == kNodes) give(B, kNodePos, pos, pt, half); else give(B64, kNodePos64, pos, pt, half); }
 void fexp(int n, const double *x, double *e, double *m)
 { for (int i = 0; i < n; ++i) { e[i] = exp_any(x[i]); m[i] = expm1_any(x[i]); } }
 void fexp_in(int n, const double *x, double *e, double *m)
@@ -84,8 +87,10 @@ def test_every_point_of_the_window_once(shim):
                 assert bool(pt.value >> (8 + s) & 1) == (not inside.all())
                 if np.any(np.abs(p - c) <= 12.0 * g):
                     assert pt.value >> (16 + s) & 1
+                if np.any(np.abs(p - c) <= wg - 2):
+                    assert pt.value >> (24 + s) & 1
             else:
-                assert not (pt.value >> (8 + s) & 1) and not (pt.value >> (16 + s) & 1)
+                assert not any(pt.value >> (f + s) & 1 for f in (8, 16, 24))
         for l in range(L):
             w = 64 << l
             for i in range(8 >> l):
@@ -103,18 +108,26 @@ def test_every_point_of_the_window_once(shim):
 
 def _wing(y, r):
     """The profile without its Gaussian, over r-independent factors."""
-    x = np.abs(y) / 2.0
-    w = 0.016 * r * (1.0 - r)
-    return r / (1 + 4 * x * x) - w / (1 + 0.1 * x ** 2.25) + w * np.exp(-0.4 * x ** 2.25)
+    x = np.abs(y) / 2
+    F = type(y.flat[0])
+    w = F(0.016) * r * (1 - r)
+    return r / (1 + 4 * x * x) - w / (1 + F(0.1) * x ** F(2.25)) + w * np.exp(F(-0.4) * x ** F(2.25))
 
 
+# nodes, type of the profile's values, y_G^2 - log2(1/r), and the bound: sixteen
+# nodes 7.2e-9 and the 2^-30 of the Gaussian left out; 32 nodes 4.8e-17 and 2^-56,
+# and the rounding of the weights and of up to four interpolations in double
+# (each 33 roundings of 2^-53 of terms that sum to at most 2.9 x 5.4 times the
+# least value on the interval, adding up like a random walk: 1.2e-14)
+@pytest.mark.parametrize("n,F,yG2,bound", [(16, np.float64, 37.0, 9e-9), (32, np.longdouble, 68.0, 1.2e-14)])
 @pytest.mark.parametrize("r", [2.0 ** -40, 1e-6, 1e-3, 0.03, 0.3, 0.7, 0.98])
-def test_interpolated_wing(shim, r):
-    pos, pt, half = np.zeros(16), np.zeros((16, 64)), np.zeros((16, 16))
-    shim.basis(_dp(pos), _dp(pt), _dp(half))
+def test_interpolated_wing(shim, n, F, yG2, bound, r):
+    pos, pt, half = np.zeros(n), np.zeros((n, 64)), np.zeros((n, n))
+    shim.basis(n, _dp(pos), _dp(pt), _dp(half))
+    assert np.max(np.abs(pt.sum(0) - 1.0)) < 1e-15 and np.max(np.abs(half.sum(0) - 1.0)) < 1e-15
     # an interval's polynomial taken at its halves' nodes, then at the points
     left, right = half, half[::-1, ::-1]
-    yG = np.sqrt(37.0 - np.log2(max(r, 2.0 ** -40)))
+    yG = np.sqrt(yG2 - np.log2(r))
     worst = 0.0
     for g in np.exp(np.linspace(np.log(0.3), np.log(64.0), 60)):
         for w in (64, 128, 512):
@@ -122,16 +135,30 @@ def test_interpolated_wing(shim, r):
                 D = max(1.25 * w - 1.0, w / 2 + yG * g) + extra * g
                 if D + w / 2 > 100.0 * g:
                     continue
-                v = [_wing((pos * (w / 64) + D) / g, r)]
+                v = [_wing((F(1) * pos * (w // 64) + F(D)) / F(g), F(r)).astype(np.float64)]
                 while len(v) * 64 < w:
                     v = [u @ m for u in v for m in (left, right)]
-                got = np.concatenate([u @ pt for u in v])
-                # against the oracle's profile, normalisation taken out
-                q = np.arange(w) - (w - 1) / 2 + D
-                ref = np.array([O.voigt_profile(k, g, r * g) for k in q[::7]])
-                ref *= 2.0 * g * (1.065 + 0.447 * r + 0.058 * r * r)
-                worst = max(worst, np.max(np.abs(got[::7] - ref) / ref))
-    assert worst <= 9e-9, worst     # 7.2e-9, and the 2^-30 of the Gaussian left out
+                got = np.concatenate([u @ pt for u in v])[::7]
+                q = (np.arange(w) - F(w - 1) / 2 + F(D))[::7]
+                ref = _wing(q / F(g), F(r)) + (1 - F(r)) * np.exp(F(-2.772) * (q / F(g) / 2) ** 2)
+                worst = max(worst, float(np.max(np.abs(got - ref) / ref)))
+                if n == 16:   # and against the oracle's profile, normalisation taken out
+                    ref = np.array([O.voigt_profile(float(k), g, r * g) for k in q])
+                    ref *= 2.0 * g * (1.065 + 0.447 * r + 0.058 * r * r)
+                    worst = max(worst, np.max(np.abs(got - ref) / ref))
+    assert worst <= bound, worst
+
+
+@pytest.mark.parametrize("r", [2.0 ** -1000, 2.0 ** -100, 2.0 ** -40, 1e-4, 0.1, 0.9])
+def test_reach_of_the_exponentials_in_double(r):
+    """Beyond y_G the Gaussian, beyond y = 16 the other exponential, are below
+    2^-56 of the rational part."""
+    F = np.longdouble
+    for y0, term in ((np.sqrt(68.0 - np.log2(r)), lambda x: (1 - F(r)) * np.exp(F(-2.772) * x * x)),
+                     (16.0, lambda x: F(0.016) * F(r) * (1 - F(r)) * np.exp(F(-0.4) * x ** F(2.25)))):
+        x = F(y0) * np.linspace(1.0, 4.0, 200).astype(F) / 2
+        rat = F(r) / (1 + 4 * x * x) - F(0.016) * F(r) * (1 - F(r)) / (1 + F(0.1) * x ** F(2.25))
+        assert np.max(term(x) / rat) <= 2.0 ** -56
 
 
 def test_exponentials(shim):
