@@ -973,12 +973,12 @@ lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisio
     if (c->rays_cells != c->n_cells)
         return fail(c, LRT_E_STATE, "rays expect %lld cells, %lld set", (long long)c->rays_cells, (long long)c->n_cells);
     lrt_status r;
-    const MarchPlan plan = march_plan(c->n_rays, c->n_cells, n_band, prec == LRT_FP32_COMP);
+    const MarchPlan plan = march_plan(c->n_rays, c->n_cells, n_band, prec == LRT_FP32_COMP, partials ? cap : INT64_MAX);
     const int64_t need = c->n_rays * (int64_t)plan.n_chunks;
     if (partials) {
         // what the caller's buffer is held to: chunks of 128 points from 128
-        // segments per cell on, else of 256 (never fewer sums than the plan's,
-        // but where it takes 128-point chunks for want of waves, which are few)
+        // segments per cell on, else of 256 (the plan takes 128-point chunks only
+        // where the buffer holds their sums)
         const int32_t points = c->h_off.back() >= 128 * c->n_cells ? 128 : 256;
         const int64_t held = c->n_rays * (int64_t)((n_band + points - 1) / points);
         if (std::max(held, need) > cap)

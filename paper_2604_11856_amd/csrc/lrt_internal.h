@@ -50,37 +50,49 @@ constexpr int kTileF64 = kThreadsF64 * kPPL;
 // March tile: one workgroup of 4 waves; each wave marches one ray over one
 // chunk of 64 x ppt consecutive points, ppt per lane, and the waves share no
 // state.
-//   ppt: 256-point chunks, or 128-point ones where those would leave fewer than
-//     three waves per SIMD (kMarchFewWaves).  March time with 256 / 128 points:
-//     782 waves of 256 points (one ray, 64 cells) 40 / 30 us; 944 (8 rays, 131
-//     cells) 69 / 51; 2,304 (384 rays, 2,400 cells) 57 / 43; 4,096 (128 rays,
-//     8,192 cells) 113 / 121; 17 rays on 2^19 points 1.80 / 1.99 ms.
 //   rays: from kMarchManyRays rays on a workgroup takes 4 of them on one chunk,
 //     which then share rows in the L1; below, 4 consecutive chunks of one ray.
-//     4 rays / one ray: 128 rays 133 / 113 us, 256: 191 / 192, 512: 304 / 366,
-//     1,024: 522 / 684, 2,048: 0.99 / 1.26 ms, 4,096: 1.78 / 2.16.
+//     4 rays / one ray: 160 rays 313 / 259 us, 195: 115 / 113, 256: 80 / 85,
+//     735: 195 / 275, 1,024: 522 / 684, 2,048: 0.99 / 1.26 ms, 4,096: 1.78 / 2.16.
+//   ppt: 256-point chunks, or 128-point ones for more, shorter waves:
+//     Few rays: where 256 points leave fewer than three waves per SIMD
+//     (kMarchFewWaves).  256 / 128 points: 782 waves of 256 points (one ray, 64
+//     cells) 40 / 30 us; 944 (8 rays, 131 cells) 69 / 51; 2,624 (16 rays, 181
+//     cells) 172 / 165; 17 rays on 2^19 points 1.80 / 1.99 ms.
+//     Many rays: on bands under kMarchWideBand points, where the XCDs' shares of
+//     the chunks and of the rays' unequal lengths are coarse.  864 rays x 2,436
+//     points 260 / 157 us; 1,120 x 982 422 / 146; 6,144 x 4,000 2.00 / 1.37 ms;
+//     7,168 x 4,000 3.80 / 3.64; 1,024 x 8,192 550 / 559 us; 1,024 x 65,536
+//     4.10 / 4.43 ms; 5,120 x 16,384 2.09 / 2.40.  From kMarchShareRays rays on
+//     the chunk's rows are reused enough for 256 points from 1,024 points on:
+//     8,192 x 2,048 0.81 / 0.90 ms; 131,072 x 1,024 29.8 / 32.4 (both shared);
+//     16,384 x 500 2.10 / 1.24 (both shared).
 //   shared: every XCD on the same chunk (march_item) where the rows of eight
-//     chunks, one per XCD, exceed the last-level cache, and there are many rays
-//     to share them.  32,768 cells, 8,192 rays: 4.13 ms against 4.48 without;
-//     8,192 cells, 4,096 rays: 1.84 against 1.73.
+//     chunks, one per XCD, exceed the last-level cache, and there are very many
+//     rays to share them.  32,768 cells, 8,192 rays: 4.13 ms against 4.48 without;
+//     2,048 rays: 5.84 against 5.10.
 constexpr int kMarchThreads = 256;
 constexpr int64_t kMarchFewWaves = 3072;
 constexpr int32_t kMarchManyRays = 256;
+constexpr int32_t kMarchShareRays = 8192;
+constexpr int32_t kMarchWideBand = 8192;
 constexpr int64_t kLastLevelBytes = int64_t(256) << 20;
 
 struct MarchPlan {
     int32_t ppt, rays, n_chunks;
     bool shared;
 };
-inline MarchPlan march_plan(int64_t n_rays, int64_t n_cells, int32_t n_band, bool fp32)
+// max_sums: rays x chunks that a caller's buffer for the chunks' sums holds.
+inline MarchPlan march_plan(int64_t n_rays, int64_t n_cells, int32_t n_band, bool fp32, int64_t max_sums)
 {
     MarchPlan p;
-    const int64_t wide = n_rays * ((n_band + 255) / 256);
-    p.ppt = wide < kMarchFewWaves ? 2 : 4;
+    const bool many = n_rays >= kMarchManyRays, share = n_rays >= kMarchShareRays;
+    const bool wide = many ? n_band >= (share ? kMarchWideBand / 8 : kMarchWideBand)
+                           : n_rays * ((n_band + 255) / 256) >= kMarchFewWaves;
+    p.ppt = wide || n_rays * ((n_band + 127) / 128) > max_sums ? 4 : 2;
     p.n_chunks = (n_band + 64 * p.ppt - 1) / (64 * p.ppt);
-    p.rays = n_rays >= kMarchManyRays ? 4 : 1;
-    const int64_t rows = 8 * n_cells * (int64_t)(64 * p.ppt) * 2 * (fp32 ? 4 : 8);
-    p.shared = p.rays > 1 && rows > kLastLevelBytes;
+    p.rays = many ? 4 : 1;
+    p.shared = share && 8 * n_cells * int64_t(256) * 2 * (fp32 ? 4 : 8) > kLastLevelBytes;
     return p;
 }
 

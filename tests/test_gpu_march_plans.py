@@ -48,12 +48,25 @@ def _reference(eta, kap, dx, mu, linear):
     return I
 
 
+def _legendre_nodes(n):
+    """Ascending Gauss-Legendre nodes by Newton steps."""
+    x = -np.cos(np.pi * (np.arange(1, n + 1) - 0.25) / (n + 0.5))
+    for _ in range(6 if n else 0):
+        a, b = np.ones(n), x
+        for k in range(2, n + 1):
+            a, b = b, ((2 * k - 1) * x * b - (k - 1) * a) / k
+        x = x - b * (x * x - 1.0) / (n * (x * b - a))
+    return x
+
+
 @pytest.mark.parametrize("n_cells,n_mu,n_points", [
     (1, 0, 1), (2, 0, 129), (63, 3, 257), (64, 3, 512), (65, 2, 301), (128, 0, 130), (129, 1, 1000),
     (5, 254, 70), (5, 255, 70), (66, 258, 333),         # around four rays per workgroup, a last group of 3
     (3, 11, 65536 + 3),                                  # 256-point chunks, one ray per workgroup
-    (3, 300, 256 * 11 + 5),                              # 256-point chunks, four rays
-    (33000, 256, 37),                                    # all XCDs on one chunk
+    (3, 300, 256 * 11 + 5),                              # 128-point chunks, four rays
+    (3, 300, 8191), (3, 258, 8192 + 5),                  # up to and from 256-point chunks
+    (3, 8190, 1024), (3, 8191, 1023), (3, 8191, 1024 + 1),   # and of very many rays
+    (33000, 8192, 37), (33000, 8192, 1030),              # all XCDs on one chunk
 ])
 @pytest.mark.parametrize("depth", [1e-4, 0.5])
 @pytest.mark.parametrize("linear", [False, True])
@@ -62,6 +75,8 @@ def test_march_plans(n_cells, n_mu, n_points, depth, linear, prec):
     import torch
     if n_cells > 1000 and (linear or depth > 0.1):   # 33,000 steps of numpy
         pytest.skip("one large list is enough")
+    if n_cells > 1000 and prec == lrt.LRT_FP64:
+        n_cells //= 2   # the rule is in bytes
     rng = np.random.Generator(np.random.PCG64(n_cells + 7 * n_points))
     dt = np.float64 if prec == lrt.LRT_FP64 else np.float32
     dx = rng.uniform(0.5, 1.5, n_cells)
@@ -76,8 +91,7 @@ def test_march_plans(n_cells, n_mu, n_points, depth, linear, prec):
                               np.ones(n_cells)))
     ctx.set_rays(synth.SlabGeometry(dx, n_mu))
     ctx.set_march(lrt.LRT_MARCH_LINEAR_J if linear else lrt.LRT_MARCH_CELL)
-    x, _ = np.polynomial.legendre.leggauss(n_mu) if n_mu else (np.zeros(0), None)
-    mu = np.concatenate([[1.0], 0.5 * (x + 1.0)])
+    mu = np.concatenate([[1.0], 0.5 * (_legendre_nodes(n_mu) + 1.0)])
     # a base one element past an aligned address: rows start anywhere
     buf = torch.zeros((2, n_cells * n_points + 1), dtype=torch.from_numpy(eta).dtype, device="cuda:0")
     e, k = (b[1:].view(n_cells, n_points) for b in buf)
@@ -88,7 +102,10 @@ def test_march_plans(n_cells, n_mu, n_points, depth, linear, prec):
     s = torch.empty(n_mu + 1, dtype=torch.float64, device="cuda:0")
     ctx.march(0, prec, e, k, esc, I, s)
     torch.cuda.synchronize()
-    ref = _reference(eta.astype(np.float64), kap.astype(np.float64), dx, mu, linear)
-    err = np.max(np.abs(I.cpu().numpy() - ref) / ref.max(axis=1, keepdims=True))
+    # every ray of a small set, some of a large one, and of its points
+    r = np.arange(n_mu + 1) if n_mu * n_points < 1 << 21 else np.sort(rng.choice(n_mu + 1, 24, replace=False))
+    p = np.arange(n_points) if n_cells < 1000 else np.unique(np.concatenate([np.arange(0, n_points, 29), [n_points - 1]]))
+    ref = _reference(eta[:, p].astype(np.float64), kap[:, p].astype(np.float64), dx, mu[r], linear)
+    err = np.max(np.abs(I.cpu().numpy()[r][:, p] - ref) / ref.max(axis=1, keepdims=True))
     assert err <= TOL[prec], err
     ctx.close()
