@@ -744,15 +744,16 @@ __device__ __forceinline__ void node_flush(float pe, float pk, int lane, double 
 // the waves' parts of each interval, then level by level from the whole tile,
 // each interval's polynomial taken at the nodes of its halves.  An interval's
 // sums end up with the first wave under it.  Called by the whole workgroup, after
-// a barrier; ends with one.
+// a barrier, tid the thread of its group; ends with a barrier.
 template <int N, int kThreads>
-__device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][2][N], const NodeBasis<N> &basis)
+__device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][2][N], const NodeBasis<N> &basis,
+                                           int tid)
 {
 #pragma unroll
     for (int l = kLevels - 1; l >= 0; --l) {
         // thread -> (interval, quantity, node)
-        const int node = threadIdx.x % N, qy = threadIdx.x / N % 2;
-        for (int it = threadIdx.x / (2 * N); it < (kSlices >> l); it += kThreads / (2 * N)) {
+        const int node = tid % N, qy = tid / N % 2;
+        for (int it = tid / (2 * N); it < (kSlices >> l); it += kThreads / (2 * N)) {
             const int w0 = l > 0 ? it << (l - 1) : it >> 1, set = l > 0 ? kPPL - 1 + l : it & 1;
             double v = sums[w0][set][qy][node];
             for (int w = 1; w < (1 << l) / 2; ++w) v += sums[w0 + w][set][qy][node];
@@ -770,6 +771,36 @@ __device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][
     }
 }
 
+// Adds the sums of a workgroup's other groups (accum_groups) to those of
+// group 0, in their order.  buf: per group 2 kPPL kThreads doubles of LDS that no
+// thread needs any more.  Called by the whole workgroup.
+template <int kGroups, int kThreads, typename F>
+__device__ __forceinline__ void add_groups(F buf, int group, int tid, double (&se)[kPPL], double (&sk)[kPPL])
+{
+    if constexpr (kGroups > 1) {
+        if (group > 0) {
+            double *b = buf(group);
+#pragma unroll
+            for (int j = 0; j < kPPL; ++j) {
+                b[2 * j * kThreads + tid] = se[j];
+                b[(2 * j + 1) * kThreads + tid] = sk[j];
+            }
+        }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+            for (int o = 1; o < kGroups; ++o) {
+                const double *b = buf(o);
+#pragma unroll
+                for (int j = 0; j < kPPL; ++j) {
+                    se[j] += b[2 * j * kThreads + tid];
+                    sk[j] += b[(2 * j + 1) * kThreads + tid];
+                }
+            }
+        }
+    }
+}
+
 // eta and kappa of one cell on one tile (kTilePoints points starting at the
 // global index kt) in single precision: every round stages kStage candidate
 // lines (one FP64 setup per thread) into LDS, then each wave evaluates the
@@ -778,13 +809,18 @@ __device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][
 // 128-point interval they make, and of each larger one every 2^n-th block of
 // lines, shared with the other waves under it.  Lanes hold the sums in double
 // precision; the function returns eta[j], kappa[j] of point kt + kw + 64 j +
-// lane (scaled by 2^-ese, 2^-esk).  Must be called by the whole workgroup.
-__device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines &L, const DevGrid &g,
+// lane (scaled by 2^-ese, 2^-esk).  Must be called by the whole workgroup: kGroups
+// groups of kAccumThreads threads, of which each takes every kGroups-th round
+// with its own shared memory (sg[group]), tid the thread of the group; group 0
+// returns the results.
+template <int kGroups>
+__device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int tid, const DevLines &L, const DevGrid &g,
                                                     const CellConst &k, const CellSpecies *csc,
                                                     const double *lnd_c, int ese, int esk, int2 rg, int32_t kt,
                                                     int32_t kw, int lane, float (&eta)[kPPL],
                                                     float (&kap)[kPPL])
 {
+    AccumLds &sm = sg[group];
     constexpr int kWaves = kAccumThreads / 64, kBlocks = kStage / kBlock;
     static_assert(kTilePoints == 1 << kTileBits && kPPL == 2 && kWaves * kPPL == kSlices && kBlocks == 4,
                   "a wave owns the two halves of a 128-point interval");
@@ -814,7 +850,8 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
         se[j] = sk[j] = 0.0;
         ae[j] = ak[j] = 0.0f;
     }
-    for (int base = rg.x; base < rg.y; base += kStage) {
+    for (int b0 = rg.x; b0 < rg.y; b0 += kGroups * kStage) {
+        const int base = b0 + group * kStage;
         // stage: one (cell, line) setup per thread, in double precision
         RecPos rp;
         RecAmp ra;
@@ -823,7 +860,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
         ra.edges = rm.pt = rm.node = 0u;
         const int n = rg.y - base;   // lines left
         // (opaque, so that no per-lane line pointers are kept across the rounds)
-        uint32_t t = threadIdx.x;
+        uint32_t t = (uint32_t)tid;
         asm volatile("" : "+v"(t));
         if ((int)t < n) {
             PairF64 p;
@@ -853,9 +890,9 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
                                 (int32_t)fminf((float)kCoreHalfWidth * gs, 1.1e9f) + 2, at_nodes);
             }
         }
-        sm.pos[threadIdx.x] = rp;
-        sm.amp[threadIdx.x] = ra;
-        sm.mode[threadIdx.x] = rm;
+        sm.pos[tid] = rp;
+        sm.amp[tid] = ra;
+        sm.mode[tid] = rm;
         const uint32_t any = wave_or((rm.pt & 0xffu) | (rm.node << 16 >> 8));
         if (lane == 0) sm.any[wave] = any;
         __syncthreads();
@@ -946,7 +983,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
     }
     // node sums to the points
     if (at_nodes) {
-        nodes_down<kNodes, kAccumThreads>(sm.node, kBasis);
+        nodes_down<kNodes, kAccumThreads>(sm.node, kBasis, tid);
 #pragma unroll 8
         for (int q = 0; q < kNodes; ++q) {
             const double c = kBasis.pt[q][lane];
@@ -958,6 +995,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
         }
         __syncthreads();   // the next call clears the sums
     }
+    add_groups<kGroups, kAccumThreads>([&](int o) { return (double *)&sg[o]; }, group, tid, se, sk);
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         eta[j] = (float)se[j];
@@ -965,24 +1003,31 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds &sm, const DevLines
     }
 }
 
-__global__ __launch_bounds__(kAccumThreads) __attribute__((amdgpu_waves_per_eu(LRT_ACCUM_WAVES)))
+template <int kGroups>
+__global__ __launch_bounds__(kAccumThreads *kGroups) __attribute__((amdgpu_waves_per_eu(LRT_ACCUM_WAVES)))
 void accum_f32_kernel(
     DevLines L, DevGrid g, const CellConst *cc, const CellSpecies *cs, const int32_t *escale,
     const int2 *ranges, int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band,
     int32_t n_tiles, uint32_t b0, DevCont ct, float *eta, float *kappa)
 {
-    __shared__ AccumLds sm;
+    static_assert(sizeof(AccumLds) >= 2 * kPPL * kAccumThreads * sizeof(double), "add_groups");
+    __shared__ AccumLds sm[kGroups];
     int tile, c;
     block_tile_cell(b0 + blockIdx.x, n_cells, n_tiles, tile, c);
     // the wave index is uniform across the wave: keep it (and every bound
     // derived from it) in scalar registers so slice tests are scalar branches
-    const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
+    constexpr int kWaves = kAccumThreads / 64;
+    const int lane = threadIdx.x & 63, wave_all = uniform_i(threadIdx.x >> 6);
+    const int group = wave_all / kWaves, wave = wave_all % kWaves;
+    const int tid = threadIdx.x & (kAccumThreads - 1);
     const int32_t kt = k_first + tile * kTilePoints;   // first (global) point of the tile
     const int32_t kw = wave * 64 * kPPL;               // first point of the wave, tile-relative
     const int32_t kend = k_first + n_band;             // exclusive, global
     float e[kPPL], kp[kPPL];
-    accum_cell_tile_f32(sm, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c), escale[2 * c + 0],
-                        escale[2 * c + 1], ranges[(int64_t)c * n_tiles + tile], kt, kw, lane, e, kp);
+    accum_cell_tile_f32<kGroups>(sm, group, tid, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c),
+                                 escale[2 * c + 0], escale[2 * c + 1], ranges[(int64_t)c * n_tiles + tile], kt,
+                                 kw, lane, e, kp);
+    if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         const int32_t kk = kt + kw + 64 * j + lane;
@@ -1096,19 +1141,29 @@ __device__ __forceinline__ void node_flush_f64(double pe, double pk, int lane, d
                                  __longlong_as_double(((uint64_t)hi[1] << 32) | lo[1]);
 }
 
+struct AccumLds64 {
+    RecPos64 pos[kThreadsF64];
+    RecAmp64 amp[kThreadsF64];
+    RecMode mode[kThreadsF64];
+    uint32_t any[kThreadsF64 / kBlock];
+    double node[kThreadsF64 / 64][kSets][2][kNodes64];
+};
+
 // Candidate lines from which the double-precision tile uses nodes: 64, 128 and
-// 256 measure the same within 1 % (1.55 ms on 21 cells x 22,000 points of a
+// 256 measure the same within 1 % (1.82 ms on 24 cells x 20,001 points of a
 // line-dense spectrum); below 128 no line setup fills two waves.
 constexpr int32_t kNodeLines64 = 128;
 
 // Double-precision accumulation: 512-point tiles, 4 waves, 2 points per lane,
 // the wings at 32 nodes per interval.  Bound by the FP64 VALU.  32 nodes bring
 // the interpolation to 1e-16 of a term; with every term at the points the same
-// kernel takes 2.38 ms instead of 1.55 ms (21 cells x 22,000 points), with a
-// library exponential, a division and two square roots per term besides 2.8 ms.
+// kernel takes 2.38 ms instead of 1.82 ms (24 cells x 20,001 points), with a
+// library exponential, a division and two square roots per term besides 3.12 ms.
 // Compiled for 6 waves per SIMD it takes 89 VGPRs and runs 5; for 4 it
 // measures the same.
-__global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))) void accum_f64_kernel(
+template <int kGroups>
+__global__ __launch_bounds__(kThreadsF64 *kGroups) __attribute__((amdgpu_waves_per_eu(kGroups > 2 ? 4 : 6)))
+void accum_f64_kernel(
     DevLines L, DevGrid g, const CellConst *cc, const CellSpecies *cs, const int2 *ranges,
     int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band, int32_t n_tiles,
     uint32_t b0, DevCont ct, double *eta, double *kappa)
@@ -1116,14 +1171,14 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
     constexpr int kWaves = kThreadsF64 / 64, kBlocks = kThreadsF64 / kBlock;
     static_assert(kTileF64 == 1 << kTileBits && kWaves * kPPL == kSlices && kBlocks == 4,
                   "a wave owns the two halves of a 128-point interval");
-    __shared__ RecPos64 s_pos[kThreadsF64];
-    __shared__ RecAmp64 s_amp[kThreadsF64];
-    __shared__ RecMode s_mode[kThreadsF64];
-    __shared__ uint32_t s_any[kBlocks];
-    __shared__ double s_node[kWaves][kSets][2][kNodes64];
+    static_assert(sizeof(AccumLds64) >= 2 * kPPL * kThreadsF64 * sizeof(double), "add_groups");
+    __shared__ AccumLds64 sg[kGroups];
     int tile, c;
     block_tile_cell(b0 + blockIdx.x, n_cells, n_tiles, tile, c);
-    const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave_all = uniform_i(threadIdx.x >> 6);
+    const int group = wave_all / kWaves, wave = wave_all % kWaves;
+    const int tid = threadIdx.x & (kThreadsF64 - 1);
+    AccumLds64 &sm = sg[group];
     const int32_t kt = k_first + tile * kTileF64;
     const int32_t kw = wave * 64 * kPPL;   // tile-relative
     const int32_t kend = k_first + n_band;
@@ -1140,7 +1195,7 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
         se[j] = sk[j] = 0.0;
         kd[j] = (double)(kw + 64 * j + lane);
     }
-    double (*acc)[2][kNodes64] = s_node[wave];
+    double (*acc)[2][kNodes64] = sm.node[wave];
     double x64 = 0.0;
     if (at_nodes) {
         for (int j = lane; j < kSets * 2 * kNodes64; j += 64) (&acc[0][0][0])[j] = 0.0;
@@ -1149,11 +1204,12 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
             if ((lane & 31) == i) x64 = kNodePos64[i];
     }
 
-    for (int base = rg.x; base < rg.y; base += kThreadsF64) {
+    for (int b0r = rg.x; b0r < rg.y; b0r += kGroups * kThreadsF64) {
+        const int base = b0r + group * kThreadsF64;
         RecPos64 rp{0.0, 0.0, 0.0, 0.0};
         RecAmp64 ra{0.0, 0.0, 0.0, 0u, 0u};
         RecMode rm{0u, 0u};
-        uint32_t t = threadIdx.x;
+        uint32_t t = (uint32_t)tid;
         asm volatile("" : "+v"(t));
         if ((int)t < rg.y - base) {
             PairF64 p;
@@ -1177,15 +1233,15 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
                                 (int32_t)fminf((float)kF64WexpReach * gs, 1.1e9f) + 2, at_nodes);
             }
         }
-        s_pos[threadIdx.x] = rp;
-        s_amp[threadIdx.x] = ra;
-        s_mode[threadIdx.x] = rm;
+        sm.pos[tid] = rp;
+        sm.amp[tid] = ra;
+        sm.mode[tid] = rm;
         const uint32_t any = wave_or((rm.pt & 0xffu) | (rm.node << 16 >> 8));
-        if (lane == 0) s_any[wave] = any;
+        if (lane == 0) sm.any[wave] = any;
         __syncthreads();
         uint32_t of[kBlocks];
 #pragma unroll
-        for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)s_any[b]);
+        for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)sm.any[b]);
         auto blocks_of = [&](uint32_t bits) {
             uint32_t m = 0u;
 #pragma unroll
@@ -1195,7 +1251,7 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
 #pragma unroll 1
         for (uint32_t todo4 = blocks_of(((1u << kPPL) - 1u) << wshift); todo4; todo4 &= todo4 - 1u) {
             const int l0 = __builtin_ctz(todo4) * kBlock;
-            const uint32_t mi = s_mode[l0 + lane].pt >> wshift;
+            const uint32_t mi = sm.mode[l0 + lane].pt >> wshift;
             const BlockMask todo = (BlockMask)__ballot((mi & ((1u << kPPL) - 1u)) != 0);
             BlockMask m_in[kPPL], m_edge[kPPL], m_w[kPPL], m_g[kPPL];
 #pragma unroll
@@ -1218,8 +1274,8 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
                 }
                 uint32_t off = (uint32_t)((l0 + g8) * 32);
                 asm volatile("" : "+v"(off));
-                const RecPos64 *rp8 = (const RecPos64 *)((const char *)s_pos + off);
-                const RecAmp64 *ra8 = (const RecAmp64 *)((const char *)s_amp + off);
+                const RecPos64 *rp8 = (const RecPos64 *)((const char *)sm.pos + off);
+                const RecAmp64 *ra8 = (const RecAmp64 *)((const char *)sm.amp + off);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     if ((gt >> u) & 1u) line_terms_f64(rp8[u], ra8[u], u, kd, gi, gw, gg, ge, se, sk);
@@ -1241,17 +1297,17 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
 #pragma unroll 1
             for (; todo4; todo4 &= todo4 - 1u) {
                 const int l0 = __builtin_ctz(todo4) * kBlock;
-                const uint32_t nb = s_mode[l0 + lane].node;
+                const uint32_t nb = sm.mode[l0 + lane].node;
                 const BlockMask m = (BlockMask)__ballot((nb & bit) != 0);
                 const BlockMask mw = m & (BlockMask)__ballot((nb & wbit) != 0);
-                node_terms_f64(s_pos + l0, s_amp + l0, m, mw, x, (uint32_t)lane >> 5, pe, pk);
+                node_terms_f64(sm.pos + l0, sm.amp + l0, m, mw, x, (uint32_t)lane >> 5, pe, pk);
             }
             node_flush_f64(pe, pk, lane, acc[j]);
         }
         __syncthreads();
     }
     if (at_nodes) {
-        nodes_down<kNodes64, kThreadsF64>(s_node, kBasis64);
+        nodes_down<kNodes64, kThreadsF64>(sm.node, kBasis64, tid);
 #pragma unroll 4
         for (int q = 0; q < kNodes64; ++q) {
             const double b = kBasis64.pt[q][lane];
@@ -1261,7 +1317,10 @@ __global__ __launch_bounds__(kThreadsF64) __attribute__((amdgpu_waves_per_eu(6))
                 sk[j] = fma(b, acc[j][1][q], sk[j]);
             }
         }
+        if (kGroups > 1) __syncthreads();   // add_groups overwrites the sums
     }
+    add_groups<kGroups, kThreadsF64>([&](int o) { return (double *)&sg[o]; }, group, tid, se, sk);
+    if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         const int32_t kq = kt + kw + 64 * j + lane;
@@ -1448,7 +1507,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
         for (int32_t c = cs0; c < c1; ++c) {
             float e[kPPL], kp[kPPL];
             const int ese = R.escale[2 * c + 0], esk = R.escale[2 * c + 1];
-            accum_cell_tile_f32(sm, L, g, R.cc[c], R.cs + (int64_t)c * n_species,
+            accum_cell_tile_f32<1>(&sm, 0, threadIdx.x, L, g, R.cc[c], R.cs + (int64_t)c * n_species,
                                 R.lnd ? R.lnd + (int64_t)c * R.lnd_stride : nullptr, ese, esk,
                                 R.ranges[(int64_t)c * R.n_tiles + w.tile], kt, kw, lane, e, kp);
             if (R.ct.n_thr >= 0) {
@@ -1587,10 +1646,14 @@ hipError_t launch_accum_f32(const DevLines &L, const DevGrid &g, const CellConst
     const int32_t n_tiles = (n_band + kTilePoints - 1) / kTilePoints;
     const int64_t n_blocks = (int64_t)n_tiles * n_cells;
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
+    const int groups = accum_groups(n_blocks, L.n, g.n_points, true);
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kMaxLaunchBlocks) {
-        hipLaunchKernelGGL(accum_f32_kernel, dim3((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0)),
-                           dim3(kAccumThreads), 0, st, L, g, cc, cs, escale, ranges, n_cells, n_species,
-                           k_first, n_band, n_tiles, (uint32_t)b0, ct, eta, kappa);
+        const dim3 grid((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0));
+#define LRT_ACCUM(G)                                                                                             \
+    hipLaunchKernelGGL((accum_f32_kernel<G>), grid, dim3(kAccumThreads * G), 0, st, L, g, cc, cs, escale, ranges, \
+                       n_cells, n_species, k_first, n_band, n_tiles, (uint32_t)b0, ct, eta, kappa)
+        if (groups == 4) LRT_ACCUM(4); else if (groups == 2) LRT_ACCUM(2); else LRT_ACCUM(1);
+#undef LRT_ACCUM
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1605,10 +1668,14 @@ hipError_t launch_accum_f64(const DevLines &L, const DevGrid &g, const CellConst
     const int32_t n_tiles = (n_band + kTileF64 - 1) / kTileF64;
     const int64_t n_blocks = (int64_t)n_tiles * n_cells;
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
+    const int groups = accum_groups(n_blocks, L.n, g.n_points, false);
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kMaxLaunchBlocks) {
-        hipLaunchKernelGGL(accum_f64_kernel, dim3((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0)),
-                           dim3(kThreadsF64), 0, st, L, g, cc, cs, ranges, n_cells, n_species, k_first,
-                           n_band, n_tiles, (uint32_t)b0, ct, eta, kappa);
+        const dim3 grid((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0));
+#define LRT_ACCUM(G)                                                                                   \
+    hipLaunchKernelGGL((accum_f64_kernel<G>), grid, dim3(kThreadsF64 * G), 0, st, L, g, cc, cs, ranges, \
+                       n_cells, n_species, k_first, n_band, n_tiles, (uint32_t)b0, ct, eta, kappa)
+        if (groups == 4) LRT_ACCUM(4); else if (groups == 2) LRT_ACCUM(2); else LRT_ACCUM(1);
+#undef LRT_ACCUM
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -47,6 +47,27 @@ constexpr int kStage = kAccumThreads;
 constexpr int kThreadsF64 = 256;
 constexpr int kTileF64 = kThreadsF64 * kPPL;
 
+// Groups of 4 waves per accumulation workgroup.  A workgroup's groups take its
+// rounds of candidate lines in turn, so that a grid of few (cell, tile)
+// workgroups, each a chain of many rounds, still fills the chip: 4 groups up to
+// two workgroups per CU in single precision (one in double precision, whose
+// registers and LDS leave room for half as many waves), 2 up to twice as many.
+// Coefficients with 1 / 2 / 4 groups, us, one line per point:
+//   FP32: 7 workgroups 129 / 87 / 77; 85: 110 / 87 / 60; 256: 368 / 243 / 157;
+//   1,024: 454 / 365 / 348 (0.4 lines per point 245 / 218 / 248); 1,536: 526 / 531 /
+//   498 (288 / 283 / 333); 3,072: 912 / 883 / 932 (468 / 487 / 600).
+//   FP64: 88: 670 / 468 / 361; 256: 1,075 / 707 / 520 (404 / 306 / 276); 768: 1,460 /
+//   1,327 / 1,415 (543 / 570 / 707); 1,024: 1,601 / 1,703 / 1,873.
+// Only with a line per three points or more: with few lines per tile there are
+// no rounds to share (2,124 lines on 7,347 points, 915 workgroups, per solve 89 /
+// 93 / 114 us; below some hundred workgroups all the same).
+inline int accum_groups(int64_t n_blocks, int64_t n_lines, int64_t n_points, bool fp32)
+{
+    if (3 * n_lines < n_points || n_lines > INT32_MAX - 4 * kStage) return 1;
+    const int64_t n = fp32 ? n_blocks : 2 * n_blocks;
+    return n <= 512 ? 4 : n <= 1024 ? 2 : 1;
+}
+
 // March tile: one workgroup of 4 waves; each wave marches one ray over one
 // chunk of 64 x ppt consecutive points, ppt per lane, and the waves share no
 // state.
