@@ -508,7 +508,7 @@ struct __align__(16) RecPos {
 };
 struct __align__(16) RecAmp {
     float se, sk, qg;               // strengths times s and the cell's scale; (1-r) / s
-    uint32_t edges;                 // window, tile-relative, clamped to [-1, tile]: klo | khi << 16 (edge masks)
+    uint32_t edges;                 // window, tile-relative, clamped to the tile: klo | (khi + 1) << 16 (edge masks)
 };
 // Double-precision line record: x = |(k - k0) h2 - f2| with h2 = h/(2 gamma_V),
 // f2 = frac0/(2 gamma_V) and the tile-relative index k.
@@ -517,7 +517,7 @@ struct __align__(16) RecPos64 {
 };
 struct __align__(16) RecAmp64 {
     double w, se, sk;       // 0.016 r (1-r), strengths
-    uint32_t edges, pad;    // window, tile-relative, clamped to [-1, tile]: klo | khi << 16
+    uint32_t edges, pad;    // window, tile-relative, clamped to the tile: klo | (khi + 1) << 16
 };
 
 // The Whiting profile is evaluated in y = (nu_k - nu0) / gamma_V = +-2x, so that
@@ -629,6 +629,16 @@ constexpr int kNodeLines = LRT_NODE_LINES;
 // round, and per wave the node sums of its intervals (its two 64-point ones,
 // then one of each larger size, shared with the other waves under it).
 constexpr int kSets = kPPL + kLevels - 1;
+// Wave w of a group owns slices w and w + 4 of the tile, kSliceStep points apart:
+// a round's lines lie close together in the sorted list, so their windows reach
+// neighbouring slices, which then belong to different waves.  With two
+// neighbouring slices per wave half of the waves waited at a round's end for
+// the other half: stagnation line 392 -> 342 ms, 48 cells x 32,768 points 1.39 ->
+// 1.15 ms, 24 cells x 20,001 points in double precision 1.80 -> 1.39 ms; windows
+// of 300 points (gamma_V 1.5) 13.1 -> 11.7 ms per band of 65,536 points and 400
+// cells.
+constexpr int kSliceStep = 256;
+constexpr uint32_t kOwnSlices = 0x11u;
 struct AccumLds {
     RecPos pos[kStage];
     RecAmp amp[kStage];
@@ -637,10 +647,24 @@ struct AccumLds {
     double node[kAccumThreads / 64][kSets][2][kNodes];
 };
 
+// x on the lanes of the slice at point s0 that are inside a line's window (edges,
+// the same in every lane), zero on the others.  The lane mask is built in
+// scalar registers, whose unit has room beside the vector unit that bounds the
+// accumulation: two vector instructions instead of the seven of unpacking and
+// comparing both bounds (stagnation line 403 -> 392 ms).
+template <typename T>
+__device__ __forceinline__ T in_window(T x, uint32_t edges, int32_t s0)
+{
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)edges);
+    const int32_t a = max((int32_t)(e & 0xffffu) - s0, 0), b = min((int32_t)(e >> 16) - s0, 64);
+    const uint64_t m = (~uint64_t(0) << (a & 63)) & (~uint64_t(0) >> ((64 - b) & 63));
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? x : T(0);
+}
+
 // The terms of one staged line (bit t of the block masks) on this wave's
-// slices, added to the block partials.
+// slices, the first at point s0, added to the block partials.
 template <typename Mask>
-__device__ __forceinline__ void line_terms(const RecPos &qr, const RecAmp &ar, int t, const float (&kf)[kPPL],
+__device__ __forceinline__ void line_terms(const RecPos &qr, const RecAmp &ar, int t, int32_t s0, const float (&kf)[kPPL],
                                            const ShapeConsts &K, const Mask (&m_in)[kPPL],
                                            const Mask (&m_core)[kPPL], const Mask (&m_edge)[kPPL],
                                            float (&ae)[kPPL], float (&ak)[kPPL])
@@ -663,7 +687,7 @@ __device__ __forceinline__ void line_terms(const RecPos &qr, const RecAmp &ar, i
         // slice crossing a window edge: mask the lanes outside
         if ((m_edge[j] >> t) & 1u) {
             asm volatile("");
-            P = (kf[j] >= (float)(int16_t)(a.edges & 0xffffu) && kf[j] <= (float)((int32_t)a.edges >> 16)) ? P : 0.0f;
+            P = in_window(P, a.edges, s0 + kSliceStep * j);
         }
         ae[j] = fmaf(P, a.se, ae[j]);
         ak[j] = fmaf(P, a.sk, ak[j]);
@@ -743,7 +767,7 @@ __device__ __forceinline__ void node_flush(float pe, float pk, int lane, double 
 // The node sums of a tile's intervals brought down to its 64-point intervals:
 // the waves' parts of each interval, then level by level from the whole tile,
 // each interval's polynomial taken at the nodes of its halves.  An interval's
-// sums end up with the first wave under it.  Called by the whole workgroup, after
+// sums end up with the first wave that shares it, a slice's with its wave.  Called by the whole workgroup, after
 // a barrier, tid the thread of its group; ends with a barrier.
 template <int N, int kThreads>
 __device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][2][N], const NodeBasis<N> &basis,
@@ -754,7 +778,8 @@ __device__ __forceinline__ void nodes_down(double (&sums)[kThreads / 64][kSets][
         // thread -> (interval, quantity, node)
         const int node = tid % N, qy = tid / N % 2;
         for (int it = tid / (2 * N); it < (kSlices >> l); it += kThreads / (2 * N)) {
-            const int w0 = l > 0 ? it << (l - 1) : it >> 1, set = l > 0 ? kPPL - 1 + l : it & 1;
+            const int w0 = l > 0 ? it << (l - 1) : it % (kThreads / 64);
+            const int set = l > 0 ? kPPL - 1 + l : it / (kThreads / 64);
             double v = sums[w0][set][qy][node];
             for (int w = 1; w < (1 << l) / 2; ++w) v += sums[w0 + w][set][qy][node];
             if (l < kLevels - 1) {
@@ -805,10 +830,10 @@ __device__ __forceinline__ void add_groups(F buf, int group, int tid, double (&s
 // global index kt) in single precision: every round stages kStage candidate
 // lines (one FP64 setup per thread) into LDS, then each wave evaluates the
 // staged lines on its kPPL slices of 64 points, point by point or at the nodes
-// of the intervals it owns: the 64-point intervals of its slices, the
-// 128-point interval they make, and of each larger one every 2^n-th block of
-// lines, shared with the other waves under it.  Lanes hold the sums in double
-// precision; the function returns eta[j], kappa[j] of point kt + kw + 64 j +
+// of the intervals it owns: the 64-point intervals of its slices, one 128-point
+// interval, and of each larger one every 2^n-th block of lines, shared with
+// other waves.  Lanes hold the sums in double
+// precision; the function returns eta[j], kappa[j] of point kt + kw + kSliceStep j +
 // lane (scaled by 2^-ese, 2^-esk).  Must be called by the whole workgroup: kGroups
 // groups of kAccumThreads threads, of which each takes every kGroups-th round
 // with its own shared memory (sg[group]), tid the thread of the group; group 0
@@ -822,10 +847,9 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
 {
     AccumLds &sm = sg[group];
     constexpr int kWaves = kAccumThreads / 64, kBlocks = kStage / kBlock;
-    static_assert(kTilePoints == 1 << kTileBits && kPPL == 2 && kWaves * kPPL == kSlices && kBlocks == 4,
-                  "a wave owns the two halves of a 128-point interval");
-    const uint32_t wave = (uint32_t)(kw / (64 * kPPL));
-    const uint32_t wshift = wave * kPPL;   // first slice of this wave
+    static_assert(kTilePoints == 1 << kTileBits && kPPL == 2 && kSliceStep == 64 * kWaves && kWaves * kPPL == kSlices && kBlocks == 4,
+                  "a wave owns two slices and one 128-point interval");
+    const uint32_t wave = (uint32_t)(kw / 64);
     const ShapeConsts K = shape_consts();
     float kf[kPPL];
     float ae[kPPL], ak[kPPL];
@@ -845,7 +869,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
     }
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        kf[j] = (float)(kw + 64 * j + lane);
+        kf[j] = (float)(kw + kSliceStep * j + lane);
         asm volatile("" : "+v"(kf[j]));   // keep the float index in a register
         se[j] = sk[j] = 0.0;
         ae[j] = ak[j] = 0.0f;
@@ -877,8 +901,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
                 ra.qg = (float)((1.0 - p.r) * isc);
                 ra.se = (float)ldexp(p.se * sc, -ese);
                 ra.sk = (float)ldexp(p.sk * sc, -esk);
-                // small integers: the lanes compare their float index
-                ra.edges = ((uint32_t)max(lo, -1) & 0xffffu) | ((uint32_t)min(hi, kTilePoints) << 16);
+                ra.edges = (uint32_t)min(max(lo, 0), kTilePoints) | ((uint32_t)min(max(hi + 1, 0), kTilePoints) << 16);
                 // gamma_V, the two reaches and the centre in grid steps, the reaches
                 // rounded up and the centre down with a step of margin (k0 is
                 // clamped on very long grids, so the centre includes frac0)
@@ -910,16 +933,16 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
             return m;
         };
 #pragma unroll 1
-        for (uint32_t todo4 = blocks_of(((1u << kPPL) - 1u) << wshift); todo4; todo4 &= todo4 - 1u) {
+        for (uint32_t todo4 = blocks_of(kOwnSlices << wave); todo4; todo4 &= todo4 - 1u) {
             const int l0 = __builtin_ctz(todo4) * kBlock;
-            const uint32_t mi = sm.mode[l0 + lane].pt >> wshift;
-            const BlockMask todo = (BlockMask)__ballot((mi & ((1u << kPPL) - 1u)) != 0);
+            const uint32_t mi = sm.mode[l0 + lane].pt >> wave;
+            const BlockMask todo = (BlockMask)__ballot((mi & kOwnSlices) != 0);
             BlockMask m_in[kPPL], m_edge[kPPL], m_core[kPPL];
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
-                m_in[j] = (BlockMask)__ballot(mi & (1u << j));
-                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + j)));
-                m_core[j] = (BlockMask)__ballot(mi & (1u << (16 + j)));
+                m_in[j] = (BlockMask)__ballot(mi & (1u << (kWaves * j)));
+                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + kWaves * j)));
+                m_core[j] = (BlockMask)__ballot(mi & (1u << (16 + kWaves * j)));
             }
             // groups of 8 lines: within a group the LDS offsets are constants
             // from one base address held in a vector register, and the block
@@ -943,7 +966,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
                 const RecAmp *ra8 = (const RecAmp *)((const char *)sm.amp + off);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if ((gt >> u) & 1u) line_terms(rp8[u], ra8[u], u, kf, K, gi, gc, ge, ae, ak);
+                    if ((gt >> u) & 1u) line_terms(rp8[u], ra8[u], u, kw, kf, K, gi, gc, ge, ae, ak);
             }
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
@@ -955,11 +978,11 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         // Nodes, one interval after the other over the whole round (at most 64
         // terms per lane, added plainly): the two 64-point intervals, then of
         // level l interval wave >> (l-1), whose blocks of lines the 2^(l-1)
-        // waves under it share.
+        // waves wave>>(l-1) << (l-1) on share.
 #pragma unroll 1
         for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
             const int l = max(0, j - (kPPL - 1));
-            const uint32_t it = l > 0 ? wave >> (l - 1) : wshift + (uint32_t)j;
+            const uint32_t it = l > 0 ? wave >> (l - 1) : (uint32_t)(wave + kWaves * j);
             const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
             uint32_t todo4 = blocks_of(bit << 8);
             // the blocks b with b = wave (mod 2^(l-1))
@@ -1021,7 +1044,7 @@ void accum_f32_kernel(
     const int group = wave_all / kWaves, wave = wave_all % kWaves;
     const int tid = threadIdx.x & (kAccumThreads - 1);
     const int32_t kt = k_first + tile * kTilePoints;   // first (global) point of the tile
-    const int32_t kw = wave * 64 * kPPL;               // first point of the wave, tile-relative
+    const int32_t kw = wave * 64;               // first point of the wave, tile-relative
     const int32_t kend = k_first + n_band;             // exclusive, global
     float e[kPPL], kp[kPPL];
     accum_cell_tile_f32<kGroups>(sm, group, tid, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c),
@@ -1030,7 +1053,7 @@ void accum_f32_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t kk = kt + kw + 64 * j + lane;
+        const int32_t kk = kt + kw + kSliceStep * j + lane;
         if (kk < kend) {
             const int64_t o = (int64_t)c * n_band + (kk - k_first);
             if (ct.n_thr >= 0) {
@@ -1070,7 +1093,8 @@ __device__ __forceinline__ double exp_neg_f64(double v) { return exp_of(exp_part
 // The terms of one staged line (bit t of the block masks) on this wave's
 // slices of points kd[j], added to the sums.
 template <typename Mask>
-__device__ __forceinline__ void line_terms_f64(const RecPos64 &qr, const RecAmp64 &ar, int t, const double (&kd)[kPPL],
+__device__ __forceinline__ void line_terms_f64(const RecPos64 &qr, const RecAmp64 &ar, int t, int32_t s0,
+                                               const double (&kd)[kPPL],
                                                const Mask (&m_in)[kPPL], const Mask (&m_w)[kPPL],
                                                const Mask (&m_g)[kPPL], const Mask (&m_edge)[kPPL],
                                                double (&se)[kPPL], double (&sk)[kPPL])
@@ -1093,7 +1117,7 @@ __device__ __forceinline__ void line_terms_f64(const RecPos64 &qr, const RecAmp6
         }
         if ((m_edge[j] >> t) & 1u) {
             asm volatile("");
-            P = (kd[j] >= (double)(int16_t)(a.edges & 0xffffu) && kd[j] <= (double)((int32_t)a.edges >> 16)) ? P : 0.0;
+            P = in_window(P, a.edges, s0 + kSliceStep * j);
         }
         se[j] = fma(a.se, P, se[j]);
         sk[j] = fma(a.sk, P, sk[j]);
@@ -1150,7 +1174,7 @@ struct AccumLds64 {
 };
 
 // Candidate lines from which the double-precision tile uses nodes: 64, 128 and
-// 256 measure the same within 1 % (1.82 ms on 24 cells x 20,001 points of a
+// 256 measure the same within 1 % (1.82 ms, 1.39 since, on 24 cells x 20,001 points of a
 // line-dense spectrum); below 128 no line setup fills two waves.
 constexpr int32_t kNodeLines64 = 128;
 
@@ -1169,8 +1193,8 @@ void accum_f64_kernel(
     uint32_t b0, DevCont ct, double *eta, double *kappa)
 {
     constexpr int kWaves = kThreadsF64 / 64, kBlocks = kThreadsF64 / kBlock;
-    static_assert(kTileF64 == 1 << kTileBits && kWaves * kPPL == kSlices && kBlocks == 4,
-                  "a wave owns the two halves of a 128-point interval");
+    static_assert(kTileF64 == 1 << kTileBits && kSliceStep == 64 * kWaves && kWaves * kPPL == kSlices && kBlocks == 4,
+                  "a wave owns two slices and one 128-point interval");
     static_assert(sizeof(AccumLds64) >= 2 * kPPL * kThreadsF64 * sizeof(double), "add_groups");
     __shared__ AccumLds64 sg[kGroups];
     int tile, c;
@@ -1180,7 +1204,7 @@ void accum_f64_kernel(
     const int tid = threadIdx.x & (kThreadsF64 - 1);
     AccumLds64 &sm = sg[group];
     const int32_t kt = k_first + tile * kTileF64;
-    const int32_t kw = wave * 64 * kPPL;   // tile-relative
+    const int32_t kw = wave * 64;   // tile-relative
     const int32_t kend = k_first + n_band;
     const CellConst k = cc[c];
     const CellSpecies *csc = cs + (int64_t)c * n_species;
@@ -1189,11 +1213,10 @@ void accum_f64_kernel(
     const bool at_nodes = rg.y - rg.x >= kNodeLines64;
 
     double se[kPPL], sk[kPPL], kd[kPPL];
-    const uint32_t wshift = (uint32_t)(wave * kPPL);
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
         se[j] = sk[j] = 0.0;
-        kd[j] = (double)(kw + 64 * j + lane);
+        kd[j] = (double)(kw + kSliceStep * j + lane);
     }
     double (*acc)[2][kNodes64] = sm.node[wave];
     double x64 = 0.0;
@@ -1223,7 +1246,7 @@ void accum_f64_kernel(
                 ra.w = 0.016 * p.r * (1.0 - p.r);
                 ra.se = p.se;
                 ra.sk = p.sk;
-                ra.edges = ((uint32_t)max(lo, -1) & 0xffffu) | ((uint32_t)min(hi, kTileF64) << 16);
+                ra.edges = (uint32_t)min(max(lo, 0), kTileF64) | ((uint32_t)min(max(hi + 1, 0), kTileF64) << 16);
                 // the reaches and the centre in grid steps (as the single-precision form)
                 const float gs = __builtin_amdgcn_rcpf((float)(2.0 * rp.h2));
                 const float yG = sqrtf(68.5f - (float)max(ilogb(p.r), -1000));
@@ -1249,17 +1272,17 @@ void accum_f64_kernel(
             return m;
         };
 #pragma unroll 1
-        for (uint32_t todo4 = blocks_of(((1u << kPPL) - 1u) << wshift); todo4; todo4 &= todo4 - 1u) {
+        for (uint32_t todo4 = blocks_of(kOwnSlices << wave); todo4; todo4 &= todo4 - 1u) {
             const int l0 = __builtin_ctz(todo4) * kBlock;
-            const uint32_t mi = sm.mode[l0 + lane].pt >> wshift;
-            const BlockMask todo = (BlockMask)__ballot((mi & ((1u << kPPL) - 1u)) != 0);
+            const uint32_t mi = sm.mode[l0 + lane].pt >> wave;
+            const BlockMask todo = (BlockMask)__ballot((mi & kOwnSlices) != 0);
             BlockMask m_in[kPPL], m_edge[kPPL], m_w[kPPL], m_g[kPPL];
 #pragma unroll
             for (int j = 0; j < kPPL; ++j) {
-                m_in[j] = (BlockMask)__ballot(mi & (1u << j));
-                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + j)));
-                m_w[j] = (BlockMask)__ballot(mi & (1u << (16 + j)));
-                m_g[j] = (BlockMask)__ballot(mi & (1u << (24 + j)));
+                m_in[j] = (BlockMask)__ballot(mi & (1u << (kWaves * j)));
+                m_edge[j] = (BlockMask)__ballot(mi & (1u << (8 + kWaves * j)));
+                m_w[j] = (BlockMask)__ballot(mi & (1u << (16 + kWaves * j)));
+                m_g[j] = (BlockMask)__ballot(mi & (1u << (24 + kWaves * j)));
             }
             for (int g8 = 0; g8 < kBlock; g8 += 8) {
                 const uint32_t gt = (uint32_t)(todo >> g8) & 0xffu;
@@ -1278,14 +1301,14 @@ void accum_f64_kernel(
                 const RecAmp64 *ra8 = (const RecAmp64 *)((const char *)sm.amp + off);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if ((gt >> u) & 1u) line_terms_f64(rp8[u], ra8[u], u, kd, gi, gw, gg, ge, se, sk);
+                    if ((gt >> u) & 1u) line_terms_f64(rp8[u], ra8[u], u, kw, kd, gi, gw, gg, ge, se, sk);
             }
         }
         // nodes, as the single-precision form
 #pragma unroll 1
         for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
             const int l = max(0, j - (kPPL - 1));
-            const uint32_t it = l > 0 ? (uint32_t)wave >> (l - 1) : wshift + (uint32_t)j;
+            const uint32_t it = l > 0 ? (uint32_t)wave >> (l - 1) : (uint32_t)(wave + kWaves * j);
             const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
             uint32_t todo4 = blocks_of(bit << 8);
             if (l == 2) todo4 &= (wave & 1) ? 0xau : 0x5u;
@@ -1323,7 +1346,7 @@ void accum_f64_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t kq = kt + kw + 64 * j + lane;
+        const int32_t kq = kt + kw + kSliceStep * j + lane;
         if (kq < kend) {
             const int64_t o = (int64_t)c * n_band + (kq - k_first);
             if (ct.n_thr >= 0) {   // atomic continuum
@@ -1425,7 +1448,7 @@ __device__ __forceinline__ void linear_j_step(const float (&fe)[kPPL], const flo
     const float Lk = (float)fmin(ldexp(Ls, fek), 3.0e38);
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        int32_t loc = kw + 64 * j + lane;
+        int32_t loc = kw + kSliceStep * j + lane;
         asm volatile("" : "+v"(loc));   // recomputed here, not held across the accumulation
         const float t = fk[j] * Lk;
         const float ex = __builtin_amdgcn_exp2f(t * (float)(-kLog2e));
@@ -1447,7 +1470,7 @@ __device__ __forceinline__ void serve_compose_tile(const ServeReq &R, const DevG
     double part = 0.0;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t loc = kw + 64 * j + lane;
+        const int32_t loc = kw + kSliceStep * j + lane;
         const int32_t t = tile * kTilePoints + loc;
         if (t < R.n_window) {
             double I = R.T_far > 0.0 ? planck_f64(g.nu_min + (double)(R.k_first + t) * g.h, R.T_far) : 0.0;
@@ -1461,7 +1484,7 @@ __device__ __forceinline__ void serve_compose_tile(const ServeReq &R, const DevG
         }
     }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if (lane == 0) s_part[kw / (64 * kPPL)] = part;
+    if (lane == 0) s_part[kw / 64] = part;
     __syncthreads();
     if (threadIdx.x == 0) {
         double sum = 0.0;
@@ -1477,7 +1500,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
     __shared__ int32_t s_last;
     __shared__ double s_part[kAccumThreads / 64];
     const int lane = threadIdx.x & 63, wave = uniform_i(threadIdx.x >> 6);
-    const int32_t kw = wave * 64 * kPPL;
+    const int32_t kw = wave * 64;
     {
         const ServeItem w = items[blockIdx.x];
         // the request's fields are read where used: held in registers across
@@ -1492,7 +1515,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
         double *ts = R.TS + ((int64_t)w.tile * R.n_chunks + w.chunk) * 2 * kTilePoints;
 #pragma unroll
         for (int j = 0; j < kPPL; ++j) {
-            const int32_t loc = kw + 64 * j + lane;
+            const int32_t loc = kw + kSliceStep * j + lane;
             ts[loc] = 1.0;
             ts[kTilePoints + loc] = 0.0;
         }
@@ -1516,7 +1539,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
                 for (int j = 0; j < kPPL; ++j) {
                     // (recomputed per cell: the per-point parts hoisted out of
                     // the cell loop would be spilled across the accumulation)
-                    int32_t kk = kt + kw + 64 * j + lane;
+                    int32_t kk = kt + kw + kSliceStep * j + lane;
                     asm volatile("" : "+v"(kk));
                     const double nu = g.nu_min + (double)kk * g.h;
                     double ce, ck;
@@ -1532,7 +1555,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
                 segment_scales(ds, ese, esk, dsu, dsl);
 #pragma unroll
                 for (int j = 0; j < kPPL; ++j) {
-                    int32_t loc = kw + 64 * j + lane;
+                    int32_t loc = kw + kSliceStep * j + lane;
                     asm volatile("" : "+v"(loc));
                     double at, em;
                     segment_f32(e[j], kp[j], dsu, dsl, at, em);

@@ -20,9 +20,9 @@ constexpr double kPi = 3.14159265358979323846;
 // one workgroup owns 256 * kPPL consecutive points of one cell.  The
 // accumulation kernels are compiled for LRT_ACCUM_WAVES waves per SIMD
 // (register budget 512 / waves per lane).  Measured on the 400-cell, 2.2M-line
-// stagnation case: 8 waves 400 ms, 7 waves 404 ms, 6 waves 427 ms; 1,024-point
-// tiles of 8 waves, which set up fewer (cell, line) pairs but leave more waves
-// waiting at the rounds' barriers, 429 ms.  At 8 waves the FP64 staging code
+// stagnation case, when it took 400 ms with 8 waves: 7 waves 404 ms, 6 waves 427
+// ms; 1,024-point tiles of 8 waves, which set up fewer (cell, line) pairs but
+// leave more waves waiting at the rounds' barriers, 429 ms.  At 8 waves the FP64 staging code
 // fits the 64-register budget only if the compiler's machine-level loop
 // invariant motion is off (it hoists FP64 constants into registers that then
 // spill); the build passes that option for the accumulation's unit.

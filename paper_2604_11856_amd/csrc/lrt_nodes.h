@@ -45,9 +45,10 @@ struct alignas(8) RecMode {
 // slots 0.98 full on the stagnation line).  There (gamma_V 11 grid steps on
 // average, windows of 2,300 points) a tile took 9,400 slice evaluations point by
 // point; it takes 2,450 (around the centre and at the window's two edges) and
-// 1,420 of four lines at sixteen nodes: accumulation 815 -> 390 ms.  With windows
-// of 300 points (gamma_V 1.5) little is away from centre and edge: 13.2 -> 13.0
-// ms per band of 65,536 points and 400 cells.
+// 1,420 of four lines at sixteen nodes: accumulation 815 -> 390 ms (341 with the
+// waves' slices apart and the edges masked in scalar registers).  With windows of
+// 300 points (gamma_V 1.5) little is away from centre and edge: 13.2 -> 13.0 ms
+// per band of 65,536 points and 400 cells.
 // ---------------------------------------------------------------------------
 constexpr int kNodes = 16;
 constexpr float kNodeReach = 2.5f;
