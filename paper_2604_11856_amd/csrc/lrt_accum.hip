@@ -183,6 +183,29 @@ __device__ __forceinline__ T line_at(const T *a, int64_t i0, uint32_t t)
 }
 
 // Line i0 + t of the list, i0 the same for the whole wave.
+// The line list's pointers and a cell's constants, read again (scalar loads) for
+// every round of setups: held across the kernel they do not fit in the scalar
+// registers beside the masks, and come back from spills by one vector
+// instruction per register (stagnation line 343 -> 330 ms, one served request
+// 2.25 -> 2.12 ms; the double-precision kernel 89 -> 64 VGPRs).  DevLines is the
+// first argument of the kernels that use lines_arg.
+template <typename T>
+__device__ __forceinline__ const T &reread(const T *p)
+{
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    auto q = (const __attribute__((address_space(4))) T *)(((uint64_t)hi << 32) | lo);
+    asm volatile("" : "+s"(q));
+    return *(const T *)q;
+}
+__device__ __forceinline__ const DevLines &lines_arg()
+{
+    auto q = (const __attribute__((address_space(4))) DevLines *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));
+    return *(const DevLines *)q;
+}
+
 __device__ __forceinline__ bool pair_setup(const DevLines &L, const DevGrid &g, const CellConst &k,
                                            const CellSpecies *csc, const double *lnd_c, int64_t i0, uint32_t t,
                                            PairF64 &p)
@@ -839,8 +862,8 @@ __device__ __forceinline__ void add_groups(F buf, int group, int tid, double (&s
 // with its own shared memory (sg[group]), tid the thread of the group; group 0
 // returns the results.
 template <int kGroups>
-__device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int tid, const DevLines &L, const DevGrid &g,
-                                                    const CellConst &k, const CellSpecies *csc,
+__device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int tid, const DevGrid &g,
+                                                    const CellConst &kc, const CellSpecies *csc,
                                                     const double *lnd_c, int ese, int esk, int2 rg, int32_t kt,
                                                     int32_t kw, int lane, float (&eta)[kPPL],
                                                     float (&kap)[kPPL])
@@ -888,6 +911,8 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         asm volatile("" : "+v"(t));
         if ((int)t < n) {
             PairF64 p;
+            const DevLines &L = lines_arg();
+            const CellConst &k = reread(&kc);
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
                 const double frac0 = line_at(L.frac0, base, t);
@@ -908,7 +933,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
                 const float gs = __builtin_amdgcn_rcpf(rp.hg);
                 const float yG = __builtin_amdgcn_sqrtf(37.0f - __builtin_amdgcn_logf((float)sc));
                 const float cf = floorf(fmaf(rp.fg, gs, rp.k0f));
-                rm = line_modes(lo, hi, (int32_t)fmaxf(-1e9f, fminf(cf, 1e9f)) - 1,
+                rm = line_modes<false>(lo, hi, (int32_t)fmaxf(-1e9f, fminf(cf, 1e9f)) - 1,
                                 (int32_t)fminf(yG * gs, 1.1e9f) + 2,
                                 (int32_t)fminf((float)kCoreHalfWidth * gs, 1.1e9f) + 2, at_nodes);
             }
@@ -1047,7 +1072,7 @@ void accum_f32_kernel(
     const int32_t kw = wave * 64;               // first point of the wave, tile-relative
     const int32_t kend = k_first + n_band;             // exclusive, global
     float e[kPPL], kp[kPPL];
-    accum_cell_tile_f32<kGroups>(sm, group, tid, L, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c),
+    accum_cell_tile_f32<kGroups>(sm, group, tid, g, cc[c], cs + (int64_t)c * n_species, cr_row(L, c),
                                  escale[2 * c + 0], escale[2 * c + 1], ranges[(int64_t)c * n_tiles + tile], kt,
                                  kw, lane, e, kp);
     if (group > 0) return;
@@ -1183,8 +1208,7 @@ constexpr int32_t kNodeLines64 = 128;
 // the interpolation to 1e-16 of a term; with every term at the points the same
 // kernel takes 2.38 ms instead of 1.82 ms (24 cells x 20,001 points), with a
 // library exponential, a division and two square roots per term besides 3.12 ms.
-// Compiled for 6 waves per SIMD it takes 89 VGPRs and runs 5; for 4 it
-// measures the same.
+// Its LDS leaves room for 5 waves per SIMD.
 template <int kGroups>
 __global__ __launch_bounds__(kThreadsF64 *kGroups) __attribute__((amdgpu_waves_per_eu(kGroups > 2 ? 4 : 6)))
 void accum_f64_kernel(
@@ -1206,7 +1230,7 @@ void accum_f64_kernel(
     const int32_t kt = k_first + tile * kTileF64;
     const int32_t kw = wave * 64;   // tile-relative
     const int32_t kend = k_first + n_band;
-    const CellConst k = cc[c];
+    const CellConst &kc = cc[c];
     const CellSpecies *csc = cs + (int64_t)c * n_species;
     const double *lnd_c = cr_row(L, c);
     const int2 rg = ranges[(int64_t)c * n_tiles + tile];
@@ -1236,6 +1260,8 @@ void accum_f64_kernel(
         asm volatile("" : "+v"(t));
         if ((int)t < rg.y - base) {
             PairF64 p;
+            const DevLines &L = lines_arg();
+            const CellConst &k = reread(&kc);
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
                 rp.k0 = (double)(line_at(L.k0, base, t) - kt);
@@ -1530,7 +1556,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
         for (int32_t c = cs0; c < c1; ++c) {
             float e[kPPL], kp[kPPL];
             const int ese = R.escale[2 * c + 0], esk = R.escale[2 * c + 1];
-            accum_cell_tile_f32<1>(&sm, 0, threadIdx.x, L, g, R.cc[c], R.cs + (int64_t)c * n_species,
+            accum_cell_tile_f32<1>(&sm, 0, threadIdx.x, g, R.cc[c], R.cs + (int64_t)c * n_species,
                                 R.lnd ? R.lnd + (int64_t)c * R.lnd_stride : nullptr, ese, esk,
                                 R.ranges[(int64_t)c * R.n_tiles + w.tile], kt, kw, lane, e, kp);
             if (R.ct.n_thr >= 0) {

@@ -51,7 +51,7 @@ constexpr int kTileF64 = kThreadsF64 * kPPL;
 // rounds of candidate lines in turn, so that a grid of few (cell, tile)
 // workgroups, each a chain of many rounds, still fills the chip: 4 groups up to
 // two workgroups per CU in single precision (one in double precision, whose
-// registers and LDS leave room for half as many waves), 2 up to twice as many.
+// LDS leaves room for half as many waves), 2 up to twice as many.
 // Coefficients with 1 / 2 / 4 groups, us, one line per point:
 //   FP32: 7 workgroups 129 / 87 / 77; 85: 110 / 87 / 60; 256: 368 / 243 / 157;
 //   1,024: 454 / 365 / 348 (0.4 lines per point 245 / 218 / 248); 1,536: 526 / 531 /

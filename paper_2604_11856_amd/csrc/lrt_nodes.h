@@ -122,8 +122,11 @@ struct NodeBasis {
 // Bits a..b-1 of a mask of n <= 8 bits (clamped to it; none when a >= b).
 LRT_HD uint32_t bit_run(int32_t a, int32_t b, int32_t n)
 {
-    const int32_t lo = a < 0 ? 0 : a < n ? a : n, hi = b < 0 ? 0 : b < n ? b : n;
-    return (~0u << lo) & ~(~0u << hi);
+    int32_t lo = a > 0 ? a : 0, hi = b > 0 ? b : 0;
+    lo = lo < n ? lo : n;
+    hi = hi < n ? hi : n;
+    const int32_t w = hi > lo ? hi - lo : 0;
+    return ((1u << w) - 1u) << lo;
 }
 
 // Every bit of a mask of n <= 4 bits doubled.
@@ -137,7 +140,9 @@ LRT_HD uint32_t bit_double(uint32_t x, int n)
 // Masks of a line whose window is [klo, khi] (tile-relative), with the whole
 // part cl of its centre and the reaches wg = y_G gamma_V of the Gaussian and wc of
 // e^{-0.4 x^2.25}, rounded up to grid steps; without at_nodes every slice is
-// summed point by point.
+// summed point by point, kGauss the Gaussian's mask is wanted (the single-precision
+// form takes both exponentials where either reaches).
+template <bool kGauss = true>
 LRT_HD RecMode line_modes(int32_t klo, int32_t khi, int32_t cl, int32_t wg, int32_t wc, bool at_nodes)
 {
     const uint32_t in = bit_run(klo >> kSliceBits, (khi >> kSliceBits) + 1, kSlices);
@@ -167,7 +172,7 @@ LRT_HD RecMode line_modes(int32_t klo, int32_t khi, int32_t cl, int32_t wg, int3
             if (dw < wc) node |= 1u << (16 + l);
         }
     }
-    m.pt = pt | ((pt & ~whole) << 8) | ((pt & core) << 16) | ((pt & gauss) << 24);
+    m.pt = pt | ((pt & ~whole) << 8) | ((pt & core) << 16) | (kGauss ? (pt & gauss) << 24 : 0u);
     m.node = node;
     return m;
 }
