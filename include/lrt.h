@@ -622,8 +622,9 @@ typedef struct {
  * time (each slot also holds 8 bytes of pinned host memory, where the device
  * writes the request's integral).  Each request is computed by fused kernels (populations, setups,
  * accumulation and march per spectral tile and chunk of cells, then the
- * chunks composed in order), single-precision compensated profile sums, FP64
- * march state and quadrature; no eta/kappa array is stored.  The context's
+ * chunks composed in order), single-precision profile terms summed in blocks
+ * and the blocks in FP64, FP64 march state and quadrature; no eta/kappa array
+ * is stored.  The context's
  * Lorentz model, atomic continuum and QSS-CR data (lrt_set_lorentz,
  * lrt_set_continuum, lrt_set_cr, lrt_set_line_levels) apply, the CR
  * populations solved for each request's cells at admission (collision

@@ -115,7 +115,7 @@ struct lrt_ctx {
     DBuf d_T_tr, d_T_v, d_N, d_n_e;
     DBuf d_cc, d_cs;
     bool thermo_ready = false;
-    DBuf d_emax, d_escale;
+    DBuf d_escale;
     DBuf d_bin_sp, d_bin_Ev, d_bin_Er, d_bin_aeta, d_bin_akap, d_bin_nlo, d_bin_nhi;
     int64_t n_bins = 0;
     bool scale_ready = false;

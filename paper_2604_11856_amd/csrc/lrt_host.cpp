@@ -483,7 +483,6 @@ static lrt_status set_cells_device(lrt_ctx *c, const lrt_cells *x)
         (st = upload(c, c->d_N, nullptr, nc * S * 8)) || (st = upload(c, c->d_n_e, nullptr, nc * 8)) ||
         (st = upload(c, c->d_cc, nullptr, nc * sizeof(CellConst))) ||
         (st = upload(c, c->d_cs, nullptr, nc * S * sizeof(CellSpecies))) ||
-        (st = upload(c, c->d_emax, nullptr, nc * 2 * sizeof(int32_t))) ||
         (st = upload(c, c->d_escale, nullptr, nc * 2 * sizeof(int32_t))) ||
         (st = ensure(c, c->w_count, 16)))
         return st;
@@ -534,7 +533,6 @@ lrt_status lrt_set_cells(lrt_ctx *c, const lrt_cells *x)
         (st = upload(c, c->d_N, x->N, nc * S * 8)) || (st = upload(c, c->d_n_e, x->n_e, nc * 8)) ||
         (st = upload(c, c->d_cc, nullptr, nc * sizeof(CellConst))) ||
         (st = upload(c, c->d_cs, nullptr, nc * S * sizeof(CellSpecies))) ||
-        (st = upload(c, c->d_emax, nullptr, nc * 2 * sizeof(int32_t))) ||
         (st = upload(c, c->d_escale, nullptr, nc * 2 * sizeof(int32_t))))
         return st;
     c->n_cells = nc;
