@@ -52,12 +52,13 @@ constexpr int kTileF64 = kThreadsF64 * kPPL;
 // workgroups, each a chain of many rounds, still fills the chip: 4 groups up to
 // two workgroups per CU in single precision (one in double precision, whose
 // LDS leaves room for half as many waves), 2 up to twice as many.
-// Coefficients with 1 / 2 / 4 groups, us, one line per point:
-//   FP32: 7 workgroups 129 / 87 / 77; 85: 110 / 87 / 60; 256: 368 / 243 / 157;
-//   1,024: 454 / 365 / 348 (0.4 lines per point 245 / 218 / 248); 1,536: 526 / 531 /
-//   498 (288 / 283 / 333); 3,072: 912 / 883 / 932 (468 / 487 / 600).
-//   FP64: 88: 670 / 468 / 361; 256: 1,075 / 707 / 520 (404 / 306 / 276); 768: 1,460 /
-//   1,327 / 1,415 (543 / 570 / 707); 1,024: 1,601 / 1,703 / 1,873.
+// Coefficients with 1 / 2 / 4 groups, us, one line per point (in brackets 0.4):
+//   FP32: 7 workgroups 140 / 91 / 77; 85: 353 / 229 / 165 (177 / 129 / 100); 256: 290 /
+//   191 / 132; 512: 311 / 226 / 175; 768: 328 / 250 / 236 (192 / 162 / 180); 1,024: 362 /
+//   292 / 289 (223 / 197 / 218); 1,536: 441 / 420 / 416 (261 / 265 / 303); 2,048: 527 /
+//   528 / 538.
+//   FP64: 85: 757 / 491 / 387; 256: 771 / 501 / 409 (336 / 253 / 218); 512: 893 / 687 /
+//   783; 768: 1,081 / 1,022 / 1,144 (470 / 470 / 588); 1,024: 1,274 / 1,287 / 1,508.
 // Only with a line per three points or more: with few lines per tile there are
 // no rounds to share (2,124 lines on 7,347 points, 915 workgroups, per solve 89 /
 // 93 / 114 us; below some hundred workgroups all the same).
