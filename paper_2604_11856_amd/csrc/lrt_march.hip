@@ -17,45 +17,6 @@ namespace lrt {
 
 namespace {
 
-// e^-t - 1 of an optical thickness and the two quotients of the segment laws.
-// One exponential series and one reciprocal (refined to the rounding of a
-// division) per point, 45 instructions, where the library's expm1, exp and
-// divisions took 110.
-__device__ __forceinline__ double expm1_neg(double t)
-{
-    return fabs(t) < 700.0 ? expm1_of(exp_parts(-t)) : expm1_any(-t);
-}
-__device__ __forceinline__ double div_f64(double a, double b, double rb)
-{
-    const double q = a * rb;
-    return fma(fma(-b, q, a), rb, q);
-}
-
-__device__ __forceinline__ void linear_j_weights_f64(double t, double &e, double &wf, double &wn)
-{
-    const double em = expm1_neg(t);
-    e = 1.0 + em;
-    if (fabs(t) >= 0.05) {
-        const double rt = rcp_f64(t);
-        const double f = div_f64(-em, t, rt);
-        wn = div_f64(1.0 - f, t, rt);
-        wf = div_f64(f - e, t, rt);
-        return;
-    }
-    // Horner over n = 8..0 of c_n t^n with c_n = (-1)^n/(n+2)! and (n+1) c_n
-    // (first omitted terms below 5e-19)
-    double a = 0.0, b = 0.0, inv = 1.0 / 3628800.0;
-#pragma unroll
-    for (int n = 8; n >= 0; --n) {
-        const double c = (n & 1) ? -inv : inv;
-        a = fma(a, t, c);
-        b = fma(b, t, (double)(n + 1) * c);
-        inv *= (double)(n + 2);
-    }
-    wn = a;
-    wf = b;
-}
-
 // One row (the PPT consecutive points kb.. of a lane) of eta and kappa, from
 // the row bases of the segment's cell (the same for the whole wave, so the
 // loads take a scalar base and the lane's 32-bit byte offset ob = kb sizeof(T)).
@@ -197,9 +158,8 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
                 linear_j_weights_f32(t, e, wf, wn);
                 I[j] = fma(I[j], (double)e, (double)(wf * fe[j]) * Lf + (double)(wn * ne[j]) * Ln);
             } else {
-                double e, wf, wn;
-                linear_j_weights_f64(fk[j] * Lk, e, wf, wn);
-                I[j] = I[j] * e + Lf * (wf * fe[j] + wn * ne[j]);
+                const LinearLaw w = linear_law(fk[j] * Lk);
+                I[j] = I[j] * w.e + Lf * (w.far * fe[j] + w.near * ne[j]);
             }
         }
     };
@@ -274,10 +234,8 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
                         const double d = lane_value(ds, s);
 #pragma unroll
                         for (int j = 0; j < PPT; ++j) {
-                            const double tau = kv[q][j] * d;
-                            const double em = expm1_neg(tau);
-                            const double F = (tau == 0.0) ? 1.0 : div_f64(-em, tau, rcp_f64(tau));
-                            I[j] = fma(I[j], em, I[j]) + ev[q][j] * d * F;
+                            const CellLaw w = cell_law(kv[q][j] * d);
+                            I[j] = fma(I[j], w.em, I[j]) + ev[q][j] * d * w.f;
                         }
                     }
                     if (s + kAhead < n) load(q, lane_value(c, s + kAhead));

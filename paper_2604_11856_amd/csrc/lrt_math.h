@@ -1,5 +1,5 @@
-// Double-precision functions of the (cell, line) setup, for the device and (for
-// their tests) the host.
+// Double-precision functions of the (cell, line) setup and the segment laws of
+// the march, for the device and (for their tests) the host.
 #pragma once
 
 #include <cmath>
@@ -15,15 +15,23 @@ namespace lrt {
 
 // 1/x of a normal x: the hardware reciprocal and two Newton steps (five
 // instructions against eleven of the correctly rounded division; within an ulp).
+// NaN where 1/x overflows (|x| <= 2^-1024) and for infinite x.  The host takes the
+// same steps from an estimate as coarse as the hardware's (2^-23).
 LRT_HD double rcp_f64(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     double r = __builtin_amdgcn_rcp(x);
+#else
+    double r = 1.0 / x * (1.0 + 1.1920928955078125e-07);
+#endif
     r = fma(fma(-x, r, 1.0), r, r);
     return fma(fma(-x, r, 1.0), r, r);
-#else
-    return 1.0 / x;
-#endif
+}
+// a/b from rb = rcp_f64(b), refined to the rounding of a division.
+LRT_HD double div_f64(double a, double b, double rb)
+{
+    const double q = a * rb;
+    return fma(fma(-b, q, a), rb, q);
 }
 
 // e^x = 2^k (1 + p), |x| < 700: k = round(x / ln 2), p = e^r - 1 of the rest r by
@@ -32,6 +40,7 @@ LRT_HD double rcp_f64(double x)
 struct ExpParts {
     double p;
     int k;
+    double q, r;   // p = r + r^2 q
 };
 LRT_HD ExpParts exp_parts(double x)
 {
@@ -50,7 +59,7 @@ LRT_HD ExpParts exp_parts(double x)
     q = fma(q, r, 1.0 / 24.0);
     q = fma(q, r, 1.0 / 6.0);
     q = fma(q, r, 0.5);
-    return ExpParts{fma(q, r * r, r), (int)kd};
+    return ExpParts{fma(q, r * r, r), (int)kd, q, r};
 }
 LRT_HD double exp_of(const ExpParts &e) { return ldexp(1.0 + e.p, e.k); }
 LRT_HD double expm1_of(const ExpParts &e)
@@ -64,6 +73,58 @@ LRT_HD double expm1_any(double x)
 {
     const ExpParts e = exp_parts(x < -1e5 ? -1e5 : x > 1e5 ? 1e5 : x);
     return e.k > 60 ? exp_of(e) : expm1_of(e);   // beyond 2^53 the 1 is lost anyway
+}
+
+// Laws of a cell-constant and of a linear-j segment of optical depth t (Sec.
+// 2.2.3), with f = (1 - e^-t)/t: em = e^-t - 1 and f; e = e^-t and the weights
+// per unit length of the near node, (1 - f)/t, and of the far one, (f - e)/t.
+// One exponential series and one reciprocal (refined to the rounding of a
+// division) per point, 45 instructions, where a library's expm1, exp and
+// divisions take 110.  The reciprocal serves only depths of 0.34 (cell-constant)
+// or 0.05 (linear-j) to 700: below, down to zero, subnormals and their signs, the
+// series have no quotient; above, up to infinity, there is the plain division.
+struct CellLaw {
+    double em, f;
+};
+LRT_HD CellLaw cell_law(double t)
+{
+    if (!(fabs(t) < 700.0)) {
+        const double em = expm1_any(-t);
+        return CellLaw{em, -em / t};
+    }
+    const ExpParts x = exp_parts(-t);
+    const double em = expm1_of(x);
+    // k = 0: e^-t - 1 = r + r^2 q with r = -t
+    return CellLaw{em, x.k == 0 ? fma(x.q, x.r, 1.0) : div_f64(-em, t, rcp_f64(t))};
+}
+
+struct LinearLaw {
+    double e, near, far;
+};
+LRT_HD LinearLaw linear_law(double t)
+{
+    if (fabs(t) >= 700.0) {
+        const double em = expm1_any(-t), f = -em / t, e = 1.0 + em;
+        return LinearLaw{e, (1.0 - f) / t, (f - e) / t};
+    }
+    const double em = expm1_of(exp_parts(-t)), e = 1.0 + em;
+    if (fabs(t) >= 0.05) {
+        const double rt = rcp_f64(t), f = div_f64(-em, t, rt);
+        return LinearLaw{e, div_f64(1.0 - f, t, rt), div_f64(f - e, t, rt)};
+    }
+    // Horner over n = 8..0 of c_n t^n with c_n = (-1)^n/(n+2)! and (n+1) c_n
+    // (first omitted terms below 5e-19)
+    double a = 0.0, b = 0.0, inv = 1.0 / 3628800.0;
+#if defined(__HIPCC__)
+#pragma unroll
+#endif
+    for (int n = 8; n >= 0; --n) {
+        const double c = (n & 1) ? -inv : inv;
+        a = fma(a, t, c);
+        b = fma(b, t, (double)(n + 1) * c);
+        inv *= (double)(n + 2);
+    }
+    return LinearLaw{e, a, b};
 }
 
 // Voigt HWHM of the Olivero-Longbothum fit (Sec. 2.2.1) from the Lorentz and
