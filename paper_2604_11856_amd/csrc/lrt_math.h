@@ -80,9 +80,10 @@ LRT_HD double expm1_any(double x)
 // per unit length of the near node, (1 - f)/t, and of the far one, (f - e)/t.
 // One exponential series and one reciprocal (refined to the rounding of a
 // division) per point, 45 instructions, where a library's expm1, exp and
-// divisions take 110.  The reciprocal serves only depths of 0.34 (cell-constant)
-// or 0.05 (linear-j) to 700: below, down to zero, subnormals and their signs, the
-// series have no quotient; above, up to infinity, there is the plain division.
+// divisions take 110.  The reciprocal serves only depths of 0.34 to 700.  Below,
+// down to zero, subnormals and their signs, the quotients are the series' own:
+// with e^-t = 1 + r + r^2 q and r = -t, f is 1 + r q, the near weight q and the
+// far one f - q.  Above, up to infinity, there is the plain division.
 struct CellLaw {
     double em, f;
 };
@@ -93,9 +94,9 @@ LRT_HD CellLaw cell_law(double t)
         return CellLaw{em, -em / t};
     }
     const ExpParts x = exp_parts(-t);
+    if (x.k == 0) return CellLaw{x.p, fma(x.q, x.r, 1.0)};
     const double em = expm1_of(x);
-    // k = 0: e^-t - 1 = r + r^2 q with r = -t
-    return CellLaw{em, x.k == 0 ? fma(x.q, x.r, 1.0) : div_f64(-em, t, rcp_f64(t))};
+    return CellLaw{em, div_f64(-em, t, rcp_f64(t))};
 }
 
 struct LinearLaw {
@@ -103,28 +104,16 @@ struct LinearLaw {
 };
 LRT_HD LinearLaw linear_law(double t)
 {
-    if (fabs(t) >= 700.0) {
-        const double em = expm1_any(-t), f = -em / t, e = 1.0 + em;
+    if (!(fabs(t) < 700.0)) {
+        const double f = -expm1_any(-t) / t, e = exp_any(-t);
         return LinearLaw{e, (1.0 - f) / t, (f - e) / t};
     }
-    const double em = expm1_of(exp_parts(-t)), e = 1.0 + em;
-    if (fabs(t) >= 0.05) {
-        const double rt = rcp_f64(t), f = div_f64(-em, t, rt);
-        return LinearLaw{e, div_f64(1.0 - f, t, rt), div_f64(f - e, t, rt)};
-    }
-    // Horner over n = 8..0 of c_n t^n with c_n = (-1)^n/(n+2)! and (n+1) c_n
-    // (first omitted terms below 5e-19)
-    double a = 0.0, b = 0.0, inv = 1.0 / 3628800.0;
-#if defined(__HIPCC__)
-#pragma unroll
-#endif
-    for (int n = 8; n >= 0; --n) {
-        const double c = (n & 1) ? -inv : inv;
-        a = fma(a, t, c);
-        b = fma(b, t, (double)(n + 1) * c);
-        inv *= (double)(n + 2);
-    }
-    return LinearLaw{e, a, b};
+    // (e from its own parts: 1 + em keeps no digits of it from t = 37 on)
+    const ExpParts x = exp_parts(-t);
+    const double s = ldexp(1.0, x.k), e = fma(s, x.p, s);
+    if (x.k == 0) return LinearLaw{e, x.q, fma(x.q, x.r, 1.0) - x.q};
+    const double em = fma(s, x.p, s - 1.0), rt = rcp_f64(t), f = div_f64(-em, t, rt);
+    return LinearLaw{e, div_f64(1.0 - f, t, rt), div_f64(f - e, t, rt)};
 }
 
 // Voigt HWHM of the Olivero-Longbothum fit (Sec. 2.2.1) from the Lorentz and

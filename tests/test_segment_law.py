@@ -82,6 +82,16 @@ def test_linear_law(shim):
     assert np.max(np.abs(far - fx) / fx) <= 1.1e-13
 
 
+def test_attenuation_keeps_its_digits(shim):
+    """e^-t of the linear-j law, however thick the segment, as close as the
+    exponential is (below e^-708 a subnormal's spacing)."""
+    t = np.abs(_depths())
+    t = np.concatenate([t, np.linspace(1.0, 745.0, 5000)])
+    e = _call(shim.linear, t, 3)[0]
+    ref = np.exp(-t.astype(np.longdouble))
+    assert np.max(np.abs(e - ref) / np.maximum(ref, 1e-307)) <= 4.5e-16
+
+
 def test_ends(shim):
     t = np.array([0.0, -0.0, 700.0, 745.0, 1e5, 1e300, 1.7e308, np.inf])
     em, f = _call(shim.cell, t, 2)
