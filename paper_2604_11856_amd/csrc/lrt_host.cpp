@@ -978,7 +978,7 @@ lrt_status march_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisio
         // segments per cell on, else of 256 (the plan takes 128-point chunks only
         // where the buffer holds their sums)
         const int32_t points = c->h_off.back() >= 128 * c->n_cells ? 128 : 256;
-        const int64_t held = c->n_rays * (int64_t)((n_band + points - 1) / points);
+        const int64_t held = c->n_rays * (((int64_t)n_band + points - 1) / points);
         if (std::max(held, need) > cap)
             return fail(c, LRT_E_ARG, "the march needs %lld partial sums (rays x %d-point chunks), the buffer holds %lld",
                         (long long)held, points, (long long)cap);

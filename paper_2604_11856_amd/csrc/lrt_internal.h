@@ -110,9 +110,9 @@ inline MarchPlan march_plan(int64_t n_rays, int64_t n_cells, int32_t n_band, boo
     MarchPlan p;
     const bool many = n_rays >= kMarchManyRays, share = n_rays >= kMarchShareRays;
     const bool wide = many ? n_band >= (share ? kMarchWideBand / 8 : kMarchWideBand)
-                           : n_rays * ((n_band + 255) / 256) >= kMarchFewWaves;
-    p.ppt = wide || n_rays * ((n_band + 127) / 128) > max_sums ? 4 : 2;
-    p.n_chunks = (n_band + 64 * p.ppt - 1) / (64 * p.ppt);
+                           : n_rays * ((int64_t(n_band) + 255) / 256) >= kMarchFewWaves;
+    p.ppt = wide || n_rays * ((int64_t(n_band) + 127) / 128) > max_sums ? 4 : 2;
+    p.n_chunks = (int32_t)((int64_t(n_band) + 64 * p.ppt - 1) / (64 * p.ppt));
     p.rays = many ? 4 : 1;
     p.shared = share && 8 * n_cells * int64_t(256) * 2 * (fp32 ? 4 : 8) > kLastLevelBytes;
     return p;

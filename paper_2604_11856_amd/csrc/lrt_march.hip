@@ -17,12 +17,13 @@ namespace lrt {
 
 namespace {
 
-// One row (the PPT consecutive points kb.. of a lane) of eta and kappa, from
-// the row bases of the segment's cell (the same for the whole wave, so the
-// loads take a scalar base and the lane's 32-bit byte offset ob = kb sizeof(T)).
+// One row (the PPT consecutive points k0.. of a lane) of eta and kappa, from the
+// chunk's first point in the rows of the segment's cell (the same for the whole
+// wave, so the loads take a 64-bit scalar base, which bands of any length need,
+// and the lane's 32-bit offset in the chunk); left: points of the band from there.
 template <int PPT, typename T>
-__device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t kb, uint32_t ob, int32_t n_band,
-                                         bool vec, T (&ev)[PPT], T (&kv)[PPT])
+__device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t k0, int32_t left, bool vec,
+                                         T (&ev)[PPT], T (&kv)[PPT])
 {
     if (vec) {   // vector loads of up to 16 bytes
         constexpr int V = sizeof(T) == 4 ? PPT : 2;
@@ -30,8 +31,8 @@ __device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t 
         typedef T Vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
 #pragma unroll
         for (int j = 0; j < PPT; j += V) {
-            const Vec a = *(const Vec *)((const char *)erow + ob + j * sizeof(T));
-            const Vec b = *(const Vec *)((const char *)krow + ob + j * sizeof(T));
+            const Vec a = *(const Vec *)((const char *)erow + k0 * (uint32_t)sizeof(T) + j * sizeof(T));
+            const Vec b = *(const Vec *)((const char *)krow + k0 * (uint32_t)sizeof(T) + j * sizeof(T));
 #pragma unroll
             for (int i = 0; i < V; ++i) {
                 ev[j + i] = a[i];
@@ -42,9 +43,9 @@ __device__ __forceinline__ void load_row(const T *erow, const T *krow, uint32_t 
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const bool ok = (int32_t)kb + j < n_band;
-        ev[j] = ok ? erow[kb + j] : (T)0;
-        kv[j] = ok ? krow[kb + j] : (T)0;
+        const bool ok = (int32_t)k0 + j < left;
+        ev[j] = ok ? erow[k0 + j] : (T)0;
+        kv[j] = ok ? krow[k0 + j] : (T)0;
     }
 }
 
@@ -122,22 +123,23 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     int ray, chunk;
     march_item<RAYS>(b0 + blockIdx.x, wave, rays, n_chunks, shared, ray, chunk);
     if (ray < 0) return;
-    const int32_t kb = chunk * (64 * PPT) + lane * PPT;   // band-relative
+    const int32_t start = chunk * (64 * PPT);   // the chunk's first point, band-relative
+    const int32_t left = n_band - start;        // points of the band from there on
+    const int32_t k0 = lane * PPT;              // the lane's first point, chunk-relative
     const int64_t m0 = rays.off[ray], m1 = rays.off[ray + 1];
     double I[PPT];
     const double Tw = T_far ? T_far[ray] : 0.0;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         I[j] = 0.0;
-        if (Tw > 0.0 && kb + j < n_band) I[j] = planck_f64(g.nu_min + (double)(k_first + kb + j) * g.h, Tw);
+        if (Tw > 0.0 && k0 + j < left) I[j] = planck_f64(g.nu_min + (double)(k_first + start + k0 + j) * g.h, Tw);
     }
     // vector loads only when the wave's points are all inside the band (a
     // wave-uniform choice)
-    const bool vec = (int64_t)(chunk + 1) * (64 * PPT) <= n_band;
+    const bool vec = left >= 64 * PPT;
     using T = std::conditional_t<FP32, float, double>;
     const T *eta = (const T *)eta_v;
     const T *kap = (const T *)kappa_v;
-    const uint32_t ob = (uint32_t)kb * (uint32_t)sizeof(T);   // byte offset of the lane's points in a row
     constexpr int kAhead = FP32 ? 4 : 2;
     T ev[kAhead][PPT], kv[kAhead][PPT];
 
@@ -168,9 +170,8 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     const int32_t n_seg = (int32_t)(m1 - m0);
     auto march = [&](auto vec_c) {
         auto load = [&](int slot, int32_t c) {
-            const int64_t row = (int64_t)c * n_band;
-            load_row<PPT, T>(eta + row, kap + row, (uint32_t)kb, ob, n_band, decltype(vec_c)::value, ev[slot],
-                             kv[slot]);
+            const int64_t row = (int64_t)c * n_band + start;
+            load_row<PPT, T>(eta + row, kap + row, (uint32_t)k0, left, decltype(vec_c)::value, ev[slot], kv[slot]);
         };
         for (int32_t i0 = 0; i0 < n_seg; i0 += 64) {
             const int32_t n = min(64, n_seg - i0);
@@ -260,9 +261,8 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     double part = 0.0;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int32_t kl = kb + j;
-        if (kl < n_band) {
-            const int32_t kg = k_first + kl;
+        if (k0 + j < left) {
+            const int32_t kl = start + k0 + j, kg = k_first + kl;
             const double w = (kg == 0 || kg == g.n_points - 1) ? 0.5 * g.h : g.h;
             part += w * I[j];
             if (I_out) I_out[(int64_t)ray * n_band + kl] = I[j];
