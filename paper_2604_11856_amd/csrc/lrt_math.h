@@ -94,9 +94,8 @@ LRT_HD CellLaw cell_law(double t)
         return CellLaw{em, -em / t};
     }
     const ExpParts x = exp_parts(-t);
-    if (x.k == 0) return CellLaw{x.p, fma(x.q, x.r, 1.0)};
     const double em = expm1_of(x);
-    return CellLaw{em, div_f64(-em, t, rcp_f64(t))};
+    return CellLaw{em, x.k == 0 ? fma(x.q, x.r, 1.0) : div_f64(-em, t, rcp_f64(t))};
 }
 
 struct LinearLaw {
