@@ -446,9 +446,10 @@ lrt_status lrt_coeffs(lrt_ctx *ctx, int64_t band, lrt_precision prec, void *eta,
  * tau = kappa ds, F(t) = (1 - e^-t)/t, F(0) = 1.  I_out (device, [n_rays][band_len] doubles) receives the wall
  * intensity, or pass NULL; I_int_out (device, [n_rays] doubles) receives the
  * band's trapezoid sum with global-index weights (h/2 at grid ends, h inside).
- * The march works on chunks of 128 grid points when there are fewer than 3072
- * rays times 256-point chunks, else of 256; the rays over 4 times the band's
- * chunks must stay below 2^32 (LRT_E_DEVICE otherwise).
+ * The march works on chunks of 128 or 256 grid points, chosen from the numbers
+ * of rays, cells and grid points; the rays over 4 times the band's chunks must
+ * stay below 2^32 (LRT_E_DEVICE otherwise), which with 128-point chunks they
+ * may reach first.
  * Stream-ordered.  Errors: LRT_E_STATE (no rays, cells/rays mismatch),
  * LRT_E_ARG. */
 lrt_status lrt_march(lrt_ctx *ctx, int64_t band, lrt_precision prec, const void *eta,

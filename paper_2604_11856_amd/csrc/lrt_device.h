@@ -11,8 +11,6 @@ namespace lrt {
 
 constexpr double kLog2e = 1.4426950408889634;
 constexpr double kLn2 = 0.6931471805599453;
-// XCDs of the chip: workgroup ids go round-robin over them, each has its own L2.
-constexpr int kXCDs = 8;
 
 __device__ __forceinline__ int32_t uniform_i(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 

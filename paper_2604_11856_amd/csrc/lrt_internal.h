@@ -69,6 +69,9 @@ inline int accum_groups(int64_t n_blocks, int64_t n_lines, int64_t n_points, boo
     return n <= 512 ? 4 : n <= 1024 ? 2 : 1;
 }
 
+// XCDs of the chip: workgroup ids go round-robin over them, each has its own L2.
+constexpr int kXCDs = 8;
+
 // March tile: one workgroup of 4 waves; each wave marches one ray over one
 // chunk of 64 x ppt consecutive points, ppt per lane, and the waves share no
 // state.
@@ -76,45 +79,62 @@ inline int accum_groups(int64_t n_blocks, int64_t n_lines, int64_t n_points, boo
 //     which then share rows in the L1; below, 4 consecutive chunks of one ray.
 //     4 rays / one ray: 160 rays 313 / 259 us, 195: 115 / 113, 256: 80 / 85,
 //     735: 195 / 275, 1,024: 522 / 684, 2,048: 0.99 / 1.26 ms, 4,096: 1.78 / 2.16.
-//   ppt: 256-point chunks, or 128-point ones for more, shorter waves:
-//     Few rays: where 256 points leave fewer than three waves per SIMD
-//     (kMarchFewWaves).  256 / 128 points: 782 waves of 256 points (one ray, 64
-//     cells) 40 / 30 us; 944 (8 rays, 131 cells) 69 / 51; 2,624 (16 rays, 181
-//     cells) 172 / 165; 17 rays on 2^19 points 1.80 / 1.99 ms.
-//     Many rays: on bands under kMarchWideBand points, where the XCDs' shares of
-//     the chunks and of the rays' unequal lengths are coarse.  864 rays x 2,436
-//     points 260 / 157 us; 1,120 x 982 422 / 146; 6,144 x 4,000 2.00 / 1.37 ms;
-//     7,168 x 4,000 3.80 / 3.64; 1,024 x 8,192 550 / 559 us; 1,024 x 65,536
-//     4.10 / 4.43 ms; 5,120 x 16,384 2.09 / 2.40.  From kMarchShareRays rays on
-//     the chunk's rows are reused enough for 256 points from 1,024 points on:
-//     8,192 x 2,048 0.81 / 0.90 ms; 131,072 x 1,024 29.8 / 32.4 (both shared);
-//     16,384 x 500 2.10 / 1.24 (both shared).
-//   shared: every XCD on the same chunk (march_item) where the rows of eight
-//     chunks, one per XCD, exceed the last-level cache, and there are very many
-//     rays to share them.  32,768 cells, 8,192 rays: 4.13 ms against 4.48 without;
-//     2,048 rays: 5.84 against 5.10.
+//   ppt: 256-point chunks, or 128-point ones for more, shorter waves.  Times of
+//     256 / 128 points:
+//     Few rays: 128 where 256 points leave fewer than three waves per SIMD
+//     (kMarchFewWaves).  8 rays, 131 cells, 944 waves of 256 points 55 / 44 us,
+//     2,816 waves 74 / 75, 4,064 waves 90 / 96; 17 rays, 400 cells, 1,343 waves 179 /
+//     135, 2,669 waves 209 / 212, 34,816 waves 1.79 / 2.01 ms; 201 rays, 100 cells, 804
+//     waves 40 / 30, 3,216 waves 66 / 64, 6,432 waves 102 / 105.
+//     Many rays: besides, where the XCDs' shares of short bands are coarse
+//     (kMarchWideBand: 2,048 rays, 2,048 cells, 1,003 points 82 / 75 us, 1,500 points
+//     102 / 112, 4,000 points 215 / 246) and where the rows are deep (32,768 cells,
+//     1,024 rays, 12,000 points 1.96 / 1.72 ms; 2,048 rays, 2,000 points 690 / 630 us).
+//     256 where the chunks are shared.  Never for bands of one such chunk (256
+//     points, 2,048 rays, 2,048 cells 43 / 37 us).
+//   deep: the rows of eight chunks, one per XCD, exceed the last-level cache.
+//   shared: every XCD on the same chunk (march_item).  Times of shared / not:
+//     Deep rows, from kMarchShareRays rays on.  32,768 cells x 4,000 points: 2,560
+//     rays 1.77 / 1.43 ms, 3,072 rays 2.11 / 1.72, 4,096 rays 2.18 / 2.24, 6,144 rays
+//     3.12 / 3.24, 8,192 rays 3.81 / 4.10.  At the line in cells (16,384), 4,096
+//     rays and more: the same within 4 %.
+//     Others, where the band has fewer chunks than XCDs, whose shares of one chunk's
+//     rays then differ in length, from kMarchChunkRays rays per chunk on.  2,048
+//     cells: 400 points (2 chunks), 1,024 rays 47 / 35 us, 2,048 rays 57 / 59, 4,096 rays
+//     83 / 91, 8,192 rays 124 / 163; 700 points (3), 2,048 rays 75 / 66, 3,072 rays
+//     90 / 89, 8,192 rays 175 / 205; 1,003 points (4), 3,072 rays 111 / 103, 4,096 rays
+//     133 / 131, 8,192 rays 226 / 240; 2,000 points (8), 8,192 rays 427 / 397.
+//   lds: in that order too many rays of deep rows at once push each other's rows out
+//     of the L2s: 40 KB of (unused) LDS per workgroup leaves 16 waves per CU (8,192
+//     rays, 32,768 cells, 4,096 points: 4.09 against 4.67 ms without; 131,072 rays,
+//     131,072 cells, 1,024 points 29.6 / 30.8; with 32,768 cells 13.8 / 13.3).  Rows that
+//     are not deep lose by it (8,192 rays, 2,048 cells, 1,003 points 244 / 226 us).
 constexpr int kMarchThreads = 256;
 constexpr int64_t kMarchFewWaves = 3072;
 constexpr int32_t kMarchManyRays = 256;
-constexpr int32_t kMarchShareRays = 8192;
-constexpr int32_t kMarchWideBand = 8192;
+constexpr int32_t kMarchShareRays = 4096;
+constexpr int32_t kMarchChunkRays = 1024;
+constexpr int32_t kMarchWideBand = 1280;
 constexpr int64_t kLastLevelBytes = int64_t(256) << 20;
 
 struct MarchPlan {
     int32_t ppt, rays, n_chunks;
     bool shared;
+    uint32_t lds;
 };
 // max_sums: rays x chunks that a caller's buffer for the chunks' sums holds.
 inline MarchPlan march_plan(int64_t n_rays, int64_t n_cells, int32_t n_band, bool fp32, int64_t max_sums)
 {
     MarchPlan p;
-    const bool many = n_rays >= kMarchManyRays, share = n_rays >= kMarchShareRays;
-    const bool wide = many ? n_band >= (share ? kMarchWideBand / 8 : kMarchWideBand)
-                           : n_rays * ((int64_t(n_band) + 255) / 256) >= kMarchFewWaves;
-    p.ppt = wide || n_rays * ((int64_t(n_band) + 127) / 128) > max_sums ? 4 : 2;
-    p.n_chunks = (int32_t)((int64_t(n_band) + 64 * p.ppt - 1) / (64 * p.ppt));
+    const int64_t chunks = (int64_t(n_band) + 255) / 256, narrow = (int64_t(n_band) + 127) / 128;
+    const bool many = n_rays >= kMarchManyRays;
+    const bool deep = 8 * n_cells * int64_t(256) * 2 * (fp32 ? 4 : 8) > kLastLevelBytes;
+    p.shared = deep ? n_rays >= kMarchShareRays : chunks < kXCDs && n_rays >= kMarchChunkRays * chunks;
+    const bool wide = p.shared || (n_rays * chunks >= kMarchFewWaves && !(many && (deep || n_band < kMarchWideBand)));
+    p.ppt = (wide && n_band > 256) || n_rays * narrow > max_sums ? 4 : 2;
+    p.n_chunks = (int32_t)(p.ppt == 4 ? chunks : narrow);
     p.rays = many ? 4 : 1;
-    p.shared = share && 8 * n_cells * int64_t(256) * 2 * (fp32 ? 4 : 8) > kLastLevelBytes;
+    p.lds = p.shared && deep && p.ppt == 4 ? 40960u : 0u;
     return p;
 }
 

@@ -334,16 +334,10 @@ hipError_t launch_march(bool fp32, bool linear, const MarchPlan &plan, const Dev
     const int64_t n_rays = rays.n_rays, cg = kMarchThreads / 64 / plan.rays;
     const int64_t n_blocks = (n_rays + plan.rays - 1) / plan.rays * ((plan.n_chunks + cg - 1) / cg);
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
-    // Where the XCDs share a chunk, too many rays at once push each other's rows
-    // out of the L2s: 40 KB of (unused) LDS per workgroup leaves 16 waves per CU
-    // (8,192 rays: 4.13 against 4.72 ms with 28 waves, 5.83 with 12; 131,072 rays:
-    // 29.7 against 31.6).
-    // 16,384 rays in 128-point chunks: 1.24 ms without, 1.36 with.
-    const unsigned lds = plan.shared && plan.ppt == 4 ? 40960u : 0u;
     for (int64_t b0 = 0; b0 < n_blocks; b0 += kMaxLaunchBlocks) {
         const dim3 grid((unsigned)std::min(kMaxLaunchBlocks, n_blocks - b0));
 #define LRT_MARCH(F, LIN, P, R)                                                                            \
-    hipLaunchKernelGGL((march_kernel<F, LIN, P, R>), grid, dim3(kMarchThreads), lds, st, rays, g, k_first, \
+    hipLaunchKernelGGL((march_kernel<F, LIN, P, R>), grid, dim3(kMarchThreads), plan.lds, st, rays, g, k_first, \
                        n_band, eta, kappa, escale, T_far, I_out, partials, plan.n_chunks,                  \
                        plan.shared ? 1 : 0, (uint32_t)b0)
 #define LRT_MARCH_P(F, LIN)                                                       \
