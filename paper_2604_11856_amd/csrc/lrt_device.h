@@ -98,15 +98,21 @@ static __device__ __forceinline__ void segment_points_f32(const float (&ev)[N], 
 // For |t| < 0.1 both differences cancel; there the weights come from their
 // Taylor series, W_near = sum (-t)^n/(n+2)!, W_far = sum (-1)^n (n+1) t^n/(n+2)!,
 // whose first omitted terms are below 3e-11.
+constexpr float kLinearThin = 0.1f;
+static __device__ __forceinline__ void linear_j_series_f32(float t, float &wf, float &wn)
+{
+    wn = fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, -1.0f / 5040.0f, 1.0f / 720.0f), -1.0f / 120.0f), 1.0f / 24.0f),
+                      -1.0f / 6.0f), 0.5f);
+    wf = fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, -1.0f / 840.0f, 1.0f / 144.0f), -1.0f / 30.0f), 1.0f / 8.0f),
+                      -1.0f / 3.0f), 0.5f);
+}
 static __device__ __forceinline__ void linear_j_weights_f32(float t, float e, float &wf, float &wn)
 {
-    const float sn = fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, -1.0f / 5040.0f, 1.0f / 720.0f),
-                                                   -1.0f / 120.0f), 1.0f / 24.0f), -1.0f / 6.0f), 0.5f);
-    const float sf = fmaf(t, fmaf(t, fmaf(t, fmaf(t, fmaf(t, -1.0f / 840.0f, 1.0f / 144.0f),
-                                                   -1.0f / 30.0f), 1.0f / 8.0f), -1.0f / 3.0f), 0.5f);
+    float sn, sf;
+    linear_j_series_f32(t, sf, sn);
     const float r = __builtin_amdgcn_rcpf(t);
     const float f = (1.0f - e) * r;
-    const bool thin = fabsf(t) < 0.1f;
+    const bool thin = fabsf(t) < kLinearThin;
     wn = thin ? sn : (1.0f - f) * r;
     wf = thin ? sf : (f - e) * r;
 }

@@ -154,15 +154,28 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     [[maybe_unused]] int32_t pee = 0, pek = 0;
     [[maybe_unused]] double pds = 0.0;
     // one linear-j segment from node (fe, fk) to node ne, lengths scaled by the
-    // nodes' powers of two (Lf = Ln = L and Lk = L in double precision)
+    // nodes' powers of two (Lf = Ln = L and Lk = L in double precision).  Where many
+    // rays keep the vector units busy (256-point chunks, four rays) a point at
+    // which the whole wave is thin takes the series alone, and the points one after
+    // the other need fewer registers; few rays wait for the vote instead.
+    constexpr bool kThinVote = FP32 && PPT == 4 && RAYS == 4;
     [[maybe_unused]] auto linear_segment = [&](const T (&fe)[PPT], const T (&fk)[PPT], const T (&ne)[PPT], double Lf,
                                                double Ln, T Lk) {
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             if constexpr (FP32) {
                 const float t = fk[j] * Lk;
-                const float e = __builtin_amdgcn_exp2f(t * (float)(-kLog2e));
                 float wf, wn;
+                if constexpr (kThinVote) {
+                    linear_j_series_f32(t, wf, wn);
+                    if (__all(fabsf(t) < kLinearThin)) {
+                        // 1 - e^-t = t f with f = wf + wn
+                        const double x = (double)(t * (wf + wn));
+                        I[j] = fma(-x, I[j], fma((double)(wf * fe[j]), Lf, fma((double)(wn * ne[j]), Ln, I[j])));
+                        continue;
+                    }
+                }
+                const float e = __builtin_amdgcn_exp2f(t * (float)(-kLog2e));
                 linear_j_weights_f32(t, e, wf, wn);
                 I[j] = fma(I[j], (double)e, (double)(wf * fe[j]) * Lf + (double)(wn * ne[j]) * Ln);
             } else {
