@@ -1275,7 +1275,7 @@ void accum_f64_kernel(
                 ra.edges = (uint32_t)min(max(lo, 0), kTileF64) | ((uint32_t)min(max(hi + 1, 0), kTileF64) << 16);
                 // the reaches and the centre in grid steps (as the single-precision form)
                 const float gs = __builtin_amdgcn_rcpf((float)(2.0 * rp.h2));
-                const float yG = sqrtf(68.5f - (float)max(ilogb(p.r), -1000));
+                const float yG = gauss_reach_f64(p.r);
                 const float cf = floorf((float)rp.k0 + (float)(frac0 * g.inv_h));
                 rm = line_modes(lo, hi, (int32_t)fmaxf(-1e9f, fminf(cf, 1e9f)) - 1,
                                 (int32_t)fminf(yG * gs, 1.1e9f) + 2,

@@ -39,7 +39,7 @@ struct alignas(8) RecMode {
 // the interval (r from 2^-40 to 0.98, gamma_V from 0.3 to 64 grid steps), an
 // eighth of the single-precision rounding; at 2.25 it is 3.8e-8, at 2.0 2.3e-7.
 // The double-precision form takes 32 nodes (4.8e-17 at 2.5, 1.3e-15 at 2.25) and
-// y_G^2 = 68 + log2(1/s), s = max(r, 2^-1000), for 2^-56.
+// gauss_reach_f64 for 2^-56.
 //
 // Both forms are bound by vector instructions (about 15 per evaluation; issue
 // slots 0.98 full on the stagnation line).  There (gamma_V 11 grid steps on
@@ -58,6 +58,14 @@ constexpr int kLevels = kTileBits - kSliceBits + 1;                 // 64 << lev
 constexpr int kSlices = 1 << (kTileBits - kSliceBits);
 // first bit of a level in RecMode::node: the levels follow each other, finest first
 LRT_HD constexpr int node_bit0(int level) { return 2 * kSlices - (2 * kSlices >> level); }
+
+// y_G of the double-precision form: y_G^2 = 68.5 + log2(1/r), at most 1090.5, from
+// where e^{-0.693 y^2} is zero (below 2^-1090) whatever r is, zero among it.
+LRT_HD float gauss_reach_f64(double r)
+{
+    const int e = ilogb(r);
+    return sqrtf(68.5f - (float)(e > -1022 ? e : -1022));
+}
 
 // Nodes of an interval of 64 points, from its middle, in grid steps: Chebyshev
 // nodes rounded to eighths (sixteen nodes) or 64ths (the double-precision form's
