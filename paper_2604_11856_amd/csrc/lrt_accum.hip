@@ -916,8 +916,8 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
                 const double frac0 = line_at(L.frac0, base, t);
-                const int32_t k0 = line_at(L.k0, base, t) - kt;
-                rp.k0f = (float)k0;
+                // (the difference of two indices, up to 2^32)
+                rp.k0f = (float)((double)line_at(L.k0, base, t) - (double)kt);
                 rp.hg = (float)(2.0 * g.h * p.inv2g);
                 rp.fg = (float)(2.0 * frac0 * p.inv2g);
                 // profile divided by s = r, strengths times s
@@ -1264,7 +1264,7 @@ void accum_f64_kernel(
             const CellConst &k = reread(&kc);
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
-                rp.k0 = (double)(line_at(L.k0, base, t) - kt);
+                rp.k0 = (double)line_at(L.k0, base, t) - (double)kt;
                 const double frac0 = line_at(L.frac0, base, t);
                 rp.h2 = g.h * p.inv2g;
                 rp.f2 = frac0 * p.inv2g;

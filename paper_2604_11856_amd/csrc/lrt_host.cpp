@@ -768,13 +768,16 @@ lrt_status prepare_lines(lrt_ctx *c)
         // nu0 = nu_min + k0 h + frac0 with frac0 correctly rounded: k0 h and
         // nu_min + k0 h are carried as unevaluated sums (two-product by fma,
         // two-sum), so frac0 is the difference of nu0 and the exact grid point.
+        // k0 is clamped only where it leaves the index type, farther from any
+        // grid point than the grid is long: (k - k0) h and frac0 then have one sign
+        // and do not cancel in the kernels.
         const int64_t n = c->n_lines;
         std::vector<int32_t> k0(n);
         std::vector<double> fr(n);
         for (int64_t i = 0; i < n; ++i) {
             const double nu0 = c->h_nu0[i];
             double kk = std::nearbyint((nu0 - c->nu_min) / c->h);
-            kk = std::max(-16777216.0, std::min(16777216.0, kk));
+            kk = std::max(-2147483647.0, std::min(2147483647.0, kk));
             const double p = kk * c->h;
             const double pe = std::fma(kk, c->h, -p);
             const double s = c->nu_min + p;
