@@ -406,7 +406,7 @@ __global__ void ranges_kernel(DevLines L, DevGrid g, const CellConst *cc, int32_
     const int c = (int)(t / n_tiles), tile = (int)(t % n_tiles);
     const CellConst k = cc[c];
     const int32_t ka = k_first + tile * tile_points;
-    const int32_t kb = min(k_first + n_band, ka + tile_points) - 1;
+    const int32_t kb = ka + min(k_first + n_band - ka, tile_points) - 1;
     const double nu_a = g.nu_min + (double)ka * g.h - g.h;
     const double nu_b = g.nu_min + (double)kb * g.h + g.h;
     double lo = (nu_a - k.cand_G) / (1.0 + k.cand_A);
@@ -1078,8 +1078,9 @@ void accum_f32_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t kk = kt + kw + kSliceStep * j + lane;
-        if (kk < kend) {
+        const int32_t loc = kw + kSliceStep * j + lane;
+        if (loc < kend - kt) {
+            const int32_t kk = kt + loc;
             const int64_t o = (int64_t)c * n_band + (kk - k_first);
             if (ct.n_thr >= 0) {
                 // atomic continuum, added in double precision and rounded once
@@ -1372,8 +1373,9 @@ void accum_f64_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t kq = kt + kw + kSliceStep * j + lane;
-        if (kq < kend) {
+        const int32_t loc = kw + kSliceStep * j + lane;
+        if (loc < kend - kt) {
+            const int32_t kq = kt + loc;
             const int64_t o = (int64_t)c * n_band + (kq - k_first);
             if (ct.n_thr >= 0) {   // atomic continuum
                 double ce, ck;
@@ -1565,7 +1567,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
                 for (int j = 0; j < kPPL; ++j) {
                     // (recomputed per cell: the per-point parts hoisted out of
                     // the cell loop would be spilled across the accumulation)
-                    int32_t kk = kt + kw + kSliceStep * j + lane;
+                    uint32_t kk = (uint32_t)(kt + kw) + (uint32_t)(kSliceStep * j + lane);
                     asm volatile("" : "+v"(kk));
                     const double nu = g.nu_min + (double)kk * g.h;
                     double ce, ck;
@@ -1655,7 +1657,7 @@ hipError_t launch_ranges(const DevLines &L, const DevGrid &g, const CellConst *c
                          int32_t k_first, int32_t n_band, int32_t tile_points, int2 *ranges,
                          hipStream_t st)
 {
-    const int32_t n_tiles = (n_band + tile_points - 1) / tile_points;
+    const int32_t n_tiles = tiles_of(n_band, tile_points);
     const int64_t n = (int64_t)n_cells * n_tiles;
     hipLaunchKernelGGL(ranges_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, L, g, cc,
                        n_cells, k_first, n_band, tile_points, n_tiles, ranges);
@@ -1692,7 +1694,7 @@ hipError_t launch_accum_f32(const DevLines &L, const DevGrid &g, const CellConst
                             int32_t n_cells, int32_t n_species, int32_t k_first, int32_t n_band,
                             const DevCont &ct, float *eta, float *kappa, hipStream_t st)
 {
-    const int32_t n_tiles = (n_band + kTilePoints - 1) / kTilePoints;
+    const int32_t n_tiles = tiles_of(n_band, kTilePoints);
     const int64_t n_blocks = (int64_t)n_tiles * n_cells;
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
     const int groups = accum_groups(n_blocks, L.n, g.n_points, true);
@@ -1714,7 +1716,7 @@ hipError_t launch_accum_f64(const DevLines &L, const DevGrid &g, const CellConst
                             int32_t n_species, int32_t k_first, int32_t n_band, const DevCont &ct,
                             double *eta, double *kappa, hipStream_t st)
 {
-    const int32_t n_tiles = (n_band + kTileF64 - 1) / kTileF64;
+    const int32_t n_tiles = tiles_of(n_band, kTileF64);
     const int64_t n_blocks = (int64_t)n_tiles * n_cells;
     if (n_blocks > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
     const int groups = accum_groups(n_blocks, L.n, g.n_points, false);

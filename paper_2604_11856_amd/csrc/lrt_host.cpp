@@ -914,7 +914,7 @@ lrt_status coeffs_range(lrt_ctx *c, int32_t k_first, int32_t n_band, lrt_precisi
     lrt_status r;
     if ((r = prepare(c, st, prec == LRT_FP32_COMP))) return r;
     const int32_t tile = prec == LRT_FP64 ? kTileF64 : kTilePoints;
-    const int32_t n_tiles = (n_band + tile - 1) / tile;
+    const int32_t n_tiles = tiles_of(n_band, tile);
     if ((r = ensure(c, c->w_ranges, (size_t)c->n_cells * n_tiles * sizeof(int2)))) return r;
     const DevLines L = dev_lines(c);
     const DevGrid g = dev_grid(c);

@@ -143,7 +143,7 @@ struct Epoch {
 size_t request_bytes(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t cr_row, int32_t chunk_cells,
                      int32_t &n_tiles, int32_t &n_chunks)
 {
-    n_tiles = (n_window + kTilePoints - 1) / kTilePoints;
+    n_tiles = tiles_of(n_window, kTilePoints);
     n_chunks = (int32_t)((nc + chunk_cells - 1) / chunk_cells);
     size_t b = 0;
     b += 4 * align_up(nc * 8);                              // T_tr, T_v, n_e, ds
@@ -169,7 +169,7 @@ size_t request_bytes(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t
 // the longest.
 int32_t chunk_cells_of(int64_t nc, int S, int32_t n_window, int32_t n_thr, int32_t cr_row, size_t budget)
 {
-    const int64_t tiles = (n_window + kTilePoints - 1) / kTilePoints;
+    const int64_t tiles = tiles_of(n_window, kTilePoints);
     const int64_t most = nc * tiles / kMinItems;
     const int32_t c = (int32_t)std::max<int64_t>(kMinChunkCells, std::min<int64_t>(kChunkCells, most));
     int32_t t, m;
