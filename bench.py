@@ -202,7 +202,7 @@ def band_bench(args):
 # Sources of the accumulation and march kernels; a committed counter summary
 # records the sha256 of its kernel's sources (in this order).
 ACCUM_SOURCES = ("lrt_accum.hip", "lrt_nodes.h", "lrt_math.h", "lrt_device.h", "lrt_internal.h")
-MARCH_SOURCES = ("lrt_march.hip", "lrt_device.h", "lrt_internal.h")
+MARCH_SOURCES = ("lrt_march.hip", "lrt_math.h", "lrt_device.h", "lrt_internal.h")
 
 
 def sources_sha256(sources):

@@ -182,7 +182,6 @@ __device__ __forceinline__ T line_at(const T *a, int64_t i0, uint32_t t)
     return *(const T *)((const char *)(a + i0) + t * (uint32_t)sizeof(T));
 }
 
-// Line i0 + t of the list, i0 the same for the whole wave.
 // The line list's pointers and a cell's constants, read again (scalar loads) for
 // every round of setups: held across the kernel they do not fit in the scalar
 // registers beside the masks, and come back from spills by one vector
@@ -277,7 +276,7 @@ __device__ __forceinline__ bool pair_setup(const DevLines &L, const DevGrid &g, 
         p.khi = (int32_t)hi;
     }
     {
-        // core: a superset of the points within 25 gamma_V (one point of
+        // core: a superset of the points within kCoreHalfWidth gamma_V (one point of
         // margin on each side covers the rounding of the product by 1/h)
         const double Wc = kCoreHalfWidth * gV;
         double clo = fmax(ceil((nu0 - Wc - g.nu_min) * g.inv_h) - 1.0, lo);

@@ -50,10 +50,15 @@ constexpr int kEpochStreams = 2;
 // Cells of a request's work item.  Long chunks write and compose fewer
 // transmittances; short ones give a request enough workgroups for the chip: a
 // request takes the largest chunk of at most kChunkCells that makes kMinItems
-// items, but no less than kMinChunkCells (a linear-j chunk evaluates one cell
-// more than it owns).  Alone, 190 cells on 28,000 points took 6.2 ms as 330 items
+// items, but no less than kMinChunkCells.  Alone, 190 cells on 28,000 points took 6.2 ms as 330 items
 // of 32 cells, 3.4 as 1,024, 2.9 as 2,048 and 2.6 as 2,600 of 4 cells (the least);
 // 3.5 with chunks of down to one cell.  Sixteen mixed requests: 45 and 41 ms.
+// A linear-j chunk evaluates one cell more than it owns.  With at least 4 / 8 / 16 /
+// 32 cells such a request of 190 cells takes 1.94 / 2.07 / 2.76 / 4.66 ms alone; 64
+// small ones together 24.3 / 23.8 / 24.7 / 29.1, sixteen mixed ones 23.8 / 22.5 /
+// 22.1 / 23.5, 32 of 100 to 300 cells, which fill the chip many times over, 89.9 /
+// 85.5 / 81.7 / 81.8 (cell-constant 78.0 / 77.4 / 77.4 / 79.5).  The length cannot
+// follow the load, so a full server gives up to 10 % for a lone request's 2.4 times.
 constexpr int32_t kChunkCells = 32, kMinChunkCells = 4;
 constexpr int64_t kMinItems = 4096;
 constexpr int kEpochCap = 32768;            // items per epoch at most
