@@ -768,21 +768,23 @@ lrt_status prepare_lines(lrt_ctx *c)
         // nu0 = nu_min + k0 h + frac0 with frac0 correctly rounded: k0 h and
         // nu_min + k0 h are carried as unevaluated sums (two-product by fma,
         // two-sum), so frac0 is the difference of nu0 and the exact grid point.
-        // k0 is clamped only where it leaves the index type, farther from any
-        // grid point than the grid is long: (k - k0) h and frac0 then have one sign
-        // and do not cancel in the kernels.
+        // k0 is clamped only where it, or its difference from a grid index, leaves
+        // the index type.  No grid point lies between the clamped index and the
+        // line then: (k - k0) h and frac0 have one sign and do not cancel in the
+        // kernels.
         const int64_t n = c->n_lines;
+        const double nu_min = c->nu_min, h = c->h, *line_nu0 = c->h_nu0.data();
+        const double k_lo = (double)c->n_points - 2147483648.0, k_hi = 2147483647.0;
         std::vector<int32_t> k0(n);
         std::vector<double> fr(n);
         for (int64_t i = 0; i < n; ++i) {
-            const double nu0 = c->h_nu0[i];
-            double kk = std::nearbyint((nu0 - c->nu_min) / c->h);
-            kk = std::max(-2147483647.0, std::min(2147483647.0, kk));
-            const double p = kk * c->h;
-            const double pe = std::fma(kk, c->h, -p);
-            const double s = c->nu_min + p;
-            const double bb = s - c->nu_min;
-            const double se = (c->nu_min - (s - bb)) + (p - bb);
+            const double nu0 = line_nu0[i];
+            const double kk = std::max(k_lo, std::min(k_hi, std::nearbyint((nu0 - nu_min) / h)));
+            const double p = kk * h;
+            const double pe = std::fma(kk, h, -p);
+            const double s = nu_min + p;
+            const double bb = s - nu_min;
+            const double se = (nu_min - (s - bb)) + (p - bb);
             fr[i] = (nu0 - s) - (se + pe);
             k0[i] = (int32_t)kk;
         }
