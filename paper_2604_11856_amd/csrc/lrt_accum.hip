@@ -915,8 +915,8 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
                 const double frac0 = line_at(L.frac0, base, t);
-                // (the difference of two indices, up to 2^32)
-                rp.k0f = (float)((double)line_at(L.k0, base, t) - (double)kt);
+                const int32_t k0 = line_at(L.k0, base, t) - kt;
+                rp.k0f = (float)k0;
                 rp.hg = (float)(2.0 * g.h * p.inv2g);
                 rp.fg = (float)(2.0 * frac0 * p.inv2g);
                 // profile divided by s = r, strengths times s
@@ -1077,10 +1077,9 @@ void accum_f32_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t loc = kw + kSliceStep * j + lane;
-        if (loc < kend - kt) {
-            const int32_t kk = kt + loc;
-            const int64_t o = (int64_t)c * n_band + (kk - k_first);
+        const uint32_t kk = (uint32_t)kt + (uint32_t)(kw + kSliceStep * j + lane);   // (may pass 2^31)
+        if (kk < (uint32_t)kend) {
+            const int64_t o = (int64_t)c * n_band + (int32_t)(kk - (uint32_t)k_first);
             if (ct.n_thr >= 0) {
                 // atomic continuum, added in double precision and rounded once
                 double ce, ck;
@@ -1264,7 +1263,7 @@ void accum_f64_kernel(
             const CellConst &k = reread(&kc);
             if (pair_setup(L, g, k, csc, lnd_c, base, t, p)) {
                 const int32_t lo = p.klo - kt, hi = p.khi - kt;
-                rp.k0 = (double)line_at(L.k0, base, t) - (double)kt;
+                rp.k0 = (double)(line_at(L.k0, base, t) - kt);
                 const double frac0 = line_at(L.frac0, base, t);
                 rp.h2 = g.h * p.inv2g;
                 rp.f2 = frac0 * p.inv2g;
@@ -1372,10 +1371,9 @@ void accum_f64_kernel(
     if (group > 0) return;
 #pragma unroll
     for (int j = 0; j < kPPL; ++j) {
-        const int32_t loc = kw + kSliceStep * j + lane;
-        if (loc < kend - kt) {
-            const int32_t kq = kt + loc;
-            const int64_t o = (int64_t)c * n_band + (kq - k_first);
+        const uint32_t kq = (uint32_t)kt + (uint32_t)(kw + kSliceStep * j + lane);   // (may pass 2^31)
+        if (kq < (uint32_t)kend) {
+            const int64_t o = (int64_t)c * n_band + (int32_t)(kq - (uint32_t)k_first);
             if (ct.n_thr >= 0) {   // atomic continuum
                 double ce, ck;
                 continuum_point(ct, c, g.nu_min + (double)kq * g.h, ce, ck);
@@ -1566,7 +1564,7 @@ void serve_kernel(DevLines L, DevGrid g, const ServeReq *reqs, const ServeItem *
                 for (int j = 0; j < kPPL; ++j) {
                     // (recomputed per cell: the per-point parts hoisted out of
                     // the cell loop would be spilled across the accumulation)
-                    uint32_t kk = (uint32_t)(kt + kw) + (uint32_t)(kSliceStep * j + lane);
+                    uint32_t kk = (uint32_t)kt + (uint32_t)(kw + kSliceStep * j + lane);
                     asm volatile("" : "+v"(kk));
                     const double nu = g.nu_min + (double)kk * g.h;
                     double ce, ck;

@@ -46,8 +46,8 @@ constexpr int kStage = kAccumThreads;
 // Double-precision accumulation: 512-point tiles, 256 threads.
 constexpr int kThreadsF64 = 256;
 constexpr int kTileF64 = kThreadsF64 * kPPL;
-// Tiles of a band.  (A grid has up to 2^31 - 1 points: what lies past a band's last
-// point is counted from the tile's or the chunk's first, never as a grid index.)
+// Tiles of a band.  (A grid has up to 2^31 - 1 points: an index past a band's last
+// point can pass the signed type's range.)
 inline int32_t tiles_of(int32_t n_band, int32_t tile) { return (int32_t)((int64_t(n_band) + tile - 1) / tile); }
 
 // Groups of 4 waves per accumulation workgroup.  A workgroup's groups take its
