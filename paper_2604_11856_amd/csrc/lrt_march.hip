@@ -155,10 +155,10 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
     [[maybe_unused]] double pds = 0.0;
     // one linear-j segment from node (fe, fk) to node ne, lengths scaled by the
     // nodes' powers of two (Lf = Ln = L and Lk = L in double precision).  Where many
-    // rays keep the vector units busy (256-point chunks, four rays) a point at
-    // which the whole wave is thin takes the series alone, and the points one after
-    // the other need fewer registers; few rays wait for the vote instead.
-    constexpr bool kThinVote = FP32 && PPT == 4 && RAYS == 4;
+    // waves keep the vector units busy (256-point chunks) a point at which the whole
+    // wave is thin takes the series alone, and the points one after the other need
+    // fewer registers; few waves would wait for the vote instead.
+    constexpr bool kThinVote = FP32 && PPT == 4;
     [[maybe_unused]] auto linear_segment = [&](const T (&fe)[PPT], const T (&fk)[PPT], const T (&ne)[PPT], double Lf,
                                                double Ln, T Lk) {
 #pragma unroll
