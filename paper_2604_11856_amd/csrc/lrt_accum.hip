@@ -896,6 +896,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         se[j] = sk[j] = 0.0;
         ae[j] = ak[j] = 0.0f;
     }
+    uint32_t used = 0u;   // intervals that have taken a line's nodes
     for (int b0 = rg.x; b0 < rg.y; b0 += kGroups * kStage) {
         const int base = b0 + group * kStage;
         // stage: one (cell, line) setup per thread, in double precision
@@ -950,6 +951,8 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         uint32_t of[kBlocks];
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)sm.any[b]);
+        const uint32_t in_nodes = (of[0] | of[1] | of[2] | of[3]) >> 8;
+        used |= in_nodes;
         auto blocks_of = [&](uint32_t bits) {
             uint32_t m = 0u;
 #pragma unroll
@@ -1004,7 +1007,7 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         // level l interval wave >> (l-1), whose blocks of lines the 2^(l-1)
         // waves wave>>(l-1) << (l-1) on share.
 #pragma unroll 1
-        for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
+        for (int j = 0; j < (in_nodes ? kSets : 0); ++j) {
             const int l = max(0, j - (kPPL - 1));
             const uint32_t it = l > 0 ? wave >> (l - 1) : (uint32_t)(wave + kWaves * j);
             const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
@@ -1028,8 +1031,9 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         }
         __syncthreads();
     }
-    // node sums to the points
-    if (at_nodes) {
+    // node sums to the points (the same choice in all waves; groups have rounds of
+    // their own)
+    if (at_nodes && (kGroups > 1 || used)) {
         nodes_down<kNodes, kAccumThreads>(sm.node, kBasis, tid);
 #pragma unroll 8
         for (int q = 0; q < kNodes; ++q) {
@@ -1250,6 +1254,7 @@ void accum_f64_kernel(
             if ((lane & 31) == i) x64 = kNodePos64[i];
     }
 
+    uint32_t used = 0u;
     for (int b0r = rg.x; b0r < rg.y; b0r += kGroups * kThreadsF64) {
         const int base = b0r + group * kThreadsF64;
         RecPos64 rp{0.0, 0.0, 0.0, 0.0};
@@ -1290,6 +1295,8 @@ void accum_f64_kernel(
         uint32_t of[kBlocks];
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b) of[b] = (uint32_t)uniform_i((int32_t)sm.any[b]);
+        const uint32_t in_nodes = (of[0] | of[1] | of[2] | of[3]) >> 8;
+        used |= in_nodes;
         auto blocks_of = [&](uint32_t bits) {
             uint32_t m = 0u;
 #pragma unroll
@@ -1331,7 +1338,7 @@ void accum_f64_kernel(
         }
         // nodes, as the single-precision form
 #pragma unroll 1
-        for (int j = 0; j < (at_nodes ? kSets : 0); ++j) {
+        for (int j = 0; j < (in_nodes ? kSets : 0); ++j) {
             const int l = max(0, j - (kPPL - 1));
             const uint32_t it = l > 0 ? (uint32_t)wave >> (l - 1) : (uint32_t)(wave + kWaves * j);
             const uint32_t bit = 1u << (node_bit0(l) + it), wbit = 1u << (16 + l);
@@ -1354,7 +1361,7 @@ void accum_f64_kernel(
         }
         __syncthreads();
     }
-    if (at_nodes) {
+    if (at_nodes && (kGroups > 1 || used)) {
         nodes_down<kNodes64, kThreadsF64>(sm.node, kBasis64, tid);
 #pragma unroll 4
         for (int q = 0; q < kNodes64; ++q) {
