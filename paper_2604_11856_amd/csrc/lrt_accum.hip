@@ -1031,8 +1031,9 @@ __device__ __forceinline__ void accum_cell_tile_f32(AccumLds *sg, int group, int
         }
         __syncthreads();
     }
-    // node sums to the points (the same choice in all waves; groups have rounds of
-    // their own)
+    // node sums to the points, where there are any: with windows of 40 to 90 points
+    // no line takes nodes (32,768 cells x 65,536 points 163 -> 144 ms).  All waves
+    // have seen the same masks; several groups have seen different ones.
     if (at_nodes && (kGroups > 1 || used)) {
         nodes_down<kNodes, kAccumThreads>(sm.node, kBasis, tid);
 #pragma unroll 8
